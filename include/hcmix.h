@@ -38,10 +38,10 @@
  * pointers).  HCMIX_ERR_HIP: a HIP call or kernel launch failed; the message
  * is available from hcmix_last_hip_error().
  *
- * Kernels of the mixing layer: bf16 widths that are a multiple of 64 run on
- * matrix-core (MFMA) kernels; fp32 and the other bf16 widths (multiples of 8)
- * run on fp32 FMA kernels.  Both accumulate in fp32 and round each bf16
- * output once, so they agree up to the order of summation.
+ * Kernels of the mixing layer: matrix-core (MFMA) kernels for both types and
+ * every width, bf16 operands on the bf16 instructions (widths that are not a
+ * multiple of 64 padded with zeros on chip), fp32 operands on the fp32 ones.
+ * All accumulate in fp32 and round each bf16 output once.
  */
 #ifndef HCMIX_H
 #define HCMIX_H
@@ -183,8 +183,12 @@ hcmix_status hcmix_stack_forward(int64_t batch, int64_t n, int64_t width, int32_
  *    weight-gradient launch when the stack is too short to fill the chip
  *    (hcmix_stack_weight_gradients_workspace_bytes).
  *  - fused path: the per-window weight-gradient partials;
+ *  - fp32, and bf16 widths that are not a multiple of 64: the intermediate
+ *    gradients of as many layers as 1 GiB holds (at least two buffers) and the
+ *    row-range partials of those layers' weight gradients.  The backward also
+ *    runs, slower, on two gradient buffers alone (none for one layer);
  *  - otherwise, layer by layer: two gradient buffers, the split-K partials of
- *    one layer and (bf16, two or more layers) the transposed weights. */
+ *    one layer and (two or more layers) the transposed weights. */
 size_t hcmix_stack_backward_workspace_bytes(int64_t batch, int64_t n, int64_t width,
                                             int32_t num_layers, int32_t dtype);
 
@@ -217,8 +221,9 @@ hcmix_status hcmix_stack_backward(int64_t batch, int64_t n, int64_t width, int32
  * any input or another output.  bf16 with width a multiple of 128: one launch
  * per 64 layers whose blocks each own a 128 x 128 tile of both matrices over
  * every row (or, when layers x tiles cannot fill the chip, over a row range,
- * plus a fixed-order sum of the ranges); other shapes: the per-layer kernels
- * of hcmix_backward.  Bitwise-repeatable.  The workspace (256-byte aligned,
+ * plus a fixed-order sum of the ranges); fp32 and widths that are not a
+ * multiple of 64: the same scheme, running without the workspace too (no row
+ * ranges then); other shapes: the per-layer kernels of hcmix_backward.  Bitwise-repeatable.  The workspace (256-byte aligned,
  * hcmix_stack_weight_gradients_workspace_bytes, possibly 0) holds those
  * partial sums. */
 size_t hcmix_stack_weight_gradients_workspace_bytes(int64_t batch, int64_t n, int64_t width,

@@ -53,14 +53,15 @@ hcmix_status check_shape(int64_t batch, int64_t n, int64_t width, int32_t layer,
   return HCMIX_OK;
 }
 
-// bf16 widths that are a multiple of 64 run on the MFMA kernels; fp32, and
-// bf16 widths that are only a multiple of 8, on the FMA kernels.
-bool mfma_path(int32_t dtype, int64_t width) { return dtype == HCMIX_BF16 && width % 64 == 0; }
+// bf16 widths that are a multiple of 64 fill the bf16 kernels' tiles.  fp32 and
+// the other bf16 widths take a workspace only in a stack's backward, and run
+// with less of it too (see RingPlan): a single layer's backward uses none.
+bool whole_width(int32_t dtype, int64_t width) { return dtype == HCMIX_BF16 && width % 64 == 0; }
 
 // Backward workspace (bf16): the split-K partial sums of the weight
 // gradients, [splits][2][width][width] fp32.
 size_t layer_workspace_bytes(int64_t batch, int64_t n, int64_t width, int32_t dtype) {
-  if (!mfma_path(dtype, width)) return 0;
+  if (!whole_width(dtype, width)) return 0;
   const int splits = dw_bf16_splits((int)(batch * n), (int)width);
   return align256((size_t)splits * 2 * width * width * sizeof(float));
 }
@@ -69,7 +70,7 @@ size_t layer_workspace_bytes(int64_t batch, int64_t n, int64_t width, int32_t dt
 // or more layers on the layer-by-layer path): dX then multiplies by W^T with
 // the same kernel and the same 128-bit fragment reads as the forward.
 size_t transposed_weight_bytes(int64_t width, int32_t num_layers, int32_t dtype) {
-  if (!mfma_path(dtype, width) || num_layers < 2) return 0;
+  if (!whole_width(dtype, width) || num_layers < 2) return 0;
   return align256((size_t)2 * num_layers * width * width * sizeof(bf16));
 }
 
@@ -96,8 +97,57 @@ size_t batch_partial_bytes(int64_t rows, int64_t width, int32_t chunk) {
   return splits > 1 ? align256((size_t)chunk * splits * 2 * width * width * sizeof(float)) : 0;
 }
 
+// Backward of an fp32 stack, or of bf16 layers whose width is not a multiple
+// of 64: `chunk` layers' dX at a time, keeping their gradients in a ring of
+// `ring` buffers, then those layers' weight gradients in one launch over
+// `splits` row ranges each.  As many layers at once as 1 GiB of gradients
+// allows: a launch of 64 x 64 tiles over one narrow layer leaves most of the
+// chip idle (8 fp32 layers of 4096 x 256: 32 blocks per layer).  `splits`
+// depends on the call's shape and depth alone, so the sums do not depend on
+// how the layers are chunked.
+struct RingPlan {
+  int chunk, ring, splits;
+  size_t act, bytes;      // one gradient buffer; the whole workspace
+};
+
+int stack_dw_splits(int64_t rows, int64_t width, int32_t num_layers, int32_t dtype) {
+  const int L = num_layers < kBatchMaxLayers ? num_layers : kBatchMaxLayers;
+  return dtype == HCMIX_BF16 ? dw_batch_splits((int)rows, (int)width, L)
+                             : dw_f32_splits((int)rows, (int)width, L);
+}
+
+size_t stack_dw_partial_bytes(int splits, int64_t width, int layers) {
+  return splits > 1 ? align256((size_t)layers * splits * 2 * width * width * sizeof(float)) : 0;
+}
+
+// The least workspace: two gradient buffers (none for one layer), one layer at
+// a time and no partial sums.
+RingPlan least_ring_plan(int64_t batch, int64_t n, int64_t width, int32_t num_layers,
+                         int32_t dtype) {
+  RingPlan p;
+  p.act = align256((size_t)(batch * n * width) * elem_size(dtype));
+  p.chunk = 1;
+  p.ring = num_layers - 1 < 2 ? num_layers - 1 : 2;
+  p.splits = 1;
+  p.bytes = num_layers > 1 ? 2 * p.act : 0;
+  return p;
+}
+
+RingPlan ring_plan(int64_t batch, int64_t n, int64_t width, int32_t num_layers, int32_t dtype) {
+  RingPlan p = least_ring_plan(batch, n, width, num_layers, dtype);
+  const size_t least = p.bytes, fit = ((size_t)1 << 30) / p.act;
+  int most = num_layers < kBatchMaxLayers ? num_layers : kBatchMaxLayers;
+  p.chunk = fit < 1 ? 1 : fit < (size_t)most ? (int)fit : most;
+  p.ring = num_layers - 1 < p.chunk + 1 ? num_layers - 1 : p.chunk + 1;
+  p.splits = stack_dw_splits(batch * n, width, num_layers, dtype);
+  p.bytes = (size_t)p.ring * p.act + stack_dw_partial_bytes(p.splits, width, p.chunk);
+  if (p.bytes < least) p.bytes = least;
+  return p;
+}
+
 // Workspace of hcmix_stack_weight_gradients: the batched launch's partials
-// (bf16, width a multiple of 128), else one layer's split-K partials.
+// (bf16, width a multiple of 128; fp32; ragged bf16 widths), else one layer's
+// split-K partials.
 size_t weight_grad_workspace_bytes(int64_t batch, int64_t n, int64_t width, int32_t num_layers,
                                    int32_t dtype) {
   if (dtype == HCMIX_BF16 && width % 128 == 0) {
@@ -109,6 +159,10 @@ size_t weight_grad_workspace_bytes(int64_t batch, int64_t n, int64_t width, int3
     }
     return part;
   }
+  if (!whole_width(dtype, width))
+    return stack_dw_partial_bytes(
+        stack_dw_splits(batch * n, width, num_layers, dtype), width,
+        num_layers < kBatchMaxLayers ? num_layers : kBatchMaxLayers);
   return layer_workspace_bytes(batch, n, width, dtype);
 }
 
@@ -120,13 +174,14 @@ size_t deferred_workspace_bytes(int64_t batch, int64_t n, int64_t width, int32_t
 }
 
 // Stack backward workspace: the deferred path's gradients, transposed weights
-// and partials; the per-window partials of the fused path; or two gradient
+// and partials; the per-window partials of the fused path; two gradient
 // buffers, one layer's partials and the transposed weights for the
-// layer-by-layer path.
+// layer-by-layer path; or the ring plan's.
 size_t stack_workspace_bytes(int64_t batch, int64_t n, int64_t width, int32_t num_layers,
                              int32_t dtype) {
   if (deferred_dw(width, num_layers, dtype))
     return deferred_workspace_bytes(batch, n, width, num_layers);
+  if (!whole_width(dtype, width)) return ring_plan(batch, n, width, num_layers, dtype).bytes;
   const size_t act = align256((size_t)(batch * n * width) * elem_size(dtype));
   const size_t layered = (num_layers > 1 ? 2 * act : 0) +
                          layer_workspace_bytes(batch, n, width, dtype) +
@@ -152,7 +207,7 @@ bool any_local_layer(const int32_t* layers, int32_t num_layers) {
 // d >= 0: hypercube layer of dimension d; d < 0: the local layer (jump 1).
 hipError_t run_forward(int rows, int w, int d, int n, int bidir, int32_t dtype, const void* x,
                        const void* w_self, const void* w_off, void* y, hipStream_t s) {
-  if (mfma_path(dtype, w)) {
+  if (dtype == HCMIX_BF16) {
     if (d < 0)
       return launch_shift_bf16((const bf16*)x, (const bf16*)w_self, (const bf16*)w_off, (bf16*)y,
                                rows, w, n, /*delta=*/-1, /*transpose_b=*/false, s);
@@ -160,8 +215,8 @@ hipError_t run_forward(int rows, int w, int d, int n, int bidir, int32_t dtype, 
                            rows, w, d, /*partner_lower=*/bidir, /*partner_upper=*/1,
                            /*transpose_b=*/false, s);
   }
-  return launch_mix_fma(x, w_self, w_off, y, rows, w, d, bidir, 1, n, /*shift=*/-1,
-                        /*transpose_w=*/false, dtype == HCMIX_BF16, s);
+  return launch_mix_f32((const float*)x, (const float*)w_self, (const float*)w_off, (float*)y,
+                        rows, w, d, bidir, 1, n, /*shift=*/-1, /*transpose_w=*/false, s);
 }
 
 // dX of one bf16 layer with the weights read as given (transpose_b) or from
@@ -175,25 +230,67 @@ hipError_t run_dx_bf16(int rows, int w, int d, int n, int bidir, const bf16* dy,
                          /*partner_upper=*/bidir, transpose_b, s);
 }
 
-hipError_t run_backward(int rows, int w, int d, int n, int bidir, int32_t dtype, const void* x,
-                        const void* w_self, const void* w_off, const void* dy, void* dx,
-                        float* dw_self, float* dw_off, int accumulate, void* workspace,
-                        hipStream_t s) {
-  hipError_t e;
-  if (mfma_path(dtype, w)) {
-    e = run_dx_bf16(rows, w, d, n, bidir, (const bf16*)dy, (const bf16*)w_self,
-                    (const bf16*)w_off, (bf16*)dx, /*transpose_b=*/true, s);
-    if (e == hipSuccess)
-      e = launch_dw_bf16((const bf16*)x, (const bf16*)dy, (float*)workspace, dw_self, dw_off,
-                         rows, w, d, n, bidir, accumulate, s);
-  } else {
-    const bool b16 = dtype == HCMIX_BF16;
-    e = launch_mix_fma(dy, w_self, w_off, dx, rows, w, d, 1, bidir, n, /*shift=*/1,
-                       /*transpose_w=*/true, b16, s);
-    if (e == hipSuccess)
-      e = launch_dw_fma(x, dy, dw_self, dw_off, rows, w, d, n, bidir, accumulate, b16, s);
+// dX of one layer with the weights as given.
+hipError_t run_dx(int rows, int w, int d, int n, int bidir, int32_t dtype, const void* dy,
+                  const void* w_self, const void* w_off, void* dx, hipStream_t s) {
+  if (dtype == HCMIX_BF16)
+    return run_dx_bf16(rows, w, d, n, bidir, (const bf16*)dy, (const bf16*)w_self,
+                       (const bf16*)w_off, (bf16*)dx, /*transpose_b=*/true, s);
+  return launch_mix_f32((const float*)dy, (const float*)w_self, (const float*)w_off, (float*)dx,
+                        rows, w, d, 1, bidir, n, /*shift=*/1, /*transpose_w=*/true, s);
+}
+
+// Weight gradients of up to kBatchMaxLayers layers in one launch (fp32, or
+// bf16 widths without split-K of their own); `partial` holds the sums of
+// `splits` row ranges per layer.
+template <typename E>
+DwBatch<E> dw_chunk_args(int rows, int w, int n, int count, const int32_t* layers, int bidir,
+                         const void* const* xs_in, const void* const* gs, float* const* dw_self,
+                         float* const* dw_off, int accumulate, float* partial, int splits) {
+  DwBatch<E> a = {};
+  for (int l = 0; l < count; l++) {
+    a.x[l] = (const E*)xs_in[l];
+    a.dy[l] = (const E*)gs[l];
+    a.dws[l] = dw_self[l];
+    a.dwo[l] = dw_off[l];
+    a.dim[l] = hcmix_dim(layers[l], n);   // -1 for the local layer
   }
-  return e;
+  a.partial = partial;
+  a.rows = rows;
+  a.width = w;
+  a.n = n;
+  a.num_layers = count;
+  a.splits = splits;
+  a.bidir = bidir;
+  a.accumulate = accumulate;
+  return a;
+}
+
+hipError_t launch_dw_chunk(int rows, int w, int n, int count, const int32_t* layers, int bidir,
+                           int32_t dtype, const void* const* xs_in, const void* const* gs,
+                           float* const* dw_self, float* const* dw_off, int accumulate,
+                           float* partial, int splits, hipStream_t s) {
+  if (dtype == HCMIX_BF16)
+    return launch_dw_batch_bf16(dw_chunk_args<bf16>(rows, w, n, count, layers, bidir, xs_in, gs,
+                                                    dw_self, dw_off, accumulate, partial, splits),
+                                s);
+  return launch_dw_f32(dw_chunk_args<float>(rows, w, n, count, layers, bidir, xs_in, gs, dw_self,
+                                            dw_off, accumulate, partial, splits),
+                       s);
+}
+
+hipError_t run_backward(int rows, int w, int32_t layer, int n, int bidir, int32_t dtype,
+                        const void* x, const void* w_self, const void* w_off, const void* dy,
+                        void* dx, float* dw_self, float* dw_off, int accumulate, void* workspace,
+                        hipStream_t s) {
+  const int d = hcmix_dim(layer, n);
+  const hipError_t e = run_dx(rows, w, d, n, bidir, dtype, dy, w_self, w_off, dx, s);
+  if (e != hipSuccess) return e;
+  if (whole_width(dtype, w))
+    return launch_dw_bf16((const bf16*)x, (const bf16*)dy, (float*)workspace, dw_self, dw_off,
+                          rows, w, d, n, bidir, accumulate, s);
+  return launch_dw_chunk(rows, w, n, 1, &layer, bidir, dtype, &x, &dy, &dw_self, &dw_off,
+                         accumulate, nullptr, /*splits=*/1, s);
 }
 
 // A buffer in a call: its address and extent in bytes.
@@ -244,31 +341,6 @@ hipError_t transpose_weights(int w, int32_t num_layers, const void* const* w_sel
   return e;
 }
 
-// Weight gradients of up to kBatchMaxLayers bf16 layers (width a multiple of
-// 128) in one launch; `partial` is the workspace for split row ranges.
-hipError_t launch_dw_chunk(int rows, int w, int n, int count, const int32_t* layers, int bidir,
-                           const void* const* xs_in, const void* const* gs,
-                           float* const* dw_self, float* const* dw_off, int accumulate,
-                           float* partial, hipStream_t s) {
-  DwBatchArgs a = {};
-  for (int l = 0; l < count; l++) {
-    a.x[l] = (const bf16*)xs_in[l];
-    a.dy[l] = (const bf16*)gs[l];
-    a.dws[l] = dw_self[l];
-    a.dwo[l] = dw_off[l];
-    a.dim[l] = hcmix_dim(layers[l], n);   // -1 for the local layer
-  }
-  a.partial = partial;
-  a.rows = rows;
-  a.width = w;
-  a.n = n;
-  a.num_layers = count;
-  a.splits = dw_batch_splits(rows, w, count);
-  a.bidir = bidir;
-  a.accumulate = accumulate;
-  return launch_dw_batch_bf16(a, s);
-}
-
 // The deferred path (arguments validated; workspace laid out as
 // deferred_workspace_bytes counts it): gradients, transposed weights, partials.
 hipError_t stack_backward_deferred(int rows, int w, int n, int32_t num_layers,
@@ -299,8 +371,40 @@ hipError_t stack_backward_deferred(int rows, int w, int n, int32_t num_layers,
     if (e != hipSuccess) break;
     const void* gs[kBatchMaxLayers];
     for (int l = l0; l < l1; l++) gs[l - l0] = grad(l + 1);
-    e = launch_dw_chunk(rows, w, n, l1 - l0, layers + l0, bidir, xs_in + l0, gs, dw_self + l0,
-                        dw_off + l0, accumulate, partial, s);
+    e = launch_dw_chunk(rows, w, n, l1 - l0, layers + l0, bidir, HCMIX_BF16, xs_in + l0, gs,
+                        dw_self + l0, dw_off + l0, accumulate, partial,
+                        dw_batch_splits(rows, w, l1 - l0), s);
+    l1 = l0;
+  }
+  return e;
+}
+
+// The backward of a RingPlan (arguments validated): ring buffers, then the
+// partial sums.
+hipError_t stack_backward_ring(const RingPlan& p, int rows, int w, int n, int32_t num_layers,
+                               const int32_t* layers, int bidir, int32_t dtype,
+                               const void* const* xs_in, const void* dy, void* dx,
+                               const void* const* w_self, const void* const* w_off,
+                               float* const* dw_self, float* const* dw_off, int accumulate,
+                               void* workspace, hipStream_t s) {
+  char* base = (char*)workspace;
+  float* partial = (float*)(base + (size_t)p.ring * p.act);
+  // g_l: gradient of layer l's input
+  auto grad = [&](int l) -> void* {
+    if (l == num_layers) return (void*)dy;
+    return l == 0 ? dx : base + (size_t)(l % p.ring) * p.act;
+  };
+  hipError_t e = hipSuccess;
+  for (int l1 = num_layers; l1 > 0 && e == hipSuccess;) {
+    const int l0 = l1 > p.chunk ? l1 - p.chunk : 0;
+    for (int l = l1 - 1; l >= l0 && e == hipSuccess; l--)
+      e = run_dx(rows, w, hcmix_dim(layers[l], n), n, bidir, dtype, grad(l + 1), w_self[l],
+                 w_off[l], grad(l), s);
+    if (e != hipSuccess) break;
+    const void* gs[kBatchMaxLayers];
+    for (int l = l0; l < l1; l++) gs[l - l0] = grad(l + 1);
+    e = launch_dw_chunk(rows, w, n, l1 - l0, layers + l0, bidir, dtype, xs_in + l0, gs,
+                        dw_self + l0, dw_off + l0, accumulate, partial, p.splits, s);
     l1 = l0;
   }
   return e;
@@ -400,7 +504,7 @@ hcmix_status hcmix_backward(int64_t batch, int64_t n, int64_t width, int32_t lay
   if (st != HCMIX_OK) return st;
   if (!aligned(dw_self, 16) || !aligned(dw_off, 16) || (need && !aligned(workspace, 256)))
     return HCMIX_ERR_UNSUPPORTED;
-  hipError_t e = run_backward((int)(batch * n), (int)width, hcmix_dim(layer, n), (int)n,
+  hipError_t e = run_backward((int)(batch * n), (int)width, layer, (int)n,
                               mode == HCMIX_BIDIR, dtype, x, w_self, w_off, dy, dx, dw_self,
                               dw_off, accumulate != 0, workspace, (hipStream_t)stream);
   return e == hipSuccess ? HCMIX_OK : hip_fail(e);
@@ -433,7 +537,7 @@ hcmix_status hcmix_backward_no_alloc(int64_t batch, int64_t n, int64_t width, in
   }
   // the split-K partials are written in full before they are read, so the
   // scratch needs no clearing
-  hipError_t e = run_backward((int)(batch * n), (int)width, hcmix_dim(layer, n), (int)n,
+  hipError_t e = run_backward((int)(batch * n), (int)width, layer, (int)n,
                               mode == HCMIX_BIDIR, dtype, x, w_self, w_off, dy, dx, dw_self,
                               dw_off, accumulate != 0, ws, (hipStream_t)stream);
   return e == hipSuccess ? HCMIX_OK : hip_fail(e);
@@ -514,41 +618,57 @@ hcmix_status hcmix_stack_backward(int64_t batch, int64_t n, int64_t width, int32
     if (!xs_in[l] || !w_self[l] || !w_off[l] || !dw_self[l] || !dw_off[l])
       return HCMIX_ERR_INVALID_VALUE;
   }
-  const size_t need = stack_workspace_bytes(batch, n, width, num_layers, dtype);
-  if (need > 0 && (!workspace || workspace_bytes < need)) return HCMIX_ERR_INVALID_VALUE;
   const size_t es = elem_size(dtype);
   const size_t act = (size_t)(batch * n * width) * es, wgt = (size_t)(width * width) * es;
   const size_t gw = (size_t)(width * width) * sizeof(float);
   const size_t al = dtype == HCMIX_BF16 ? 16 : 4;
-  // Outputs: dx, the workspace and every weight gradient.  Inputs: dy, every
-  // layer input and weight.  No output may overlap any input or other output.
-  const Span outs_fixed[2] = {{dx, act}, {workspace, need}};
-  {
-    const Span ins[1] = {{dy, act}};
-    hcmix_status st = check_spans(ins, 1, outs_fixed, 2, al);
-    if (st != HCMIX_OK) return st;
-  }
-  for (int l = 0; l < num_layers; l++) {
-    const Span ins[3] = {{xs_in[l], act}, {w_self[l], wgt}, {w_off[l], wgt}};
-    const Span outs[4] = {outs_fixed[0], outs_fixed[1], {dw_self[l], gw}, {dw_off[l], gw}};
-    hcmix_status st = check_spans(ins, 3, outs, 4, al);
-    if (st != HCMIX_OK) return st;
-    for (int j = 0; j < num_layers; j++) {
-      if (j == l) continue;
-      const Span other_ins[3] = {{xs_in[j], act}, {w_self[j], wgt}, {w_off[j], wgt}};
-      const Span other_outs[2] = {{dw_self[j], gw}, {dw_off[j], gw}};
-      for (int k = 2; k < 4; k++) {
-        for (int m = 0; m < 3; m++)
-          if (overlaps(outs[k].p, outs[k].n, other_ins[m].p, other_ins[m].n))
-            return HCMIX_ERR_INVALID_VALUE;
-        for (int m = 0; m < 2; m++)
-          if (overlaps(outs[k].p, outs[k].n, other_outs[m].p, other_outs[m].n))
-            return HCMIX_ERR_INVALID_VALUE;
-      }
+  // Outputs: dx, the workspace (`need` bytes of it) and every weight gradient.
+  // Inputs: dy, every layer input and weight.  No output may overlap any input
+  // or other output.
+  auto check = [&](size_t need) -> hcmix_status {
+    if (need > 0 && (!workspace || workspace_bytes < need)) return HCMIX_ERR_INVALID_VALUE;
+    const Span outs_fixed[2] = {{dx, act}, {workspace, need}};
+    {
+      const Span ins[1] = {{dy, act}};
+      hcmix_status st = check_spans(ins, 1, outs_fixed, 2, al);
+      if (st != HCMIX_OK) return st;
     }
-    if (!aligned(dw_self[l], 16) || !aligned(dw_off[l], 16)) return HCMIX_ERR_UNSUPPORTED;
+    for (int l = 0; l < num_layers; l++) {
+      const Span ins[3] = {{xs_in[l], act}, {w_self[l], wgt}, {w_off[l], wgt}};
+      const Span outs[4] = {outs_fixed[0], outs_fixed[1], {dw_self[l], gw}, {dw_off[l], gw}};
+      hcmix_status st = check_spans(ins, 3, outs, 4, al);
+      if (st != HCMIX_OK) return st;
+      for (int j = 0; j < num_layers; j++) {
+        if (j == l) continue;
+        const Span other_ins[3] = {{xs_in[j], act}, {w_self[j], wgt}, {w_off[j], wgt}};
+        const Span other_outs[2] = {{dw_self[j], gw}, {dw_off[j], gw}};
+        for (int k = 2; k < 4; k++) {
+          for (int m = 0; m < 3; m++)
+            if (overlaps(outs[k].p, outs[k].n, other_ins[m].p, other_ins[m].n))
+              return HCMIX_ERR_INVALID_VALUE;
+          for (int m = 0; m < 2; m++)
+            if (overlaps(outs[k].p, outs[k].n, other_outs[m].p, other_outs[m].n))
+              return HCMIX_ERR_INVALID_VALUE;
+        }
+      }
+      if (!aligned(dw_self[l], 16) || !aligned(dw_off[l], 16)) return HCMIX_ERR_UNSUPPORTED;
+    }
+    return need && !aligned(workspace, 256) ? HCMIX_ERR_UNSUPPORTED : HCMIX_OK;
+  };
+  RingPlan plan = {};
+  hcmix_status st;
+  if (whole_width(dtype, width)) {
+    st = check(stack_workspace_bytes(batch, n, width, num_layers, dtype));
+  } else {
+    // the whole plan, or the least one where the caller's workspace ends there
+    plan = ring_plan(batch, n, width, num_layers, dtype);
+    st = check(plan.bytes);
+    if (st != HCMIX_OK) {
+      plan = least_ring_plan(batch, n, width, num_layers, dtype);
+      st = check(plan.bytes);
+    }
   }
-  if (need && !aligned(workspace, 256)) return HCMIX_ERR_UNSUPPORTED;
+  if (st != HCMIX_OK) return st;
 
   const int rows = (int)(batch * n), w = (int)width;
   const int bidir = mode == HCMIX_BIDIR;
@@ -579,6 +699,9 @@ hcmix_status hcmix_stack_backward(int64_t batch, int64_t n, int64_t width, int32
   } else if (deferred_dw(width, num_layers, dtype)) {
     e = stack_backward_deferred(rows, w, (int)n, num_layers, layers, bidir, xs_in, dy, dx,
                                 w_self, w_off, dw_self, dw_off, accumulate != 0, workspace, s);
+  } else if (!whole_width(dtype, w)) {
+    e = stack_backward_ring(plan, rows, w, (int)n, num_layers, layers, bidir, dtype, xs_in, dy,
+                            dx, w_self, w_off, dw_self, dw_off, accumulate != 0, workspace, s);
   } else {
     // layer by layer; intermediate gradients ping-pong in the workspace
     const size_t act_al = align256(act);
@@ -594,7 +717,7 @@ hcmix_status hcmix_stack_backward(int64_t batch, int64_t n, int64_t width, int32
     for (int l = num_layers - 1; l >= 0 && e == hipSuccess; l--) {
       void* out = l == 0 ? dx : gbuf[l & 1];
       const int d = hcmix_dim(layers[l], n);
-      if (mfma_path(dtype, w) && num_layers > 1) {
+      if (num_layers > 1) {
         // dX = W_self^T dy (+ partner W_off^T dy): the forward kernels on W^T
         e = run_dx_bf16(rows, w, d, (int)n, bidir, (const bf16*)g, wt + 2 * (size_t)l * ww,
                         wt + (2 * (size_t)l + 1) * ww, (bf16*)out, /*transpose_b=*/false, s);
@@ -602,7 +725,7 @@ hcmix_status hcmix_stack_backward(int64_t batch, int64_t n, int64_t width, int32
           e = launch_dw_bf16((const bf16*)xs_in[l], (const bf16*)g, (float*)layer_ws, dw_self[l],
                              dw_off[l], rows, w, d, (int)n, bidir, accumulate != 0, s);
       } else {
-        e = run_backward(rows, w, d, (int)n, bidir, dtype, xs_in[l], w_self[l], w_off[l], g, out,
+        e = run_backward(rows, w, layers[l], (int)n, bidir, dtype, xs_in[l], w_self[l], w_off[l], g, out,
                          dw_self[l], dw_off[l], accumulate != 0, layer_ws, s);
       }
       g = out;
@@ -675,17 +798,11 @@ hcmix_status hcmix_stack_backward_data(int64_t batch, int64_t n, int64_t width,
   if (need > 0) e = transpose_weights(w, num_layers, w_self, w_off, wt, s);
   for (int l = num_layers - 1; l >= 0 && e == hipSuccess; l--) {
     const int d = hcmix_dim(layers[l], n);
-    if (mfma_path(dtype, w)) {
-      if (need > 0)
-        e = run_dx_bf16(rows, w, d, (int)n, bidir, (const bf16*)g(l + 1), wt + 2 * (size_t)l * ww,
-                        wt + (2 * (size_t)l + 1) * ww, (bf16*)g(l), /*transpose_b=*/false, s);
-      else
-        e = run_dx_bf16(rows, w, d, (int)n, bidir, (const bf16*)g(l + 1), (const bf16*)w_self[l],
-                        (const bf16*)w_off[l], (bf16*)g(l), /*transpose_b=*/true, s);
-    } else {
-      e = launch_mix_fma(g(l + 1), w_self[l], w_off[l], g(l), rows, w, d, 1, bidir, (int)n,
-                         /*shift=*/1, /*transpose_w=*/true, dtype == HCMIX_BF16, s);
-    }
+    if (need > 0)
+      e = run_dx_bf16(rows, w, d, (int)n, bidir, (const bf16*)g(l + 1), wt + 2 * (size_t)l * ww,
+                      wt + (2 * (size_t)l + 1) * ww, (bf16*)g(l), /*transpose_b=*/false, s);
+    else
+      e = run_dx(rows, w, d, (int)n, bidir, dtype, g(l + 1), w_self[l], w_off[l], g(l), s);
   }
   return e == hipSuccess ? HCMIX_OK : hip_fail(e);
 }
@@ -711,48 +828,56 @@ hcmix_status hcmix_stack_weight_gradients(int64_t batch, int64_t n, int64_t widt
     if (st != HCMIX_OK) return st;
     if (!xs_in[l] || !dys[l] || !dw_self[l] || !dw_off[l]) return HCMIX_ERR_INVALID_VALUE;
   }
-  const size_t need = weight_grad_workspace_bytes(batch, n, width, num_layers, dtype);
-  if (need > 0 && (!workspace || workspace_bytes < need)) return HCMIX_ERR_INVALID_VALUE;
   const size_t act = (size_t)(batch * n * width) * elem_size(dtype);
   const size_t gw = (size_t)(width * width) * sizeof(float);
   const size_t al = dtype == HCMIX_BF16 ? 16 : 4;
   // Outputs: the workspace and every weight gradient; inputs: every xs_in[l]
   // and dys[l].  No output may overlap any input or another output.
-  for (int l = 0; l < num_layers; l++) {
-    const Span ins[2] = {{xs_in[l], act}, {dys[l], act}};
-    const Span outs[3] = {{workspace, need}, {dw_self[l], gw}, {dw_off[l], gw}};
-    hcmix_status st = check_spans(ins, 2, outs, 3, al);
-    if (st != HCMIX_OK) return st;
-    for (int j = 0; j < num_layers; j++) {
-      if (j == l) continue;
-      const Span other[4] = {{xs_in[j], act}, {dys[j], act}, {dw_self[j], gw}, {dw_off[j], gw}};
-      for (int k = 1; k < 3; k++)
-        for (int m = 0; m < 4; m++)
-          if (overlaps(outs[k].p, outs[k].n, other[m].p, other[m].n))
-            return HCMIX_ERR_INVALID_VALUE;
+  auto check = [&](size_t need) -> hcmix_status {
+    if (need > 0 && (!workspace || workspace_bytes < need)) return HCMIX_ERR_INVALID_VALUE;
+    for (int l = 0; l < num_layers; l++) {
+      const Span ins[2] = {{xs_in[l], act}, {dys[l], act}};
+      const Span outs[3] = {{workspace, need}, {dw_self[l], gw}, {dw_off[l], gw}};
+      hcmix_status st = check_spans(ins, 2, outs, 3, al);
+      if (st != HCMIX_OK) return st;
+      for (int j = 0; j < num_layers; j++) {
+        if (j == l) continue;
+        const Span other[4] = {{xs_in[j], act}, {dys[j], act}, {dw_self[j], gw}, {dw_off[j], gw}};
+        for (int k = 1; k < 3; k++)
+          for (int m = 0; m < 4; m++)
+            if (overlaps(outs[k].p, outs[k].n, other[m].p, other[m].n))
+              return HCMIX_ERR_INVALID_VALUE;
+      }
+      if (!aligned(dw_self[l], 16) || !aligned(dw_off[l], 16)) return HCMIX_ERR_UNSUPPORTED;
     }
-    if (!aligned(dw_self[l], 16) || !aligned(dw_off[l], 16)) return HCMIX_ERR_UNSUPPORTED;
+    return need && !aligned(workspace, 256) ? HCMIX_ERR_UNSUPPORTED : HCMIX_OK;
+  };
+  hcmix_status st = check(weight_grad_workspace_bytes(batch, n, width, num_layers, dtype));
+  int splits = 0;
+  if (!whole_width(dtype, width)) {
+    splits = stack_dw_splits(batch * n, width, num_layers, dtype);
+    if (st != HCMIX_OK) {   // no room for the partials: every block walks all rows
+      splits = 1;
+      st = check(0);
+    }
   }
-  if (need && !aligned(workspace, 256)) return HCMIX_ERR_UNSUPPORTED;
+  if (st != HCMIX_OK) return st;
   const int rows = (int)(batch * n), w = (int)width;
   const int bidir = mode == HCMIX_BIDIR;
   hipStream_t s = (hipStream_t)stream;
   hipError_t e = hipSuccess;
-  if (dtype == HCMIX_BF16 && width % 128 == 0) {
+  if (splits > 0 || width % 128 == 0) {
     for (int l0 = 0; l0 < num_layers && e == hipSuccess; l0 += kBatchMaxLayers) {
       const int count = num_layers - l0 < kBatchMaxLayers ? num_layers - l0 : kBatchMaxLayers;
-      e = launch_dw_chunk(rows, w, (int)n, count, layers + l0, bidir, xs_in + l0, dys + l0,
-                          dw_self + l0, dw_off + l0, accumulate != 0, (float*)workspace, s);
+      e = launch_dw_chunk(rows, w, (int)n, count, layers + l0, bidir, dtype, xs_in + l0, dys + l0,
+                          dw_self + l0, dw_off + l0, accumulate != 0, (float*)workspace,
+                          splits > 0 ? splits : dw_batch_splits(rows, w, count), s);
     }
   } else {
     for (int l = 0; l < num_layers && e == hipSuccess; l++) {
       const int d = hcmix_dim(layers[l], n);
-      if (mfma_path(dtype, w))
-        e = launch_dw_bf16((const bf16*)xs_in[l], (const bf16*)dys[l], (float*)workspace,
-                           dw_self[l], dw_off[l], rows, w, d, (int)n, bidir, accumulate != 0, s);
-      else
-        e = launch_dw_fma(xs_in[l], dys[l], dw_self[l], dw_off[l], rows, w, d, (int)n, bidir,
-                          accumulate != 0, dtype == HCMIX_BF16, s);
+      e = launch_dw_bf16((const bf16*)xs_in[l], (const bf16*)dys[l], (float*)workspace,
+                         dw_self[l], dw_off[l], rows, w, d, (int)n, bidir, accumulate != 0, s);
     }
   }
   return e == hipSuccess ? HCMIX_OK : hip_fail(e);
@@ -1009,7 +1134,7 @@ hcmix_status hcmix_decode_step(int64_t batch, int64_t n, int64_t width, int32_t 
       a.in_stride = a.partner_stride = a.out_stride = a.rec_stride = width;
       a.batch = (int)batch;
       a.width = (int)width;
-      e = mfma_path(dtype, width) ? launch_decode_bf16(a, s) : launch_decode_bf16_fma(a, s);
+      e = whole_width(dtype, width) ? launch_decode_bf16(a, s) : launch_decode_bf16_fma(a, s);
     } else {
       DecodeLayerArgsF32 a = {};
       a.x_in = (const float*)in;

@@ -47,26 +47,19 @@ __device__ __forceinline__ bf16 to_bf16(float v) { return (bf16)v; }
 
 // ---- launchers (each returns hipGetLastError() of its launch) ----
 
-// FMA path (fp32 arithmetic; data fp32, or bf16 when bf16_data, widened
-// exactly and each output rounded once):
+// fp32 (any width, 4-byte aligned):
 // out[r][j] = sum_k A[r][k] B1(j,k) + m(r) sum_k A[p(r)][k] B2(j,k).
 // B(j,k) = W[j*width+k] when !transpose_w, W[k*width+j] when transpose_w.
 // d >= 0: p(r) = r ^ 2^d, m(r) = partner_lower for rows with bit d clear,
 // partner_upper otherwise.  d < 0 (local layer): p(r) = r + shift over windows
 // of n rows, shift = -1 (m = 0 at a window's first row) or +1 (at its last).
-// The weight gradients (fp32 out) of a local layer (d < 0) pair row r with
-// r - 1.
-hipError_t launch_mix_fma(const void* A, const void* W1, const void* W2, void* out, int rows,
-                          int width, int d, int partner_lower, int partner_upper, int n,
-                          int shift, bool transpose_w, bool bf16_data, hipStream_t st);
+hipError_t launch_mix_f32(const float* A, const float* W1, const float* W2, float* out, int rows,
+                          int width, int d, int partner_lower, int partner_upper, int n, int shift,
+                          bool transpose_w, hipStream_t st);
 
-hipError_t launch_dw_fma(const void* X, const void* dY, float* dws, float* dwo, int rows,
-                         int width, int d, int n, int bidir, int accumulate, bool bf16_data,
-                         hipStream_t st);
-
-// bf16 MFMA: same contraction as launch_mix_fma.  B(j,k) = B[j*width+k] when
+// bf16 MFMA: same contraction as launch_mix_f32.  B(j,k) = B[j*width+k] when
 // !transpose_b, B[k*width+j] when transpose_b (read transposed from LDS).
-// width % 64 == 0.
+// width % 8 == 0.
 hipError_t launch_mix_bf16(const bf16* A, const bf16* B1, const bf16* B2, bf16* out,
                            int rows, int width, int d, int partner_lower, int partner_upper,
                            bool transpose_b, hipStream_t st);
@@ -113,21 +106,26 @@ struct DwReduce {
 hipError_t launch_dw_reduce(const DwReduce& r, int width, hipStream_t st);
 
 // Weight gradients of a whole stack (up to kBatchMaxLayers layers) in one
-// launch (bf16, width % 128 == 0), plus a fixed-order reduction when the
+// launch (bf16, width % 8 == 0; fp32), plus a fixed-order reduction when the
 // layers are split over row ranges.
 constexpr int kBatchMaxLayers = 64;
-struct DwBatchArgs {
-  const bf16* x[kBatchMaxLayers];    // input of each layer
-  const bf16* dy[kBatchMaxLayers];   // gradient of each layer's output
+template <typename E>
+struct DwBatch {
+  const E* x[kBatchMaxLayers];       // input of each layer
+  const E* dy[kBatchMaxLayers];      // gradient of each layer's output
   float* dws[kBatchMaxLayers];
   float* dwo[kBatchMaxLayers];
   int dim[kBatchMaxLayers];          // hypercube dimension, or -1 for the local layer
   float* partial;                    // [L][splits][2][width][width] when splits > 1
   int rows, width, n, num_layers, splits, bidir, accumulate;
 };
+typedef DwBatch<bf16> DwBatchArgs;
+typedef DwBatch<float> DwBatchArgsF32;
 // Splits per layer for num_layers layers of this shape (1: no partials).
 int dw_batch_splits(int rows, int width, int num_layers);
 hipError_t launch_dw_batch_bf16(const DwBatchArgs& a, hipStream_t st);
+int dw_f32_splits(int rows, int width, int num_layers);
+hipError_t launch_dw_f32(const DwBatchArgsF32& a, hipStream_t st);
 
 // ---- fused small-width stack (width 64, n in {64, 128, 256}) ----
 

@@ -1,223 +1,373 @@
-// FMA path of the mixing layer: LDS-tiled kernels with no matrix
-// instructions, every product and sum an IEEE fp32 operation.  Used for fp32
-// inputs of any width, and for bf16 inputs whose width is a multiple of 8 but
-// not of 64 (the MFMA tiles of kernels_bf16.hip need 64): bf16 operands are
-// widened to fp32 exactly, and each bf16 output is rounded once (RNE), as on
-// the MFMA path.
+// fp32 path of the mixing layer on the fp32 matrix instructions
+// (v_mfma_f32_16x16x4_f32: fp32 operands, products and sums, nothing rounded
+// below 32 bits), for any width, alignment and row count.
+//
+// What bounds it: the matrix cores, which do 256 flop per clock and CU in fp32
+// (a 8192^3 library product reaches 154 TFLOP/s), four times what one FMA per
+// lane and clock would give a kernel that also has to read its operands from
+// LDS.  The tiles are 64 x 64 with 32-wide contraction slices: 16 flop per
+// byte moved into the CU, 16 B/clk at full matrix rate, which L2 serves; two
+// slices sit in LDS and the next one travels through registers meanwhile.
+// Measured at 4096 rows x 256, 8 layers, forward and backward: 296 us (65
+// TFLOP/s), against 6998 us with 4 x 4 FMAs per thread and a launch of one
+// block per weight-gradient tile for every layer.
 #include "hcmix_internal.h"
 
 namespace hcmix {
 
 namespace {
 
-__device__ __forceinline__ float widen(float v) { return v; }
-__device__ __forceinline__ float widen(bf16 v) { return (float)v; }
-template <typename E> __device__ __forceinline__ E narrow(float v);
-template <> __device__ __forceinline__ float narrow<float>(float v) { return v; }
-template <> __device__ __forceinline__ bf16 narrow<bf16>(float v) { return to_bf16(v); }
+constexpr int BM = 64;    // rows per block (hypercube layers: 32 lower rows, then their partners)
+constexpr int BN = 64;    // output columns per block, 16 per wave
+constexpr int KC = 32;    // contraction slice
+constexpr int NT = 256;
+// LDS row strides in floats.  A [row][k] tile is read 16 bytes per lane, 16
+// rows at a time: 144-byte rows put them in 16 distinct bank groups.  A
+// [k][column] tile is read 4 bytes per lane, 4 k-rows of 16 columns: the k-rows
+// a lane group reads lie 4 apart (weights, LDT) or 1 apart (gradients, LDR),
+// and must fall 16 banks apart.
+constexpr int LDK = KC + 4;
+constexpr int LDT = BN + 4;
+constexpr int LDR = BN + 16;
 
-constexpr int T = 64;    // output tile edge
-constexpr int KC = 16;   // contraction chunk
-constexpr int NT = 256;  // threads per block: 16 x 16, 4 x 4 outputs each
+__device__ __forceinline__ f32x4 mfma4(float a, float b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// Columns col .. col + 3 of a row (zero outside the width, or if !valid).
+// VEC: width a multiple of 4 and 16-byte aligned rows, so a piece of four is
+// wholly inside or outside.
+template <bool VEC>
+__device__ __forceinline__ f32x4 load4(const float* __restrict__ row, int col, int width,
+                                       bool valid) {
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (VEC) {
+    if (valid && col < width) v = *(const f32x4*)(row + col);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; e++)
+      if (valid && col + e < width) v[e] = row[col + e];
+  }
+  return v;
+}
+
+template <bool VEC>
+__device__ __forceinline__ void put4(float* __restrict__ dst, int col, int width, const f32x4& v,
+                                     bool add) {
+  if constexpr (VEC) {
+    if (col < width) {
+      f32x4* p = (f32x4*)(dst + col);
+      *p = add ? *p + v : v;
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; e++)
+      if (col + e < width) dst[col + e] = add ? dst[col + e] + v[e] : v[e];
+  }
+}
 
 // out[r][j] = sum_k A[r][k] W1(j,k) + m(r) sum_k A[p(r)][k] W2(j,k)
-// Hypercube layer (d >= 0): p(r) = r ^ 2^d, m(r) = partner_upper / partner_lower
-// by bit d of r.  Local layer (d < 0): p(r) = r + shift with shift = -1
-// (forward; m = 0 at a window's first row) or +1 (dX; m = 0 at its last row).
-template <typename E, bool TRANSPOSE_W>
-__global__ __launch_bounds__(NT) void mix_fma_kernel(
-    const E* __restrict__ A, const E* __restrict__ W1, const E* __restrict__ W2,
-    E* __restrict__ out, int rows, int width, int d, int partner_lower, int partner_upper,
+// Hypercube layer: p(r) = r ^ 2^d, m(r) = partner_upper / partner_lower by bit
+// d of r; the block's rows are 32 lower rows and their 32 partners, so a row's
+// partner is the other half's row of the same tile and causal blocks do no
+// product for the half that takes none.  Local layer (NEAR): p(r) = r + shift
+// with shift = -1 (forward; m = 0 at a window's first row) or +1 (dX; m = 0 at
+// its last row); the partners are a tile of their own.
+// Each wave takes all 64 rows and 16 columns, so every wave has the same work.
+// The weights are the first MFMA operand: a lane ends with four consecutive
+// columns of one row.  Contraction order within a slice: lane group g holds
+// k = 16 i + 4 g + e in the e-th product of step i, for both operands.
+template <bool VEC, bool TRANSPOSE_W, bool NEAR>
+__global__ __launch_bounds__(NT) void mix_f32_kernel(
+    const float* __restrict__ A, const float* __restrict__ W1, const float* __restrict__ W2,
+    float* __restrict__ out, int rows, int width, int d, int partner_lower, int partner_upper,
     int n, int shift) {
-  __shared__ float sA[KC][T + 1];
-  __shared__ float sP[KC][T + 1];
-  __shared__ float sW1[KC][T + 1];
-  __shared__ float sW2[KC][T + 1];
-  const int tid = threadIdx.x;
-  const int tx = tid % 16, ty = tid / 16;
-  const int r0 = blockIdx.x * T, j0 = blockIdx.y * T;
-  const int s = d >= 0 ? 1 << d : 0;
-  float acc[4][4] = {};
+  constexpr int A_SZ = BM * LDK, W_SZ = TRANSPOSE_W ? KC * LDT : BN * LDK;
+  constexpr int STAGE = (NEAR ? 2 : 1) * A_SZ + 2 * W_SZ;
+  __shared__ __attribute__((aligned(16))) float smem[2 * STAGE];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l15 = lane & 15, g = lane >> 4;
+  const int j0 = blockIdx.y * BN;
+  const int s = NEAR ? 0 : 1 << d;
+  const int pairs = rows / 2;
+  // tile row m -> row of the tensor (-1: outside)
+  auto row_of = [&](int m) {
+    if constexpr (NEAR) {
+      const int r = blockIdx.x * BM + m;
+      return r < rows ? r : -1;
+    }
+    const int q = blockIdx.x * (BM / 2) + (m & 31);
+    return q < pairs ? lower_row(q, d) + (m >= 32 ? s : 0) : -1;
+  };
 
-  for (int k0 = 0; k0 < width; k0 += KC) {
-    for (int e = 0; e < (T * KC) / NT; e++) {
-      const int idx = tid + NT * e;
-      // activations: 16 consecutive k of one row per 16 threads
-      {
-        const int m = idx / KC, kk = idx % KC;
-        const int r = r0 + m, k = k0 + kk;
-        float a = 0.f, p = 0.f;
-        if (r < rows && k < width) {
-          a = widen(A[(size_t)r * width + k]);
-          int take, pr;
-          if (d >= 0) {
-            take = ((r >> d) & 1) ? partner_upper : partner_lower;
-            pr = r ^ s;
-          } else {
-            const int pos = r & (n - 1);
-            take = shift < 0 ? pos != 0 : pos != n - 1;
-            pr = r + shift;
-          }
-          if (take) p = widen(A[(size_t)pr * width + k]);
-        }
-        sA[kk][m] = a;
-        sP[kk][m] = p;
-      }
-      // weights
-      {
-        int j, kk;
-        if (TRANSPOSE_W) { kk = idx / T; j = idx % T; }   // contiguous along j
-        else { j = idx / KC; kk = idx % KC; }             // contiguous along k
-        const int jj = j0 + j, k = k0 + kk;
-        float w1 = 0.f, w2 = 0.f;
-        if (jj < width && k < width) {
-          const size_t off = TRANSPOSE_W ? (size_t)k * width + jj : (size_t)jj * width + k;
-          w1 = widen(W1[off]);
-          w2 = widen(W2[off]);
-        }
-        sW1[kk][j] = w1;
-        sW2[kk][j] = w2;
+  // this thread's two 16-byte pieces of each tile
+  const float *a_row[2], *p_row[2];
+  bool a_ok[2], p_ok[2];
+#pragma unroll
+  for (int j = 0; j < 2; j++) {
+    const int r = row_of((tid + NT * j) >> 3);
+    a_ok[j] = r >= 0;
+    a_row[j] = A + (size_t)(r >= 0 ? r : 0) * width;
+    if constexpr (NEAR) {
+      const int pos = r & (n - 1);
+      p_ok[j] = r >= 0 && (shift < 0 ? pos != 0 : pos != n - 1);
+      p_row[j] = p_ok[j] ? A + (size_t)(r + shift) * width : A;
+    }
+  }
+  f32x4 ra[2], rp[2], r1[2], r2[2];
+  auto fetch = [&](int k0) {
+#pragma unroll
+    for (int j = 0; j < 2; j++) {
+      const int p = tid + NT * j;
+      const int col = k0 + (p & 7) * 4;
+      ra[j] = load4<VEC>(a_row[j], col, width, a_ok[j]);
+      if constexpr (NEAR) rp[j] = load4<VEC>(p_row[j], col, width, p_ok[j]);
+      if constexpr (TRANSPOSE_W) {   // rows are k, contiguous along the output columns
+        const int k = k0 + (p >> 4);
+        const size_t off = (size_t)(k < width ? k : 0) * width;
+        r1[j] = load4<VEC>(W1 + off, j0 + (p & 15) * 4, width, k < width);
+        r2[j] = load4<VEC>(W2 + off, j0 + (p & 15) * 4, width, k < width);
+      } else {
+        const int o = j0 + (p >> 3);
+        const size_t off = (size_t)(o < width ? o : 0) * width;
+        r1[j] = load4<VEC>(W1 + off, col, width, o < width);
+        r2[j] = load4<VEC>(W2 + off, col, width, o < width);
       }
     }
-    __syncthreads();
+  };
+  auto stage = [&](float* b) {
+    float* w1 = b + (NEAR ? 2 : 1) * A_SZ;
 #pragma unroll
-    for (int kk = 0; kk < KC; kk++) {
-      float a[4], p[4], b1[4], b2[4];
+    for (int j = 0; j < 2; j++) {
+      const int p = tid + NT * j;
+      const int ka = (p >> 3) * LDK + (p & 7) * 4, kt = (p >> 4) * LDT + (p & 15) * 4;
+      *(f32x4*)(b + ka) = ra[j];
+      if constexpr (NEAR) *(f32x4*)(b + A_SZ + ka) = rp[j];
+      *(f32x4*)(w1 + (TRANSPOSE_W ? kt : ka)) = r1[j];
+      *(f32x4*)(w1 + W_SZ + (TRANSPOSE_W ? kt : ka)) = r2[j];
+    }
+  };
+
+  f32x4 acc[4] = {};
+  auto compute = [&](const float* b) {
+    const float* w1 = b + (NEAR ? 2 : 1) * A_SZ;
+    const float* w2 = w1 + W_SZ;
 #pragma unroll
-      for (int i = 0; i < 4; i++) {
-        a[i] = sA[kk][ty * 4 + i];
-        p[i] = sP[kk][ty * 4 + i];
-        b1[i] = sW1[kk][tx * 4 + i];
-        b2[i] = sW2[kk][tx * 4 + i];
+    for (int i = 0; i < KC / 16; i++) {
+      const int k = 16 * i + 4 * g;
+      f32x4 b1, b2, a[4], pv[4];
+      if constexpr (TRANSPOSE_W) {
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+          b1[e] = w1[(k + e) * LDT + 16 * wave + l15];
+          b2[e] = w2[(k + e) * LDT + 16 * wave + l15];
+        }
+      } else {
+        b1 = *(const f32x4*)(w1 + (16 * wave + l15) * LDK + k);
+        b2 = *(const f32x4*)(w2 + (16 * wave + l15) * LDK + k);
       }
 #pragma unroll
-      for (int i = 0; i < 4; i++)
+      for (int t = 0; t < 4; t++) {
+        a[t] = *(const f32x4*)(b + (16 * t + l15) * LDK + k);
+        if constexpr (NEAR) pv[t] = *(const f32x4*)(b + A_SZ + (16 * t + l15) * LDK + k);
+      }
 #pragma unroll
-        for (int j = 0; j < 4; j++) acc[i][j] = fmaf(p[i], b2[j], fmaf(a[i], b1[j], acc[i][j]));
+      for (int e = 0; e < 4; e++)
+#pragma unroll
+        for (int t = 0; t < 4; t++) acc[t] = mfma4(b1[e], a[t][e], acc[t]);
+      if constexpr (NEAR) {
+#pragma unroll
+        for (int e = 0; e < 4; e++)
+#pragma unroll
+          for (int t = 0; t < 4; t++) acc[t] = mfma4(b2[e], pv[t][e], acc[t]);
+      } else {
+        if (partner_upper) {
+#pragma unroll
+          for (int e = 0; e < 4; e++)
+#pragma unroll
+            for (int t = 2; t < 4; t++) acc[t] = mfma4(b2[e], a[t - 2][e], acc[t]);
+        }
+        if (partner_lower) {
+#pragma unroll
+          for (int e = 0; e < 4; e++)
+#pragma unroll
+            for (int t = 0; t < 2; t++) acc[t] = mfma4(b2[e], a[t + 2][e], acc[t]);
+        }
+      }
     }
+  };
+
+  const int nk = (width + KC - 1) / KC;
+  fetch(0);
+  stage(smem);
+  __syncthreads();
+  for (int kt = 0; kt < nk; kt++) {
+    if (kt + 1 < nk) fetch((kt + 1) * KC);
+    compute(smem + (kt & 1) * STAGE);
+    if (kt + 1 < nk) stage(smem + ((kt + 1) & 1) * STAGE);
     __syncthreads();
   }
 #pragma unroll
-  for (int i = 0; i < 4; i++) {
-    const int r = r0 + ty * 4 + i;
-    if (r >= rows) continue;
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-      const int jj = j0 + tx * 4 + j;
-      if (jj < width) out[(size_t)r * width + jj] = narrow<E>(acc[i][j]);
-    }
+  for (int t = 0; t < 4; t++) {
+    const int r = row_of(16 * t + l15);
+    if (r >= 0) put4<VEC>(out + (size_t)r * width, j0 + 16 * wave + 4 * g, width, acc[t], false);
   }
 }
 
-// dws[o][c] (+)= sum_r dY[r][o] X[r][c];  dwo[o][c] (+)= sum_r m(r) dY[r][o] X[p(r)][c]
-// with p(r) = r ^ 2^d (hypercube layer) or r - 1 (local layer, d < 0; m = 0 at
-// a window's first row).  One block per 64 x 64 output tile walks every row in
-// a fixed order.
-template <typename E>
-__global__ __launch_bounds__(NT) void dw_fma_kernel(
-    const E* __restrict__ X, const E* __restrict__ dY, float* __restrict__ dws,
-    float* __restrict__ dwo, int rows, int width, int d, int n, int bidir, int accumulate) {
-  __shared__ float sG[KC][T + 1];
-  __shared__ float sX[KC][T + 1];
-  __shared__ float sXP[KC][T + 1];
-  const int tid = threadIdx.x;
-  const int tx = tid % 16, ty = tid / 16;
-  const int o0 = blockIdx.y * T, c0 = blockIdx.x * T;
-  const int s = d >= 0 ? 1 << d : 0;
-  float accS[4][4] = {}, accO[4][4] = {};
+// Weight gradients of the layers of a stack in one launch:
+//   dws[o][c] (+)= sum_r dY[r][o] X[r][c],  dwo[o][c] (+)= sum_r m(r) dY[r][o] X[p(r)][c].
+// Block -> (layer, row range, matrix, 64 x 64 tile); the off-diagonal matrix of
+// a causal hypercube layer walks the receiving rows only.  Rows are walked in
+// order, so the sums do not depend on the launch.  With one range per layer
+// the tile goes straight to dws / dwo, otherwise to partial[layer][range][2].
+template <bool VEC>
+__global__ __launch_bounds__(NT) void dw_f32_kernel(DwBatchArgsF32 a) {
+  constexpr int T_SZ = KC * LDR;
+  __shared__ __attribute__((aligned(16))) float smem[4 * T_SZ];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l15 = lane & 15, g = lane >> 4;
+  const int width = a.width, te = (width + 63) / 64, tiles = te * te;
+  int lin = blockIdx.x;
+  const int tile = lin % tiles;
+  lin /= tiles;
+  const int off = lin & 1;
+  lin >>= 1;
+  const int split = lin % a.splits, layer = lin / a.splits;
+  const int o0 = (tile / te) * 64, c0 = (tile % te) * 64;
+  const int d = a.dim[layer];
+  const int s = d < 0 ? 0 : 1 << d;
+  const float* X = a.x[layer];
+  const float* dY = a.dy[layer];
+  const bool half = off && d >= 0 && !a.bidir;     // receiving (upper) rows only
+  const int units = half ? a.rows / 2 : a.rows;
+  const int per = ((units + KC - 1) / KC + a.splits - 1) / a.splits * KC;
+  const int beg = min(units, split * per), end = min(units, beg + per);
 
-  for (int rb = 0; rb < rows; rb += KC) {
-    for (int e = 0; e < (T * KC) / NT; e++) {
-      const int idx = tid + NT * e;
-      const int kk = idx / T, j = idx % T;  // row kk of the chunk, column j of the tile
-      const int r = rb + kk;
-      float g = 0.f, xv = 0.f, xp = 0.f;
-      if (r < rows) {
-        if (o0 + j < width) g = widen(dY[(size_t)r * width + o0 + j]);
-        if (c0 + j < width) {
-          xv = widen(X[(size_t)r * width + c0 + j]);
-          if (d < 0) {
-            if (r & (n - 1)) xp = widen(X[(size_t)(r - 1) * width + c0 + j]);
-          } else if (bidir || ((r >> d) & 1)) {
-            xp = widen(X[(size_t)(r ^ s) * width + c0 + j]);
-          }
+  f32x4 rg[2], rx[2];
+  auto fetch = [&](int u0) {
+#pragma unroll
+    for (int j = 0; j < 2; j++) {
+      const int p = tid + NT * j;
+      const int u = u0 + (p >> 4);
+      const int r = half ? lower_row(u, d) + s : u;
+      bool take = u < end;
+      int pr = r;
+      if (off) {
+        if (d < 0) {
+          take = take && (r & (a.n - 1)) != 0;
+          pr = r - 1;
+        } else {
+          pr = r ^ s;
         }
       }
-      sG[kk][j] = g;
-      sX[kk][j] = xv;
-      sXP[kk][j] = xp;
+      rg[j] = load4<VEC>(dY + (size_t)(u < end ? r : 0) * width, o0 + (p & 15) * 4, width, u < end);
+      rx[j] = load4<VEC>(X + (size_t)(take ? pr : 0) * width, c0 + (p & 15) * 4, width, take);
     }
-    __syncthreads();
+  };
+  auto stage = [&](float* b) {
 #pragma unroll
-    for (int kk = 0; kk < KC; kk++) {
-      float g[4], xv[4], xp[4];
-#pragma unroll
-      for (int i = 0; i < 4; i++) {
-        g[i] = sG[kk][ty * 4 + i];
-        xv[i] = sX[kk][tx * 4 + i];
-        xp[i] = sXP[kk][tx * 4 + i];
-      }
-#pragma unroll
-      for (int i = 0; i < 4; i++)
-#pragma unroll
-        for (int j = 0; j < 4; j++) {
-          accS[i][j] = fmaf(g[i], xv[j], accS[i][j]);
-          accO[i][j] = fmaf(g[i], xp[j], accO[i][j]);
-        }
+    for (int j = 0; j < 2; j++) {
+      const int p = tid + NT * j, at = (p >> 4) * LDR + (p & 15) * 4;
+      *(f32x4*)(b + at) = rg[j];
+      *(f32x4*)(b + T_SZ + at) = rx[j];
     }
+  };
+  f32x4 acc[4] = {};
+  auto compute = [&](const float* b) {
+#pragma unroll
+    for (int k = 0; k < KC; k += 4) {
+      const float* gr = b + (k + g) * LDR;
+      const float gv = gr[16 * wave + l15];
+#pragma unroll
+      for (int t = 0; t < 4; t++) acc[t] = mfma4(gr[T_SZ + 16 * t + l15], gv, acc[t]);
+    }
+  };
+  const int nk = (end - beg + KC - 1) / KC;
+  if (nk > 0) {
+    fetch(beg);
+    stage(smem);
+  }
+  __syncthreads();
+  for (int kt = 0; kt < nk; kt++) {
+    if (kt + 1 < nk) fetch(beg + (kt + 1) * KC);
+    compute(smem + (kt & 1) * 2 * T_SZ);
+    if (kt + 1 < nk) stage(smem + ((kt + 1) & 1) * 2 * T_SZ);
     __syncthreads();
   }
+  // lane: output row o0 + 16 wave + l15, columns c0 + 16 t + 4 g + 0..3
+  const int o = o0 + 16 * wave + l15;
+  if (o >= width) return;
+  const size_t ww = (size_t)width * width;
+  float* dst = a.splits == 1 ? (off ? a.dwo[layer] : a.dws[layer])
+                             : a.partial + (((size_t)layer * a.splits + split) * 2 + off) * ww;
 #pragma unroll
-  for (int i = 0; i < 4; i++) {
-    const int o = o0 + ty * 4 + i;
-    if (o >= width) continue;
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-      const int c = c0 + tx * 4 + j;
-      if (c >= width) continue;
-      const size_t off = (size_t)o * width + c;
-      dws[off] = accumulate ? dws[off] + accS[i][j] : accS[i][j];
-      dwo[off] = accumulate ? dwo[off] + accO[i][j] : accO[i][j];
-    }
+  for (int t = 0; t < 4; t++)
+    put4<VEC>(dst + (size_t)o * width, c0 + 16 * t + 4 * g, width, acc[t],
+              a.splits == 1 && a.accumulate);
+}
+
+// dW[l] (+)= sum over ranges of partial[l][range], in range order.
+__global__ __launch_bounds__(256) void dw_f32_reduce_kernel(DwBatchArgsF32 a) {
+  const size_t ww = (size_t)a.width * a.width;
+  const int l = blockIdx.y;
+  const float* part = a.partial + (size_t)l * a.splits * 2 * ww;
+  for (size_t i = blockIdx.x * (size_t)256 + threadIdx.x; i < 2 * ww; i += (size_t)gridDim.x * 256) {
+    float acc = 0.f;
+    for (int sp = 0; sp < a.splits; sp++) acc += part[(size_t)sp * 2 * ww + i];
+    float* dst = i < ww ? a.dws[l] + i : a.dwo[l] + (i - ww);
+    *dst = a.accumulate ? *dst + acc : acc;
   }
 }
+
+bool vec16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 }  // namespace
 
-template <typename E>
-hipError_t mix_fma_launch(const void* A, const void* W1, const void* W2, void* out, int rows,
+hipError_t launch_mix_f32(const float* A, const float* W1, const float* W2, float* out, int rows,
                           int width, int d, int partner_lower, int partner_upper, int n, int shift,
                           bool transpose_w, hipStream_t st) {
-  dim3 grid((rows + T - 1) / T, (width + T - 1) / T);
-  const E *a = (const E*)A, *w1 = (const E*)W1, *w2 = (const E*)W2;
-  if (transpose_w)
-    mix_fma_kernel<E, true><<<grid, NT, 0, st>>>(a, w1, w2, (E*)out, rows, width, d,
-                                                 partner_lower, partner_upper, n, shift);
-  else
-    mix_fma_kernel<E, false><<<grid, NT, 0, st>>>(a, w1, w2, (E*)out, rows, width, d,
-                                                  partner_lower, partner_upper, n, shift);
+  const dim3 grid(d < 0 ? (rows + BM - 1) / BM : (rows / 2 + BM / 2 - 1) / (BM / 2),
+                  (width + BN - 1) / BN);
+  // fp32 tensors need only be 4-byte aligned
+  const bool vec = width % 4 == 0 && vec16(A) && vec16(W1) && vec16(W2) && vec16(out);
+#define HCMIX_MF(V, T, N)                                                                    \
+  mix_f32_kernel<V, T, N><<<grid, NT, 0, st>>>(A, W1, W2, out, rows, width, d, partner_lower, \
+                                               partner_upper, n, shift)
+#define HCMIX_MFN(V, T) (d < 0 ? HCMIX_MF(V, T, true) : HCMIX_MF(V, T, false))
+  if (vec) {
+    if (transpose_w) HCMIX_MFN(true, true);
+    else HCMIX_MFN(true, false);
+  } else {
+    if (transpose_w) HCMIX_MFN(false, true);
+    else HCMIX_MFN(false, false);
+  }
+#undef HCMIX_MFN
+#undef HCMIX_MF
   return hipGetLastError();
 }
 
-hipError_t launch_mix_fma(const void* A, const void* W1, const void* W2, void* out, int rows,
-                          int width, int d, int partner_lower, int partner_upper, int n,
-                          int shift, bool transpose_w, bool bf16_data, hipStream_t st) {
-  return bf16_data ? mix_fma_launch<bf16>(A, W1, W2, out, rows, width, d, partner_lower,
-                                          partner_upper, n, shift, transpose_w, st)
-                   : mix_fma_launch<float>(A, W1, W2, out, rows, width, d, partner_lower,
-                                           partner_upper, n, shift, transpose_w, st);
+// Row ranges per layer: about four blocks per CU over the launch (the causal
+// off-diagonal tiles are half as long), each range at least 512 rows.
+int dw_f32_splits(int rows, int width, int num_layers) {
+  const int64_t te = (width + 63) / 64;
+  const int64_t blocks = (int64_t)num_layers * 2 * te * te;
+  int64_t splits = (1024 + blocks - 1) / blocks;
+  if (splits > rows / 512) splits = rows / 512;
+  return splits < 1 ? 1 : (int)splits;
 }
 
-hipError_t launch_dw_fma(const void* X, const void* dY, float* dws, float* dwo, int rows,
-                         int width, int d, int n, int bidir, int accumulate, bool bf16_data,
-                         hipStream_t st) {
-  dim3 grid((width + T - 1) / T, (width + T - 1) / T);
-  if (bf16_data)
-    dw_fma_kernel<bf16><<<grid, NT, 0, st>>>((const bf16*)X, (const bf16*)dY, dws, dwo, rows,
-                                             width, d, n, bidir, accumulate);
-  else
-    dw_fma_kernel<float><<<grid, NT, 0, st>>>((const float*)X, (const float*)dY, dws, dwo, rows,
-                                              width, d, n, bidir, accumulate);
+hipError_t launch_dw_f32(const DwBatchArgsF32& a, hipStream_t st) {
+  const int te = (a.width + 63) / 64;
+  const size_t blocks = (size_t)a.num_layers * a.splits * 2 * te * te;
+  bool vec = a.width % 4 == 0;
+  for (int l = 0; l < a.num_layers; l++) vec = vec && vec16(a.x[l]) && vec16(a.dy[l]);
+  if (vec) dw_f32_kernel<true><<<(unsigned)blocks, NT, 0, st>>>(a);
+  else dw_f32_kernel<false><<<(unsigned)blocks, NT, 0, st>>>(a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || a.splits == 1) return e;
+  const size_t ww2 = (size_t)2 * a.width * a.width;
+  const unsigned per = (unsigned)((ww2 + 255) / 256 < 256 ? (ww2 + 255) / 256 : 256);
+  dw_f32_reduce_kernel<<<dim3(per, a.num_layers), 256, 0, st>>>(a);
   return hipGetLastError();
 }
 

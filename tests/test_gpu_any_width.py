@@ -1,0 +1,111 @@
+"""fp32 stacks and bf16 widths that are no multiple of 64: the matrix-core tiles'
+edges (a width just below, at and above a tile, odd fp32 widths on the scalar
+loads), row counts that split the weight-gradient sums, and the backward on the
+whole and on the least workspace, against the CPU oracle.
+
+Tolerances: those of the other parity tests for the activations; weight
+gradients of a single layer see no rounding below fp32, so 1e-5 (fp32) and 1e-4
+(bf16 operands, whose products are exact in fp32) bound the order of the sums."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2609_18145_amd import hcmix, inputs
+from tests.util import TOL, fro_rel_err, row_rel_err, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    hcmix.load()
+
+
+@pytest.mark.parametrize("batch,n,width,dtype,layer", [
+    (3, 16, 1, "f32", 1), (1, 2, 33, "f32", 0), (3, 32, 63, "f32", 2), (2, 32, 68, "f32", -1),
+    (5, 64, 129, "f32", 5), (1, 512, 100, "f32", -1), (2, 64, 256, "f32", 3),
+    (3, 32, 56, "bf16", 0), (2, 64, 120, "bf16", 5), (1, 512, 136, "bf16", 8),
+    (3, 64, 200, "bf16", -1), (5, 64, 264, "bf16", 2), (1, 2, 72, "bf16", 0)])
+@pytest.mark.parametrize("causal", [False, True])
+def test_layer(batch, n, width, dtype, layer, causal):
+    if layer < 0 and not causal:
+        pytest.skip("the local layer is causal")
+    print(f"case: layer {batch}x{n}x{width} {dtype} layer={layer} causal={causal}", flush=True)
+    code, ref = (hcmix.LAYER_NEAR, oracle.NEAR) if layer < 0 else (layer, layer)
+    x, ws, wo, dy = inputs.make_layer(batch, n, width, dtype, seed=width + n)
+    tx, tws, two, tdy = (to_dev(a, dtype) for a in (x, ws, wo, dy))
+    y = hcmix.forward(tx, tws, two, code, causal)
+    dx, dws, dwo = hcmix.backward(tx, tws, two, tdy, code, causal)
+    torch.cuda.synchronize()
+    ry = oracle.forward(x, ws, wo, ref, causal)
+    rdx, rws, rwo = oracle.backward(x, ws, wo, dy, ref, causal)
+    assert row_rel_err(to_host(y), ry) <= TOL[dtype]
+    assert row_rel_err(to_host(dx), rdx) <= TOL[dtype]
+    tol = 1e-5 if dtype == "f32" else 1e-4
+    assert fro_rel_err(to_host(dws), rws) <= tol and fro_rel_err(to_host(dwo), rwo) <= tol
+
+
+def test_misaligned_fp32_tensors():
+    """fp32 operands need only 4-byte alignment: the scalar loads."""
+    batch, n, width = 2, 32, 64
+    x, ws, wo, dy = inputs.make_layer(batch, n, width, "f32", seed=4)
+
+    def off(a):
+        t = to_dev(a, "f32")
+        buf = torch.zeros(t.numel() + 1, device="cuda")
+        v = buf[1:].view(t.shape)
+        v.copy_(t)
+        return v
+
+    tx, tws, two, tdy = (off(a) for a in (x, ws, wo, dy))
+    y = hcmix.forward(tx, tws, two, 2, True)
+    dx, dws, dwo = hcmix.backward(tx, tws, two, tdy, 2, True)
+    torch.cuda.synchronize()
+    ry = oracle.forward(x, ws, wo, 2, True)
+    rdx, rws, rwo = oracle.backward(x, ws, wo, dy, 2, True)
+    assert row_rel_err(to_host(y), ry) <= 1e-5 and row_rel_err(to_host(dx), rdx) <= 1e-5
+    assert fro_rel_err(to_host(dws), rws) <= 1e-5 and fro_rel_err(to_host(dwo), rwo) <= 1e-5
+
+
+@pytest.mark.parametrize("batch,n,width,dtype,schedule", [
+    (17, 64, 33, "f32", [0, 1, 2, 5]),          # two row ranges, the second ragged
+    (8, 256, 64, "f32", [7, -1, 0]),            # four, a local layer among them
+    (17, 64, 72, "bf16", [0, 3, 5, -1]),
+    (8, 256, 136, "bf16", [7, 1])])
+def test_stack_backward_with_whole_and_least_workspace(batch, n, width, dtype, schedule):
+    print(f"case: stack {batch}x{n}x{width} {dtype} {schedule}", flush=True)
+    L = len(schedule)
+    codes = [hcmix.LAYER_NEAR if v < 0 else v for v in schedule]
+    refs = [oracle.NEAR if v < 0 else v for v in schedule]
+    s = inputs.make_stack(batch, n, width, L, True, dtype, seed=width, layers=refs)
+    ws, wo = ([to_dev(w, dtype) for w in m] for m in (s.w_self, s.w_off))
+    x, dy = to_dev(s.x, dtype), to_dev(s.dy, dtype)
+    xs = hcmix.stack_forward(x, ws, wo, codes, True)
+    whole = hcmix.stack_workspace_bytes(batch, n, width, L, x.dtype)
+    act = (x.numel() * x.element_size() + 255) // 256 * 256
+    assert whole > 2 * act                       # partial sums: the rows are split
+    base = [torch.full((width, width), 0.5, device="cuda") for _ in range(2 * L)]
+    got = []
+    for nbytes in (whole, 2 * act):
+        wsp = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        acc = [t.clone() for t in base]
+        dx, _, _ = hcmix.stack_backward(xs, ws, wo, codes, dy, True, dws=acc[:L], dwo=acc[L:],
+                                        accumulate=True, workspace=wsp)
+        got.append((dx, acc))
+    again = hcmix.stack_backward(xs, ws, wo, codes, dy, True)
+    _, grads = hcmix.stack_backward_data(ws, wo, codes, dy, True)
+    apart = hcmix.stack_weight_gradients(xs[:L], [*grads, dy], codes, True)
+    torch.cuda.synchronize()
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][0], again[0])
+    for a, b in zip(again[1] + again[2], apart[0] + apart[1]):
+        assert torch.equal(a, b)
+    ref = oracle.stack_forward(s.x, s.w_self, s.w_off, refs, True)
+    rdx, rws, rwo = oracle.stack_backward(ref, s.w_self, s.w_off, refs, s.dy, True)
+    assert row_rel_err(to_host(xs[-1]), ref[-1]) <= TOL[dtype]
+    assert row_rel_err(to_host(got[0][0]), rdx) <= TOL[dtype]
+    for _, acc in got:
+        for g, r in zip(acc, rws + rwo):
+            assert fro_rel_err(to_host(g) - 0.5, r) <= TOL[dtype]
