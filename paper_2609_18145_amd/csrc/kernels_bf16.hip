@@ -50,10 +50,12 @@ __device__ __forceinline__ int whole_tiles(int width, int tile) {
 // Forward: A = x, B1 = W_self, B2 = W_off, PU = 1, PL = bidir.
 // dX:      A = dy, B = W read transposed, PL = 1, PU = bidir.
 // ---------------------------------------------------------------------------
-template <int BMP, int BN, int WM, int WN, int BK, int NS>
+// WK: groups of WM x WN waves that share the tile and split each K-step's k16
+// slices; their sums meet in LDS at the end, in group order.
+template <int BMP, int BN, int WM, int WN, int WK, int BK, int NS>
 struct MixCfg {
-  static constexpr int NT = 64 * WM * WN;
-  static constexpr int NW = WM * WN;
+  static constexpr int NW = WM * WN * WK;
+  static constexpr int NT = 64 * NW;
   static constexpr int BM = 2 * BMP;
   static constexpr int TMP = BMP / (32 * WM);   // 32-row pair blocks per wave
   static constexpr int TN = BN / (32 * WN);     // 32-column blocks per wave
@@ -61,7 +63,9 @@ struct MixCfg {
   static constexpr int B_ELEMS = BN * BK;       // same size in both layouts
   static constexpr int STAGE = A_ELEMS + 2 * B_ELEMS;
   static constexpr int LDO = BN + 8;            // row stride of the output staging tile
-  static constexpr int LDS_ELEMS = (NS * STAGE > BM * LDO) ? NS * STAGE : BM * LDO;
+  static constexpr int ACC = 2 * TMP * TN * 16; // accumulators per lane
+  static constexpr int O_ELEMS = BM * LDO + (WK - 1) * WM * WN * ACC * 64 * 2;
+  static constexpr int LDS_ELEMS = (NS * STAGE > O_ELEMS) ? NS * STAGE : O_ELEMS;
   static constexpr int A_DMA = A_ELEMS * 2 / 1024 / NW;   // 1 KB DMA blocks per wave
   static constexpr int B_DMA = B_ELEMS * 2 / 1024 / NW;
   static constexpr int O_IT = BM * (BN / 8) / NT;
@@ -81,17 +85,18 @@ struct MixCfg {
 // stride, N the output columns, ldb the row stride of B (k-contiguous B: its
 // rows are n; TRANS_B: its rows are k), ldo the output's row stride; the
 // mixing layer has K = N = ldb = ldo = width.
-template <int BMP, int BN, int WM, int WN, int BK, int NS, bool PL, bool PU, bool TRANS_B, bool RAG>
+template <int BMP, int BN, int WM, int WN, int WK, int BK, int NS, bool PL, bool PU, bool TRANS_B,
+          bool RAG>
 __device__ __forceinline__ void mix_bf16_block(
     const bf16* __restrict__ A, const bf16* __restrict__ B1, const bf16* __restrict__ B2,
     bf16* __restrict__ out, int pairs, int K, int N, int ldb, int ldo, int d, int block,
     bf16* smem) {
-  using C = MixCfg<BMP, BN, WM, WN, BK, NS>;
+  using C = MixCfg<BMP, BN, WM, WN, WK, BK, NS>;
   constexpr int RB = BN * 2;   // bytes per row of a transposed B tile
   constexpr bool HAS_B2 = PL || PU;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave % WM, wn = wave / WM;
+  const int wm = wave % WM, wn = wave / WM % WN, wk = wave / (WM * WN);
   const int s = 1 << d;
   const int tiles_n = RAG ? whole_tiles(N, BN) : N / BN;
   const int tiles_m = (pairs + BMP - 1) / BMP;
@@ -205,7 +210,8 @@ __device__ __forceinline__ void mix_bf16_block(
       }
   };
 
-  constexpr int KK = BK / 16;
+  constexpr int KK = BK / 16 / WK;    // k16 slices per wave and K-step
+  static_assert(KK * WK * 16 == BK, "");
   constexpr int NMFMA = C::TMP * C::TN * (2 + (PL ? 1 : 0) + (PU ? 1 : 0));
   constexpr int NDS = 2 * C::TMP + (HAS_B2 ? 2 : 1) * C::TN * (TRANS_B ? 2 : 1);
   const int nk = RAG ? whole_tiles(K, BK) : K / BK;
@@ -220,12 +226,12 @@ __device__ __forceinline__ void mix_bf16_block(
     __syncthreads();  // stage kt visible to all waves; buffer (kt-1) % NS free
     if (kt + NS - 1 < nk) issue(kt + NS - 1, (kt + NS - 1) % NS);
     const bf16* sA = smem + (kt % NS) * C::STAGE;
-    load_frags(f[0], sA, 0);
+    load_frags(f[0], sA, wk * KK);
 #pragma unroll
     for (int kk = 0; kk < KK; kk++) {
       // one fenced region per kk: this kk's MFMAs with the next kk's reads
       if (kk + 1 < KK) {
-        load_frags(f[(kk + 1) & 1], sA, kk + 1);
+        load_frags(f[(kk + 1) & 1], sA, wk * KK + kk + 1);
         mma(f[kk & 1]);
         interleave_front<NMFMA, NDS>();
       } else {
@@ -240,6 +246,37 @@ __device__ __forceinline__ void mix_bf16_block(
   // Accumulator element e of lane l holds output row (lane's row l%32) and
   // column 8*(e/4) + 4*(l/32) + e%4 of its 32 x 32 block.
   bf16* sO = smem;
+  if constexpr (WK > 1) {
+    float* hand = (float*)(smem + C::BM * C::LDO) + (size_t)(wave % (WM * WN)) * C::ACC * 64 + lane;
+    constexpr size_t GROUP = (size_t)WM * WN * C::ACC * 64;
+    if (wk > 0) {
+      float* dst = hand + (wk - 1) * GROUP;
+#pragma unroll
+      for (int p = 0; p < C::TMP; p++)
+#pragma unroll
+        for (int t = 0; t < C::TN; t++)
+#pragma unroll
+          for (int e = 0; e < 16; e++) {
+            dst[((p * C::TN + t) * 32 + e) * 64] = accL[p][t][e];
+            dst[((p * C::TN + t) * 32 + 16 + e) * 64] = accU[p][t][e];
+          }
+    }
+    __syncthreads();
+    if (wk == 0) {
+#pragma unroll
+      for (int g = 0; g < WK - 1; g++)
+#pragma unroll
+        for (int p = 0; p < C::TMP; p++)
+#pragma unroll
+          for (int t = 0; t < C::TN; t++)
+#pragma unroll
+            for (int e = 0; e < 16; e++) {
+              accL[p][t][e] += hand[g * GROUP + ((p * C::TN + t) * 32 + e) * 64];
+              accU[p][t][e] += hand[g * GROUP + ((p * C::TN + t) * 32 + 16 + e) * 64];
+            }
+    }
+  }
+  if (wk == 0)
 #pragma unroll
   for (int p = 0; p < C::TMP; p++)
 #pragma unroll
@@ -268,13 +305,14 @@ __device__ __forceinline__ void mix_bf16_block(
   }
 }
 
-template <int BMP, int BN, int WM, int WN, int BK, int NS, bool PL, bool PU, bool TRANS_B, bool RAG>
-__global__ __launch_bounds__(64 * WM * WN) void mix_bf16_kernel(
+template <int BMP, int BN, int WM, int WN, int WK, int BK, int NS, bool PL, bool PU, bool TRANS_B,
+          bool RAG>
+__global__ __launch_bounds__(64 * WM * WN * WK) void mix_bf16_kernel(
     const bf16* __restrict__ A, const bf16* __restrict__ B1, const bf16* __restrict__ B2,
     bf16* __restrict__ out, int pairs, int K, int N, int ldb, int ldo, int d) {
   extern __shared__ __attribute__((aligned(1024))) bf16 smem[];
-  mix_bf16_block<BMP, BN, WM, WN, BK, NS, PL, PU, TRANS_B, RAG>(A, B1, B2, out, pairs, K, N, ldb,
-                                                                ldo, d, blockIdx.x, smem);
+  mix_bf16_block<BMP, BN, WM, WN, WK, BK, NS, PL, PU, TRANS_B, RAG>(
+      A, B1, B2, out, pairs, K, N, ldb, ldo, d, blockIdx.x, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -287,11 +325,10 @@ __global__ __launch_bounds__(64 * WM * WN) void mix_bf16_kernel(
 // partner of LDS row m is LDS row m + DELTA; a lane whose output row is masked
 // zeroes its partner fragment, and both products go to one accumulator tile.
 // ---------------------------------------------------------------------------
-template <int BM, int BN, int WM, int WN, int BK>
+template <int BM, int BN, int WM, int WN, int WK, int BK, int NS>
 struct ShiftCfg {
-  static constexpr int NS = 2;                   // pipeline stages
-  static constexpr int NT = 64 * WM * WN;
-  static constexpr int NW = WM * WN;
+  static constexpr int NW = WM * WN * WK;        // WK as in MixCfg
+  static constexpr int NT = 64 * NW;
   static constexpr int HALO = 8;                 // one 1 KB DMA block of rows at BK = 64
   static constexpr int AR = BM + HALO;           // staged A rows
   static constexpr int TM = BM / (32 * WM);      // 32-row blocks per wave
@@ -300,27 +337,31 @@ struct ShiftCfg {
   static constexpr int B_ELEMS = BN * BK;
   static constexpr int STAGE = A_ELEMS + 2 * B_ELEMS;
   static constexpr int LDO = BN + 8;
-  static constexpr int LDS_ELEMS = (NS * STAGE > BM * LDO) ? NS * STAGE : BM * LDO;
+  static constexpr int ACC = TM * TN * 16;
+  static constexpr int O_ELEMS = BM * LDO + (WK - 1) * WM * WN * ACC * 64 * 2;
+  static constexpr int LDS_ELEMS = (NS * STAGE > O_ELEMS) ? NS * STAGE : O_ELEMS;
   static constexpr int A_BLOCKS = A_ELEMS * 2 / 1024;
-  static constexpr int A_DMA = (A_BLOCKS + NW - 1) / NW;   // per wave; the last may idle
+  static constexpr int A_DMA = (A_BLOCKS + NW - 1) / NW;   // per wave; the last may repeat
   static constexpr int B_DMA = B_ELEMS * 2 / 1024 / NW;
+  static constexpr int DPS = A_DMA + 2 * B_DMA;  // DMA instructions per wave per stage
   static constexpr int O_IT = BM * (BN / 8) / NT;
+  static_assert(NS >= 2 && (NS - 2) * DPS <= 63, "vmcnt range");
   static_assert(A_BLOCKS * 1024 == A_ELEMS * 2 && B_DMA * NW * 1024 == B_ELEMS * 2, "");
   static_assert(TM >= 1 && TN >= 1 && O_IT * NT == BM * (BN / 8), "");
 };
 
-template <int BM, int BN, int WM, int WN, int BK, int DELTA, bool TRANS_B, bool RAG>
-__global__ __launch_bounds__(64 * WM * WN) void shift_bf16_kernel(
+template <int BM, int BN, int WM, int WN, int WK, int BK, int NS, int DELTA, bool TRANS_B, bool RAG>
+__global__ __launch_bounds__(64 * WM * WN * WK) void shift_bf16_kernel(
     const bf16* __restrict__ A, const bf16* __restrict__ B1, const bf16* __restrict__ B2,
     bf16* __restrict__ out, int rows, int width, int n) {
-  using C = ShiftCfg<BM, BN, WM, WN, BK>;
+  using C = ShiftCfg<BM, BN, WM, WN, WK, BK, NS>;
   static_assert(DELTA == -1 || DELTA == 1, "");
   constexpr int RB = BN * 2;
   constexpr int OFF0 = DELTA < 0 ? C::HALO : 0;   // LDS row of the block's first row
   extern __shared__ __attribute__((aligned(1024))) bf16 smem[];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave % WM, wn = wave / WM;
+  const int wm = wave % WM, wn = wave / WM % WN, wk = wave / (WM * WN);
   const int tiles_n = RAG ? whole_tiles(width, BN) : width / BN;
   const int tiles_m = (rows + BM - 1) / BM;
   const int tile = xcd_tile(blockIdx.x, tiles_m * tiles_n);
@@ -367,10 +408,11 @@ __global__ __launch_bounds__(64 * WM * WN) void shift_bf16_kernel(
     bf16* sB1 = sA + C::A_ELEMS;
     bf16* sB2 = sB1 + C::B_ELEMS;
 #pragma unroll
-    for (int j = 0; j < C::A_DMA; j++)
-      if (j * C::NW + wave < C::A_BLOCKS)   // wave-uniform
-        dma16(RAG && a_k[j] + kt * BK >= width ? g_zero16 : a_src[j] + kt * BK,
-              sA + (j * C::NW + wave) * 512);
+    for (int j = 0; j < C::A_DMA; j++) {
+      // every wave issues the same number: past the last block, that one again
+      const int b = min(j * C::NW + wave, C::A_BLOCKS - 1);
+      dma16(RAG && a_k[j] + kt * BK >= width ? g_zero16 : a_src[j] + kt * BK, sA + b * 512);
+    }
 #pragma unroll
     for (int j = 0; j < C::B_DMA; j++) {
       const bool pad = RAG && !(b_in[j] && b_k[j] + kt * BK < width);
@@ -434,22 +476,26 @@ __global__ __launch_bounds__(64 * WM * WN) void shift_bf16_kernel(
     }
   };
 
-  constexpr int KK = BK / 16;
+  constexpr int KK = BK / 16 / WK;
+  static_assert(KK * WK * 16 == BK, "");
   constexpr int NMFMA = 2 * C::TM * C::TN;
   constexpr int NDS = 2 * C::TM + 2 * C::TN * (TRANS_B ? 2 : 1);
   const int nk = RAG ? whole_tiles(width, BK) : width / BK;
-  issue(0, 0);
+  // NS-stage ring, as in the mix block
+#pragma unroll
+  for (int st = 0; st < NS - 1; st++)
+    if (st < nk) issue(st, st);
   Frags f[2];
   for (int kt = 0; kt < nk; kt++) {
-    wait_dma();
-    __syncthreads();  // stage kt visible to all waves; buffer (kt-1) % 2 free
-    if (kt + 1 < nk) issue(kt + 1, (kt + 1) & 1);
-    const bf16* sA = smem + (kt & 1) * C::STAGE;
-    load_frags(f[0], sA, 0);
+    wait_stages<NS - 1, C::DPS>(min(nk, kt + NS - 1) - (kt + 1));
+    __syncthreads();  // stage kt visible to all waves; buffer (kt-1) % NS free
+    if (kt + NS - 1 < nk) issue(kt + NS - 1, (kt + NS - 1) % NS);
+    const bf16* sA = smem + (kt % NS) * C::STAGE;
+    load_frags(f[0], sA, wk * KK);
 #pragma unroll
     for (int kk = 0; kk < KK; kk++) {
       if (kk + 1 < KK) {
-        load_frags(f[(kk + 1) & 1], sA, kk + 1);
+        load_frags(f[(kk + 1) & 1], sA, wk * KK + kk + 1);
         mma(f[kk & 1]);
         interleave_front<NMFMA, NDS>();
       } else {
@@ -461,6 +507,32 @@ __global__ __launch_bounds__(64 * WM * WN) void shift_bf16_kernel(
   __syncthreads();  // every wave done with the stage buffers
 
   bf16* sO = smem;
+  if constexpr (WK > 1) {
+    float* hand = (float*)(smem + BM * C::LDO) + (size_t)(wave % (WM * WN)) * C::ACC * 64 + lane;
+    constexpr size_t GROUP = (size_t)WM * WN * C::ACC * 64;
+    if (wk > 0) {
+#pragma unroll
+      for (int t = 0; t < C::TM; t++)
+#pragma unroll
+        for (int u = 0; u < C::TN; u++)
+#pragma unroll
+          for (int e = 0; e < 16; e++)
+            hand[(wk - 1) * GROUP + ((t * C::TN + u) * 16 + e) * 64] = acc[t][u][e];
+    }
+    __syncthreads();
+    if (wk == 0) {
+#pragma unroll
+      for (int g = 0; g < WK - 1; g++)
+#pragma unroll
+        for (int t = 0; t < C::TM; t++)
+#pragma unroll
+          for (int u = 0; u < C::TN; u++)
+#pragma unroll
+            for (int e = 0; e < 16; e++)
+              acc[t][u][e] += hand[g * GROUP + ((t * C::TN + u) * 16 + e) * 64];
+    }
+  }
+  if (wk == 0)
 #pragma unroll
   for (int t = 0; t < C::TM; t++)
 #pragma unroll
@@ -833,15 +905,44 @@ constexpr int MIX_BK = 64;            // contraction slice per pipeline stage
 constexpr int MIX_NS = 2;             // pipeline stages in LDS
 constexpr int DW_BO = 128, DW_BC = 128;
 constexpr int DW_TARGET_BLOCKS = 256;  // split-K blocks aimed for (8 waves each)
-template <int BMP, int BN, int WM, int WN, int BK, int NS, bool TRANS_B, bool RAG = false>
+
+// Block shape of a product of `pairs` row pairs and `width` columns, whose
+// largest tile is 128 pairs x big_cols.  A launch runs in whole rounds of
+// blocks over the 256 CUs, and a round lasts as long as its block, so few rows
+// want small blocks: a lone 128 x 128 block takes as long as 256 of them.
+// Measured per launch (mix, 512 columns, us; small = 32 pairs x 32 columns,
+// mid = 64 x 64, big = 128 x 128; in brackets the rounds):
+//   rows     small     mid       big
+//      64    5.5 (1)   6.8 (1)   11.8 (1)
+//     768    5.5 (1)   7.0 (1)   12.8 (1)
+//    2048    6.3 (1)   7.2 (1)   12.8 (1)
+//    4096   11.2 (2)   7.5 (1)   12.8 (1)
+//    8192              13.4 (2)  13.5 (1)
+//   16384              25.5 (4)  16.4 (1)
+// Three small blocks share a CU (48 KB of LDS each) without slowing much while
+// they are few: up to 512 in one launch.  A mid round costs 4/7 of a 128-column
+// big one, 4/14 of a 256-column and 4/5 of a 64-column one (widths 1024, 192).
+// Weights read transposed need 64 columns at least: the small block is then
+// 32 x 64, 6.6 us at 2048 rows x 512, in one round only.
+enum class Tile { kSmall, kMid, kBig };
+Tile pick_tile(int pairs, int width, int big_cols, bool transposed) {
+  auto blocks = [&](int p, int c) { return (int64_t)((pairs + p - 1) / p) * ((width + c - 1) / c); };
+  auto rounds = [](int64_t b) { return (b + 255) / 256; };
+  if (blocks(32, transposed ? 64 : 32) <= (transposed ? 256 : 512)) return Tile::kSmall;
+  const int big_cost = big_cols == 256 ? 14 : big_cols == 128 ? 7 : 5;
+  return rounds(blocks(64, 64)) * 4 <= rounds(blocks(128, big_cols)) * big_cost ? Tile::kMid
+                                                                                : Tile::kBig;
+}
+
+template <int BMP, int BN, int WM, int WN, int WK, int BK, int NS, bool TRANS_B, bool RAG>
 hipError_t mix_launch(const bf16* A, const bf16* B1, const bf16* B2, bf16* out, int pairs,
                       int width, int d, int partner_lower, int partner_upper, hipStream_t st) {
-  using C = MixCfg<BMP, BN, WM, WN, BK, NS>;
+  using C = MixCfg<BMP, BN, WM, WN, WK, BK, NS>;
   const int blocks = ((pairs + BMP - 1) / BMP) * ((width + BN - 1) / BN);
   const size_t lds = (size_t)C::LDS_ELEMS * sizeof(bf16);
 #define HCMIX_MIX(PL, PU)                                                                   \
   {                                                                                         \
-    auto k = mix_bf16_kernel<BMP, BN, WM, WN, BK, NS, PL, PU, TRANS_B, RAG>;                \
+    auto k = mix_bf16_kernel<BMP, BN, WM, WN, WK, BK, NS, PL, PU, TRANS_B, RAG>;            \
     static std::atomic<unsigned long long> lds_set{0};                                      \
     const hipError_t attr = lds_limit_once(lds_set, (const void*)k, (int)lds);             \
     if (attr != hipSuccess) return attr;                                                    \
@@ -857,14 +958,14 @@ hipError_t mix_launch(const bf16* A, const bf16* B1, const bf16* B2, bf16* out, 
 // The plain product instance (no partner terms): out [rows][N] (row stride
 // ldo) = A [rows][K] B^T with B [N][ldb] k-contiguous, or A B with B [K][ldb]
 // (TRANS_B).  Rows in consecutive pairs (dimension 0).
-template <int BN, int WM, int WN, bool TRANS_B>
+template <int BMP, int BN, int WM, int WN, int WK, int NS, bool TRANS_B>
 hipError_t gemm_launch(const bf16* A, const bf16* B, bf16* out, int rows, int K, int N, int ldb,
                        int ldo, hipStream_t st) {
-  using C = MixCfg<MIX_BMP, BN, WM, WN, MIX_BK, MIX_NS>;
+  using C = MixCfg<BMP, BN, WM, WN, WK, MIX_BK, NS>;
   const int pairs = rows / 2;
-  const int blocks = ((pairs + MIX_BMP - 1) / MIX_BMP) * (N / BN);
+  const int blocks = ((pairs + BMP - 1) / BMP) * (N / BN);
   const size_t lds = (size_t)C::LDS_ELEMS * sizeof(bf16);
-  auto k = mix_bf16_kernel<MIX_BMP, BN, WM, WN, MIX_BK, MIX_NS, false, false, TRANS_B, false>;
+  auto k = mix_bf16_kernel<BMP, BN, WM, WN, WK, MIX_BK, NS, false, false, TRANS_B, false>;
   static std::atomic<unsigned long long> lds_set{0};
   const hipError_t attr = lds_limit_once(lds_set, (const void*)k, (int)lds);
   if (attr != hipSuccess) return attr;
@@ -872,14 +973,13 @@ hipError_t gemm_launch(const bf16* A, const bf16* B, bf16* out, int rows, int K,
   return hipGetLastError();
 }
 
-template <int BN, int WM, int WN, int DELTA, bool TRANS_B, bool RAG = false>
+template <int BM, int BN, int WM, int WN, int WK, int NS, int DELTA, bool TRANS_B, bool RAG>
 hipError_t shift_launch(const bf16* A, const bf16* B1, const bf16* B2, bf16* out, int rows,
                         int width, int n, hipStream_t st) {
-  constexpr int BM = 256;
-  using C = ShiftCfg<BM, BN, WM, WN, MIX_BK>;
+  using C = ShiftCfg<BM, BN, WM, WN, WK, MIX_BK, NS>;
   const int blocks = ((rows + BM - 1) / BM) * ((width + BN - 1) / BN);
   const size_t lds = (size_t)C::LDS_ELEMS * sizeof(bf16);
-  auto k = shift_bf16_kernel<BM, BN, WM, WN, MIX_BK, DELTA, TRANS_B, RAG>;
+  auto k = shift_bf16_kernel<BM, BN, WM, WN, WK, MIX_BK, NS, DELTA, TRANS_B, RAG>;
   static std::atomic<unsigned long long> lds_set{0};
   const hipError_t attr = lds_limit_once(lds_set, (const void*)k, (int)lds);
   if (attr != hipSuccess) return attr;
@@ -887,47 +987,60 @@ hipError_t shift_launch(const bf16* A, const bf16* B1, const bf16* B2, bf16* out
   return hipGetLastError();
 }
 
-template <int DELTA, bool TRANS_B>
+template <int DELTA, bool TRANS_B, bool RAG>
 hipError_t shift_dispatch(const bf16* A, const bf16* B1, const bf16* B2, bf16* out, int rows,
                           int width, int n, hipStream_t st) {
-  if (width % 64 != 0) {
-    if ((width + 63) / 64 % 2 == 0)
-      return shift_launch<128, 2, 2, DELTA, TRANS_B, true>(A, B1, B2, out, rows, width, n, st);
-    return shift_launch<64, 4, 1, DELTA, TRANS_B, true>(A, B1, B2, out, rows, width, n, st);
+  const bool wide = (width + 63) / 64 % 2 == 0;
+  const Tile tile = pick_tile((rows + 1) / 2, width, wide ? 128 : 64, TRANS_B);
+  if (tile == Tile::kSmall) {
+    if constexpr (TRANS_B)
+      return shift_launch<64, 64, 2, 2, 2, 3, DELTA, TRANS_B, RAG>(A, B1, B2, out, rows, width, n, st);
+    else
+      return shift_launch<64, 32, 2, 1, 2, 3, DELTA, TRANS_B, RAG>(A, B1, B2, out, rows, width, n, st);
   }
-  if (width % 128 == 0)
-    return shift_launch<128, 2, 2, DELTA, TRANS_B>(A, B1, B2, out, rows, width, n, st);
-  return shift_launch<64, 4, 1, DELTA, TRANS_B>(A, B1, B2, out, rows, width, n, st);
+  if (tile == Tile::kMid)
+    return shift_launch<128, 64, 4, 1, 1, 3, DELTA, TRANS_B, RAG>(A, B1, B2, out, rows, width, n, st);
+  // eight waves, as the mix kernel: 20.3 -> 19.2 us at 16384 x 512
+  if (wide)
+    return shift_launch<256, 128, 4, 2, 1, 2, DELTA, TRANS_B, RAG>(A, B1, B2, out, rows, width, n, st);
+  return shift_launch<256, 64, 4, 1, 1, 2, DELTA, TRANS_B, RAG>(A, B1, B2, out, rows, width, n, st);
 }
 
-template <bool TRANS_B>
+template <bool TRANS_B, bool RAG>
 hipError_t mix_dispatch(const bf16* A, const bf16* B1, const bf16* B2, bf16* out, int rows,
                         int width, int d, int partner_lower, int partner_upper, hipStream_t st) {
   const int pairs = rows / 2;
-  // Ragged widths: the column tile that pads less, the wide one on a tie.
-  if (width % 64 != 0) {
-    if ((width + 63) / 64 % 2 == 0)
-      return mix_launch<MIX_BMP, 128, 2, 4, MIX_BK, MIX_NS, TRANS_B, true>(
+  const bool wide = (width + 63) / 64 % 2 == 0;
+  const bool widest = !TRANS_B && !RAG && width % 256 == 0 && width >= 1024;
+  const Tile tile = pick_tile(pairs, width, widest ? 256 : wide ? 128 : 64, TRANS_B);
+  if (tile == Tile::kSmall) {
+    if constexpr (TRANS_B)
+      return mix_launch<32, 64, 1, 2, 2, MIX_BK, 3, TRANS_B, RAG>(
           A, B1, B2, out, pairs, width, d, partner_lower, partner_upper, st);
-    return mix_launch<MIX_BMP, 64, 4, 1, MIX_BK, MIX_NS, TRANS_B, true>(
-        A, B1, B2, out, pairs, width, d, partner_lower, partner_upper, st);
+    else
+      return mix_launch<32, 32, 1, 1, 4, MIX_BK, 3, TRANS_B, RAG>(
+          A, B1, B2, out, pairs, width, d, partner_lower, partner_upper, st);
   }
+  if (tile == Tile::kMid)
+    return mix_launch<64, 64, 2, 2, 1, MIX_BK, 3, TRANS_B, RAG>(
+        A, B1, B2, out, pairs, width, d, partner_lower, partner_upper, st);
   // Wide layers (1024 and up): 256-column tiles, 96 flop -> 131 flop per byte
   // moved into the CU, in 32-wide K-steps with three stages (the LDS holds
   // 3 x 48 KB).  Measured at 32768 x 1024: 126-130 -> 119-124 us per forward
   // launch.  Weights read transposed keep the 128-column tile.
-  if constexpr (!TRANS_B) {
-    if (width % 256 == 0 && width >= 1024)
-      return mix_launch<MIX_BMP, 256, 2, 4, 32, 3, TRANS_B>(A, B1, B2, out, pairs, width, d,
-                                                            partner_lower, partner_upper, st);
+  if constexpr (!TRANS_B && !RAG) {
+    if (widest)
+      return mix_launch<MIX_BMP, 256, 2, 4, 1, 32, 3, TRANS_B, RAG>(A, B1, B2, out, pairs, width, d,
+                                                                 partner_lower, partner_upper, st);
   }
   // Two waves per SIMD (8 per block, each 64 pairs x 32 columns): one wave's
   // LDS reads and barrier waits hide under the other's MFMAs.  Measured at
-  // 16384 x 512: dX 18.1 -> 16.8 us, forward unchanged within noise.
-  if (width % 128 == 0)
-    return mix_launch<MIX_BMP, 128, 2, 4, MIX_BK, MIX_NS, TRANS_B>(
+  // 16384 x 512: dX 18.1 -> 16.8 us, forward unchanged within noise.  (Ragged
+  // widths: the column tile that pads less, the wide one on a tie.)
+  if (wide)
+    return mix_launch<MIX_BMP, 128, 2, 4, 1, MIX_BK, MIX_NS, TRANS_B, RAG>(
         A, B1, B2, out, pairs, width, d, partner_lower, partner_upper, st);
-  return mix_launch<MIX_BMP, 64, 4, 1, MIX_BK, MIX_NS, TRANS_B>(
+  return mix_launch<MIX_BMP, 64, 4, 1, 1, MIX_BK, MIX_NS, TRANS_B, RAG>(
       A, B1, B2, out, pairs, width, d, partner_lower, partner_upper, st);
 }
 
@@ -996,19 +1109,29 @@ hipError_t dw_launch(const bf16* X, const bf16* dY, float* partial, int pairs, i
 
 hipError_t launch_gemm_bf16(const bf16* A, const bf16* B, bf16* out, int rows, int K, int N,
                             int ldb, int ldo, bool transpose_b, hipStream_t st) {
-  if (N % 128 == 0)
-    return transpose_b ? gemm_launch<128, 2, 4, true>(A, B, out, rows, K, N, ldb, ldo, st)
-                       : gemm_launch<128, 2, 4, false>(A, B, out, rows, K, N, ldb, ldo, st);
-  return transpose_b ? gemm_launch<64, 4, 1, true>(A, B, out, rows, K, N, ldb, ldo, st)
-                     : gemm_launch<64, 4, 1, false>(A, B, out, rows, K, N, ldb, ldo, st);
+#define HCMIX_GEMM(BMP, BN, WM, WN, WK, NS)                                                       \
+  (transpose_b ? gemm_launch<BMP, BN, WM, WN, WK, NS, true>(A, B, out, rows, K, N, ldb, ldo, st)  \
+               : gemm_launch<BMP, BN, WM, WN, WK, NS, false>(A, B, out, rows, K, N, ldb, ldo, st))
+  const bool wide = N % 128 == 0;
+  const Tile tile = pick_tile(rows / 2, N, wide ? 128 : 64, transpose_b);
+  if (tile == Tile::kSmall)
+    return transpose_b
+               ? gemm_launch<32, 64, 1, 2, 2, 3, true>(A, B, out, rows, K, N, ldb, ldo, st)
+               : gemm_launch<32, 32, 1, 1, 4, 3, false>(A, B, out, rows, K, N, ldb, ldo, st);
+  if (tile == Tile::kMid) return HCMIX_GEMM(64, 64, 2, 2, 1, 3);
+  if (wide) return HCMIX_GEMM(MIX_BMP, 128, 2, 4, 1, MIX_NS);
+  return HCMIX_GEMM(MIX_BMP, 64, 4, 1, 1, MIX_NS);
+#undef HCMIX_GEMM
 }
 
 hipError_t launch_mix_bf16(const bf16* A, const bf16* B1, const bf16* B2, bf16* out, int rows,
                            int width, int d, int partner_lower, int partner_upper,
                            bool transpose_b, hipStream_t st) {
-  if (transpose_b)
-    return mix_dispatch<true>(A, B1, B2, out, rows, width, d, partner_lower, partner_upper, st);
-  return mix_dispatch<false>(A, B1, B2, out, rows, width, d, partner_lower, partner_upper, st);
+#define HCMIX_MIXD(T, R) \
+  mix_dispatch<T, R>(A, B1, B2, out, rows, width, d, partner_lower, partner_upper, st)
+  if (width % 64 == 0) return transpose_b ? HCMIX_MIXD(true, false) : HCMIX_MIXD(false, false);
+  return transpose_b ? HCMIX_MIXD(true, true) : HCMIX_MIXD(false, true);
+#undef HCMIX_MIXD
 }
 
 hipError_t launch_transpose_bf16(const TransposeArgs& a, int count, hipStream_t st) {
@@ -1019,11 +1142,12 @@ hipError_t launch_transpose_bf16(const TransposeArgs& a, int count, hipStream_t 
 
 hipError_t launch_shift_bf16(const bf16* A, const bf16* B1, const bf16* B2, bf16* out, int rows,
                              int width, int n, int delta, bool transpose_b, hipStream_t st) {
-  if (delta < 0)
-    return transpose_b ? shift_dispatch<-1, true>(A, B1, B2, out, rows, width, n, st)
-                       : shift_dispatch<-1, false>(A, B1, B2, out, rows, width, n, st);
-  return transpose_b ? shift_dispatch<1, true>(A, B1, B2, out, rows, width, n, st)
-                     : shift_dispatch<1, false>(A, B1, B2, out, rows, width, n, st);
+#define HCMIX_SHIFT(D, T)                                                             \
+  (width % 64 == 0 ? shift_dispatch<D, T, false>(A, B1, B2, out, rows, width, n, st) \
+                   : shift_dispatch<D, T, true>(A, B1, B2, out, rows, width, n, st))
+  if (delta < 0) return transpose_b ? HCMIX_SHIFT(-1, true) : HCMIX_SHIFT(-1, false);
+  return transpose_b ? HCMIX_SHIFT(1, true) : HCMIX_SHIFT(1, false);
+#undef HCMIX_SHIFT
 }
 
 hipError_t launch_dw_reduce(const DwReduce& r, int width, hipStream_t st) {

@@ -1,0 +1,63 @@
+"""Every block shape of the mixing, local and linear products (few rows to
+many), at its tiles' edges: row counts that leave a tile ragged, widths of an
+odd number of 64-column tiles, weights read as given and transposed.  Against
+the CPU oracle (the linear maps against their definition)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2609_18145_amd import hcmix, inputs
+from tests.util import TOL, fro_rel_err, row_rel_err, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    hcmix.load()
+
+
+# (batch, n, width): small, mid and big blocks of both kinds of width
+SHAPES = [(3, 2, 64), (35, 2, 448), (3, 256, 512), (33, 64, 512), (63, 64, 512), (129, 64, 512),
+          (33, 128, 192), (65, 256, 192), (1, 1024, 1024), (5, 512, 1024), (9, 1024, 1024),
+          (33, 64, 200), (130, 64, 328)]
+
+
+@pytest.mark.parametrize("batch,n,width", SHAPES)
+@pytest.mark.parametrize("layer", [0, 5, -1])
+def test_layer_and_stack_dx(batch, n, width, layer):
+    print(f"case: {batch}x{n}x{width} layer={layer}", flush=True)
+    code, ref = (hcmix.LAYER_NEAR, oracle.NEAR) if layer < 0 else (layer, layer)
+    x, ws, wo, dy = inputs.make_layer(batch, n, width, "bf16", seed=width + n)
+    tx, tws, two, tdy = (to_dev(a, "bf16") for a in (x, ws, wo, dy))
+    y = hcmix.forward(tx, tws, two, code, True)
+    dx, dws, dwo = hcmix.backward(tx, tws, two, tdy, code, True)
+    # a two-layer data chain: the same products on transposed copies
+    dx2, grads = hcmix.stack_backward_data([tws] * 2, [two] * 2, [code] * 2, tdy, True)
+    torch.cuda.synchronize()
+    ry = oracle.forward(x, ws, wo, ref, True)
+    rdx, rws, rwo = oracle.backward(x, ws, wo, dy, ref, True)
+    assert row_rel_err(to_host(y), ry) <= TOL["bf16"]
+    assert row_rel_err(to_host(dx), rdx) <= TOL["bf16"]
+    assert row_rel_err(to_host(grads[0]), rdx) <= TOL["bf16"]
+    assert fro_rel_err(to_host(dws), rws) <= 1e-4 and fro_rel_err(to_host(dwo), rwo) <= 1e-4
+
+
+@pytest.mark.parametrize("rows,n_in,n_out", [(2, 64, 64), (70, 128, 448), (770, 512, 1536),
+                                             (2050, 512, 512), (4098, 192, 512),
+                                             (8200, 512, 192)])
+def test_linear(rows, n_in, n_out):
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    x = torch.randn(rows, n_in, generator=g, device="cuda").bfloat16()
+    w = (torch.randn(n_out, n_in, generator=g, device="cuda") * n_in ** -0.5).bfloat16()
+    dy = torch.randn(rows, n_out, generator=g, device="cuda").bfloat16()
+    y = hcmix.linear_forward(x, w)
+    dx, dw = hcmix.linear_backward(x, w, dy)
+    torch.cuda.synchronize()
+    xd, wd, gd = (t.double().cpu().numpy() for t in (x, w, dy))
+    assert row_rel_err(to_host(y), xd @ wd.T) <= TOL["bf16"]
+    assert row_rel_err(to_host(dx), gd @ wd) <= TOL["bf16"]
+    assert fro_rel_err(to_host(dw), gd.T @ xd) <= 1e-4
