@@ -4,27 +4,39 @@
 //   A_l[i] = T_l[i][i],  B_l[i] = m(i) T_l[i][p(i)].
 // Every channel is independent, so a block owns one window and one slice of
 // channels (8 pieces of 16 bytes in memory: 64 bf16 or 32 fp32 channels) and
-// keeps that tile in LDS, in fp32, through every layer of the stack: the
+// keeps that tile in registers, in fp32, through every layer of the stack: the
 // forward reads x_0 once and writes each layer's output once (rounded to the
 // storage type; the chain itself goes on in fp32), and the backward reads dy
 // once and each saved input once, and writes dx once.  The work is a handful
-// of FMAs per element, so HBM bandwidth bounds it.
+// of FMAs per element, so HBM bandwidth bounds it, and what a layer adds on
+// top (exchanging partners, barriers, waiting for its coefficients) has to
+// stay out of the stream's way.
 //
 // Thread mapping (256 threads): thread tid owns memory piece k = tid % 8 of
 // the positions tid / 8 + 32 j.  A wave covers 8 consecutive positions, and
-// its global accesses are 128 contiguous bytes per position.  In LDS a row
-// holds the slice in fp32 (256 bytes for bf16 slices, two 16-byte LDS pieces
-// per thread, the pair swapped on odd rows; 128 bytes for fp32 slices): each
-// 16-lane group of a read then covers two rows in distinct banks, for its
-// own rows and for the partner rows alike (a stride of 8 or more maps 8
-// consecutive rows onto 8 consecutive rows; a smaller stride or the local
-// layer keeps neighbouring rows of opposite parity).
+// its global accesses are 128 contiguous bytes per position.  So the partner
+// along dimension d is
+//   d = 0, 1, 2: in another lane of the wave (lane ^ 8, 16, 32: lane moves);
+//   d = 3, 4 (and the local layer's neighbour): in another wave (through LDS);
+//   d = 5, 6, 7: in another register of the same thread.
+// Only the middle case needs LDS and barriers.  The coefficients of up to 16
+// layers are read ahead into LDS at once: read layer by layer, each layer
+// waited for them (a gather of one line per position).
+// Measured at 64 windows x 256 x 512 bf16, 16 layers, us per launch: forward
+// 57.4 (62.6 with the tile in LDS), backward 82.9 (94.0); 285 and 306 MB at a
+// device copy's 5.2 TB/s are 55 and 59.  The forward takes 512 threads (four
+// positions each, dimension 5 through LDS too: 57 against 65 us), the backward
+// 256, whose gradients and prefetched inputs do not fit 128 registers.
 #include "device_common.h"
 #include "hcmix_internal.h"
+
+#include <type_traits>
 
 namespace hcmix {
 
 namespace {
+
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int SH_THREADS = 256;
 constexpr int SH_PIECES = 8;   // 16-byte pieces of a row that one block owns
@@ -106,15 +118,30 @@ __device__ __forceinline__ float sum8(float v) {
   return v + dpp_move<0x141>(v);   // row_half_mirror: lane l of 8 <- lane 7 - l
 }
 
-// (A_l[i], B_l[i]) of every position of layer l into coef[0 .. n).
-__device__ __forceinline__ void load_coef(const float* __restrict__ tab, int d, int n, int bidir,
-                                          float2* coef) {
-  for (int i = threadIdx.x; i < n; i += SH_THREADS) {
-    bool takes;
-    const int p = fwd_partner(i, d, bidir, &takes);
-    const float a = tab[(size_t)i * n + i];
-    const float b = takes ? tab[(size_t)i * n + p] : 0.f;
-    coef[i] = make_float2(a, b);
+// (A_l[i], B_l[i]) of every position of layers l0 .. l0 + count - 1 (at most
+// SH_COEF) into coef[l % SH_COEF][i], U layers' loads in flight: all of them
+// before the tile is loaded, few once it fills the registers.
+constexpr int SH_COEF = 16;
+template <int U>
+__device__ __forceinline__ void load_coefs(const float* const* tabs, const int* dims, int l0,
+                                           int count, int n, int bidir, float2* coef) {
+  const int i = threadIdx.x;
+  if (i >= n) return;
+#pragma unroll 1
+  for (int u0 = 0; u0 < count; u0 += U) {
+    float ca[U], cb[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const int l = l0 + min(u0 + u, count - 1);
+      bool takes;
+      const int p = fwd_partner(i, dims[l], bidir, &takes);
+      const float* row = tabs[l] + (size_t)i * n;
+      ca[u] = row[i];
+      cb[u] = takes ? row[p] : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < U; u++)
+      if (u0 + u < count) coef[((l0 + u0 + u) % SH_COEF) * n + i] = make_float2(ca[u], cb[u]);
   }
 }
 
@@ -154,160 +181,252 @@ __device__ __forceinline__ Piece<E> lds_get(const f32x4* tile, int i, int k) {
   return p;
 }
 
-constexpr int SH_MAX_J = kSharedMaxN / (SH_THREADS / SH_PIECES);   // positions per thread
-
-template <typename E>
-__global__ __launch_bounds__(SH_THREADS) void shared_fwd_kernel(SharedFwdArgs a) {
-  using S = Slice<E>;
-  constexpr int V = S::V;
-  const int n = a.n, width = a.width;
-  const int chunks = width / (SH_PIECES * V);
-  const int t = blockIdx.x / chunks;
-  const int c0 = (blockIdx.x % chunks) * SH_PIECES * V;
-  extern __shared__ __align__(16) unsigned char smem[];
-  f32x4* tile = (f32x4*)smem;
-  float2* coef = (float2*)(tile + n * S::ROW);   // [2][n]
-  const int k = threadIdx.x % SH_PIECES;
-  const int i0 = threadIdx.x / SH_PIECES;
-  const int nj = n > i0 ? (n - i0 + 31) / 32 : 0;
-  const size_t row0 = (size_t)t * n;
-  const E* x0 = (const E*)a.x0;
-
-  for (int j = 0; j < nj; j++) {
-    const int i = i0 + 32 * j;
-    lds_put<E>(tile, i, k, unpack<E>(*(const u32x4*)(x0 + (row0 + i) * width + c0 + k * V)));
-  }
-  load_coef(a.tab[0], a.dim[0], n, a.bidir, coef);
-  __syncthreads();
-
-  for (int l = 0; l < a.num_layers; l++) {
-    const float2* cf = coef + (l & 1) * n;
-    // the next layer's coefficients go to the other half, last read a layer ago
-    if (l + 1 < a.num_layers)
-      load_coef(a.tab[l + 1], a.dim[l + 1], n, a.bidir, coef + ((l + 1) & 1) * n);
-    const int d = a.dim[l];
-    E* out = (E*)a.xs[l];
-    Piece<E> y[SH_MAX_J];
-#pragma unroll
-    for (int j = 0; j < SH_MAX_J; j++) {
-      if (j < nj) {
-        const int i = i0 + 32 * j;
-        bool takes;
-        const int p = fwd_partner(i, d, a.bidir, &takes);
-        const float2 ab = cf[i];
-        const Piece<E> xs = lds_get<E>(tile, i, k);
-        const Piece<E> xp = lds_get<E>(tile, p, k);
-#pragma unroll
-        for (int v = 0; v < V; v++)
-          y[j].v[v] = takes ? fmaf(ab.y, xp.v[v], ab.x * xs.v[v]) : ab.x * xs.v[v];
-        *(global_u32x4*)(out + (row0 + i) * width + c0 + k * V) = pack<E>(y[j]);
-      }
-    }
-    __syncthreads();    // every read of this layer's input is done
-#pragma unroll
-    for (int j = 0; j < SH_MAX_J; j++)
-      if (j < nj) lds_put<E>(tile, i0 + 32 * j, k, y[j]);
-    __syncthreads();
+// Value of lane ^ (8 << D), D = 0, 1, 2.
+template <int D>
+__device__ __forceinline__ float lane_partner(float x) {
+  if constexpr (D == 0) return dpp_move<0x128>(x);   // row_ror:8 of 16 lanes
+  const unsigned u = __float_as_uint(x);
+  const bool up = (threadIdx.x >> (3 + D)) & 1;
+  // the swap leaves the lower halves' values in [0], the upper halves' in [1]
+  if constexpr (D == 1) {
+    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    return __uint_as_float(up ? r[0] : r[1]);
+  } else {
+    const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return __uint_as_float(up ? r[0] : r[1]);
   }
 }
 
+// Rows exchanged through LDS at a time: four positions per thread (128 rows,
+// 32 KB of bf16 slices), and one row beyond them for the local layer.
+constexpr int SH_ROWS = 128;
 template <typename E>
-__global__ __launch_bounds__(SH_THREADS) void shared_bwd_kernel(SharedBwdArgs a) {
+constexpr size_t shared_exchange_bytes(int n) {
+  return (size_t)((n < SH_ROWS ? n : SH_ROWS) + 1) * SH_PIECES * Slice<E>::V * 4;
+}
+
+// Calls f(j, p) once for every position i0 + 32 j of this thread, p being the
+// row of its partner as it was before any of these calls (f may change s[j]):
+// XOR 2^d for d >= 0, i + near for the local layer (near = -1 or 1; the row
+// itself where that leaves the window).  `tile` is the LDS exchange buffer;
+// every thread of the block calls this with the same d.
+template <typename E, int NJ, int PJ, typename F>
+__device__ __forceinline__ void for_partners(const Piece<E> (&s)[NJ], int d, int near, int n, int i0,
+                                             int k, f32x4* tile, F f) {
+  constexpr int V = Slice<E>::V;
+#define HCMIX_REGS(B)                                                       \
+  if (d >= 0 && NJ > (1 << B) && (1 << d) == (PJ << B)) {                                        \
+    _Pragma("unroll") for (int j = 0; j < NJ; j++) {                        \
+      constexpr int M = 1 << B;                                             \
+      if (j & M) continue;                                                  \
+      const Piece<E> lo = s[j], hi = s[(j + M) % NJ];                       \
+      f(j, hi);                                                             \
+      f((j + M) % NJ, lo);                                                  \
+    }                                                                       \
+    return;                                                                 \
+  }
+#define HCMIX_LANES(D)                                                      \
+  if (d == D) {                                                             \
+    _Pragma("unroll") for (int j = 0; j < NJ; j++) {                        \
+      Piece<E> p;                                                           \
+      _Pragma("unroll") for (int v = 0; v < V; v++)                         \
+          p.v[v] = lane_partner<D>(s[j].v[v]);                              \
+      f(j, p);                                                              \
+    }                                                                       \
+    return;                                                                 \
+  }
+  HCMIX_REGS(0)
+  HCMIX_REGS(1)
+  HCMIX_REGS(2)
+  HCMIX_LANES(0)
+  HCMIX_LANES(1)
+  HCMIX_LANES(2)
+#undef HCMIX_LANES
+#undef HCMIX_REGS
+  // through LDS, SH_XJ positions per thread at a time; the local layer takes
+  // the group first whose outer neighbour belongs to the other
+  constexpr int G = NJ < SH_ROWS / PJ ? NJ : SH_ROWS / PJ;
+  const int rows = min(n, PJ * G);
+  auto group = [&](auto at_group) {
+    constexpr int j0 = decltype(at_group)::value * G;
+    const int base = PJ * j0;
+    __syncthreads();    // every read of the buffer is done
+    if (i0 < n) {
+#pragma unroll
+      for (int j = 0; j < G; j++) lds_put<E>(tile, i0 + PJ * j, k, s[j0 + j]);
+      if (j0 > 0 && d < 0 && near < 0 && i0 == PJ - 1) lds_put<E>(tile, rows, k, s[(j0 + NJ - 1) % NJ]);
+      if (j0 + G < NJ && d < 0 && near > 0 && i0 == 0) lds_put<E>(tile, rows, k, s[(j0 + G) % NJ]);
+    }
+    __syncthreads();
+    if (i0 < n)
+#pragma unroll
+      for (int j = 0; j < G; j++) {
+        const int i = base + i0 + PJ * j;
+        int q = i;
+        if (d >= 0) q = i ^ (1 << d);
+        else if (i + near >= 0 && i + near < n) q = i + near;
+        const int at = q - base;
+        f(j0 + j, lds_get<E>(tile, at < 0 || at >= rows ? rows : at, k));
+      }
+  };
+  if constexpr (NJ == G) {
+    group(std::integral_constant<int, 0>{});
+  } else if (near < 0) {
+    group(std::integral_constant<int, 1>{});
+    group(std::integral_constant<int, 0>{});
+  } else {
+    group(std::integral_constant<int, 0>{});
+    group(std::integral_constant<int, 1>{});
+  }
+}
+
+template <typename E, int NJ, int T>
+__global__ __launch_bounds__(T, T / 128) void shared_fwd_kernel(SharedFwdArgs a) {
   using S = Slice<E>;
-  constexpr int V = S::V;
+  constexpr int V = S::V, PJ = T / SH_PIECES;
   const int n = a.n, width = a.width;
   const int chunks = width / (SH_PIECES * V);
   const int t = blockIdx.x / chunks;
   const int c0 = (blockIdx.x % chunks) * SH_PIECES * V;
   extern __shared__ __align__(16) unsigned char smem[];
   f32x4* tile = (f32x4*)smem;
-  float2* coef = (float2*)(tile + n * S::ROW);
+  float2* coef = (float2*)(smem + shared_exchange_bytes<E>(n));   // [SH_COEF][n]
   const int k = threadIdx.x % SH_PIECES;
   const int i0 = threadIdx.x / SH_PIECES;
-  const int nj = n > i0 ? (n - i0 + 31) / 32 : 0;
-  const size_t row0 = (size_t)t * n;
+  const bool mine = i0 < n;
+  const size_t at0 = ((size_t)t * n + i0) * width + c0 + k * V;
+  const size_t step = (size_t)PJ * width;
+  const E* x0 = (const E*)a.x0;
+
+  u32x4 first[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; j++)
+    first[j] = mine ? *(const u32x4*)(x0 + at0 + j * step) : u32x4{0u, 0u, 0u, 0u};
+  load_coefs<SH_COEF>(a.tab, a.dim, 0, min(SH_COEF, a.num_layers), n, a.bidir, coef);
+  __syncthreads();
+  Piece<E> x[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; j++) x[j] = unpack<E>(first[j]);
+
+  for (int l = 0; l < a.num_layers; l++) {
+    if (l > 0 && l % SH_COEF == 0) {
+      __syncthreads();
+      load_coefs<2>(a.tab, a.dim, l, min(SH_COEF, a.num_layers - l), n, a.bidir, coef);
+      __syncthreads();
+    }
+    const float2* cf = coef + (l % SH_COEF) * n;
+    const int d = a.dim[l];
+    E* out = (E*)a.xs[l];
+    for_partners<E, NJ, PJ>(x, d, -1, n, i0, k, tile, [&](int j, const Piece<E>& p) {
+      if (!mine) return;
+      const int i = i0 + PJ * j;
+      bool takes;
+      fwd_partner(i, d, a.bidir, &takes);
+      const float2 ab = cf[i];
+#pragma unroll
+      for (int v = 0; v < V; v++)
+        x[j].v[v] = takes ? fmaf(ab.y, p.v[v], ab.x * x[j].v[v]) : ab.x * x[j].v[v];
+      store_wt16(out + at0 + j * step, pack<E>(x[j]));
+    });
+  }
+}
+
+template <typename E, int NJ, int T>
+__global__ __launch_bounds__(T, T / 128) void shared_bwd_kernel(SharedBwdArgs a) {
+  using S = Slice<E>;
+  constexpr int V = S::V, PJ = T / SH_PIECES;
+  const int n = a.n, width = a.width;
+  const int chunks = width / (SH_PIECES * V);
+  const int t = blockIdx.x / chunks;
+  const int c0 = (blockIdx.x % chunks) * SH_PIECES * V;
+  extern __shared__ __align__(16) unsigned char smem[];
+  f32x4* tile = (f32x4*)smem;
+  float2* coef = (float2*)(smem + shared_exchange_bytes<E>(n));
+  const int k = threadIdx.x % SH_PIECES;
+  const int i0 = threadIdx.x / SH_PIECES;
+  const bool mine = i0 < n;
+  const size_t at0 = ((size_t)t * n + i0) * width + c0 + k * V;
+  const size_t step = (size_t)PJ * width;
   const int L = a.num_layers;
   const E* dy = (const E*)a.dy;
 
-  for (int j = 0; j < nj; j++) {
-    const int i = i0 + 32 * j;
-    lds_put<E>(tile, i, k, unpack<E>(*(const u32x4*)(dy + (row0 + i) * width + c0 + k * V)));
-  }
-  load_coef(a.tab[L - 1], a.dim[L - 1], n, a.bidir, coef + ((L - 1) & 1) * n);
-  __syncthreads();
-
-  // x_l rows of the layer to come, loaded one layer ahead so that their
-  // latency passes under the barriers and LDS work of the layer before
-  // (issued inside the layer, they would cost one memory latency per
-  // position and layer).  Only the thread's own rows: the partner term of
-  // dT, sum over c of g[r][c] x[i][c] for the receiver r of i, is formed by
-  // i's thread, which holds x[i] and reads g[r] for dX anyway.
-  u32x4 xo[SH_MAX_J];
-  auto fetch_x = [&](int l) {
-    const E* x = (const E*)a.xs[l];
-#pragma unroll
-    for (int j = 0; j < SH_MAX_J; j++)
-      if (j < nj) xo[j] = *(const u32x4*)(x + (row0 + i0 + 32 * j) * width + c0 + k * V);
+  // g: the gradient of the layer's output; x_l rows are loaded a layer ahead.
+  // Only the thread's own rows: the partner term of dT, sum over c of
+  // g[r][c] x[i][c] for the receiver r of i, is formed by i's thread, which
+  // holds x[i] and needs g[r] for dX anyway.
+  Piece<E> g[NJ];
+  u32x4 xo[NJ];
+  auto fetch = [&](const E* src, int j) {   // read once: 84.5 -> 82.9 us as non-temporal
+    return mine ? __builtin_nontemporal_load((const u32x4*)(src + at0 + j * step))
+                : u32x4{0u, 0u, 0u, 0u};
   };
-  fetch_x(L - 1);
-
-  for (int l = L - 1; l >= 0; l--) {
-    // the tile holds g, the gradient of layer l's output
-    const float2* cf = coef + (l & 1) * n;
-    if (l > 0) load_coef(a.tab[l - 1], a.dim[l - 1], n, a.bidir, coef + ((l - 1) & 1) * n);
-    const int d = a.dim[l];
-    float* part = a.partial + ((size_t)l * gridDim.x + blockIdx.x) * n * 2;
-    Piece<E> g[SH_MAX_J];
 #pragma unroll
-    for (int j = 0; j < SH_MAX_J; j++) {
-      if (j < nj) {
-        const int i = i0 + 32 * j;
-        bool takes, sends;
-        fwd_partner(i, d, a.bidir, &takes);
-        const int r = receiver(i, d, n, a.bidir, &sends);
-        // i sends to r exactly when r takes i: every partner slot of the
-        // layer is written once, by the sender or (no sender) as zero
-        const float ai = cf[i].x;
-        const float cr = sends ? cf[r].y : 0.f;
-        const Piece<E> gi = lds_get<E>(tile, i, k);
-        const Piece<E> gr = lds_get<E>(tile, r, k);
-        const Piece<E> xi = unpack<E>(xo[j]);
-        float sd = 0.f, so = 0.f;
-#pragma unroll
-        for (int v = 0; v < V; v++) {
-          g[j].v[v] = sends ? fmaf(cr, gr.v[v], ai * gi.v[v]) : ai * gi.v[v];
-          sd = fmaf(gi.v[v], xi.v[v], sd);
-          so = fmaf(gr.v[v], xi.v[v], so);
-        }
-        if (l == 0)
-          *(global_u32x4*)((E*)a.dx + (row0 + i) * width + c0 + k * V) = pack<E>(g[j]);
-        // the 8 pieces of position i sit in an aligned group of 8 lanes:
-        // fixed-order sum, then the piece-0 lane writes the sums: the
-        // diagonal one of i, and the partner one of i's receiver (or, when
-        // nobody sends to i, a zero for i's own partner slot)
-        sd = sum8(sd);
-        so = sum8(so);
-        if (k == 0) {
-          part[2 * i] = sd;
-          if (sends) part[2 * r + 1] = so;
-          if (!takes) part[2 * i + 1] = 0.f;
-        }
-      }
-    }
-    if (l > 0) fetch_x(l - 1);
-    __syncthreads();    // every read of g is done
-    if (l > 0) {
-#pragma unroll
-      for (int j = 0; j < SH_MAX_J; j++)
-        if (j < nj) lds_put<E>(tile, i0 + 32 * j, k, g[j]);
-    }
+  for (int j = 0; j < NJ; j++) xo[j] = fetch(dy, j);
+  {
+    const int lo = (L - 1) / SH_COEF * SH_COEF;
+    load_coefs<SH_COEF>(a.tab, a.dim, lo, L - lo, n, a.bidir, coef);
     __syncthreads();
   }
+#pragma unroll
+  for (int j = 0; j < NJ; j++) g[j] = unpack<E>(xo[j]);
+#pragma unroll
+  for (int j = 0; j < NJ; j++) xo[j] = fetch((const E*)a.xs[L - 1], j);
+
+  for (int l = L - 1; l >= 0; l--) {
+    if (l < L - 1 && l % SH_COEF == SH_COEF - 1) {
+      __syncthreads();
+      load_coefs<2>(a.tab, a.dim, l - (SH_COEF - 1), SH_COEF, n, a.bidir, coef);
+      __syncthreads();
+    }
+    const E* xnext = (const E*)a.xs[l > 0 ? l - 1 : 0];
+    const float2* cf = coef + (l % SH_COEF) * n;
+    const int d = a.dim[l];
+    float keep_d = 0.f, keep_o = 0.f;
+    for_partners<E, NJ, PJ>(g, d, 1, n, i0, k, tile, [&](int j, const Piece<E>& p) {
+      if (!mine) return;
+      const int i = i0 + PJ * j;
+      bool sends;
+      const int r = receiver(i, d, n, a.bidir, &sends);
+      const float ai = cf[i].x;
+      const float cr = sends ? cf[r].y : 0.f;
+      const Piece<E> xi = unpack<E>(xo[j]);
+      xo[j] = fetch(xnext, j);     // the next layer's, once this one's is taken
+      float sd = 0.f, so = 0.f;
+#pragma unroll
+      for (int v = 0; v < V; v++) {
+        sd = fmaf(g[j].v[v], xi.v[v], sd);
+        so = fmaf(p.v[v], xi.v[v], so);
+        g[j].v[v] = sends ? fmaf(cr, p.v[v], ai * g[j].v[v]) : ai * g[j].v[v];
+      }
+      // the 8 pieces of position i sit in an aligned group of 8 lanes:
+      // fixed-order sum, kept by lane j of the group
+      sd = sum8(sd);
+      so = sum8(so);
+      keep_d = k == j ? sd : keep_d;
+      keep_o = k == (NJ == SH_PIECES / 2 ? j + NJ : j) ? so : keep_o;
+    });
+    if (!mine) continue;
+    // both sums of every position: dT[i][i] and, where i sends, dT[r][i].  One
+    // store per lane and layer, of the same number every layer, so that
+    // waiting for the next layer's x does not wait for the stores too.
+    float* part = a.partial + (((size_t)l * gridDim.x + blockIdx.x) * n + i0) * 2;
+    if constexpr (NJ == SH_PIECES)
+      *(__attribute__((address_space(1))) f32x2*)(part + 2 * PJ * k) = f32x2{keep_d, keep_o};
+    else if constexpr (NJ == SH_PIECES / 2)
+      *(__attribute__((address_space(1))) float*)(part + 2 * PJ * (k % NJ) + k / NJ) = k < NJ ? keep_d : keep_o;
+    else if (k < NJ)
+      *(__attribute__((address_space(1))) f32x2*)(part + 2 * PJ * k) = f32x2{keep_d, keep_o};
+  }
+  if (!mine) return;
+#pragma unroll
+  for (int j = 0; j < NJ; j++)
+    *(global_u32x4*)((E*)a.dx + at0 + j * step) = pack<E>(g[j]);
 }
 
-// dT_l: the two sums of every position over all blocks (window x channel
-// slice), then the table gradient's rows (zero off the layer's links unless
-// accumulating).  Block = (layer, 16 positions: 128 contiguous bytes of
+// dT_l: the two sums of every position i over all blocks (window x channel
+// slice), then the table gradient: dT[i][i], dT[r][i] for the receiver r that
+// i sends to, and zeros over the rest of i's row (unless accumulating; the
+// entry of i's own partner is written by the partner's block).  Block = (layer, 16 positions: 128 contiguous bytes of
 // every block's partials), 512 threads = 32 sums (16 positions x 2) x 16
 // block classes: thread (q, v) adds the blocks b = q, q + 16, ... in order,
 // and the 16 class sums are added in a fixed tree.
@@ -355,17 +474,20 @@ __global__ __launch_bounds__(SH_RED_THREADS) void shared_dt_reduce_kernel(Shared
   __syncthreads();
   float* dt = a.dt[l];
   const int d = a.dim[l];
-  for (int e = threadIdx.x; e < rows * n; e += SH_RED_THREADS) {
-    const int row = i_base + e / n, j = e % n;
-    bool takes;
-    const int p = fwd_partner(row, d, a.bidir, &takes);
-    const bool diag = j == row, off = takes && j == p;
-    const float val = diag ? sums[2 * (row - i_base)] : off ? sums[2 * (row - i_base) + 1] : 0.f;
-    float* o = dt + (size_t)row * n + j;
-    if (a.accumulate) {
-      if (diag || off) *o += val;
-    } else {
-      *o = val;
+  if (!a.accumulate)
+    for (int e = threadIdx.x; e < rows * n; e += SH_RED_THREADS) {
+      const int row = i_base + e / n, j = e % n;
+      bool takes;
+      const int p = fwd_partner(row, d, a.bidir, &takes);
+      if (j != row && !(takes && j == p)) dt[(size_t)row * n + j] = 0.f;
+    }
+  if (threadIdx.x < 2 * rows) {
+    const int i = i_base + threadIdx.x / 2, off = threadIdx.x & 1;
+    bool sends;
+    const int r = receiver(i, d, n, a.bidir, &sends);
+    if (!off || sends) {
+      float* o = dt + (size_t)(off ? r : i) * n + i;
+      *o = a.accumulate ? *o + sums[threadIdx.x] : sums[threadIdx.x];
     }
   }
 }
@@ -378,9 +500,11 @@ bool shared_stack_eligible(int64_t n, int64_t width, int32_t num_layers, int32_t
          num_layers <= kSharedMaxLayers;
 }
 
-// The fp32 tile (4 bytes per channel) and two layers' coefficients.
-static size_t shared_lds_bytes(int n, int elem_bytes) {
-  return (size_t)n * SH_PIECES * (16 / elem_bytes) * 4 + (size_t)2 * n * sizeof(float2);
+// The exchange buffer and 16 layers' coefficients: 66 KB at n = 256, two
+// blocks per CU.
+template <typename E>
+static size_t shared_lds_bytes(int n) {
+  return shared_exchange_bytes<E>(n) + (size_t)SH_COEF * n * sizeof(float2);
 }
 
 static int shared_blocks(int batch, int width, int elem_bytes) {
@@ -393,43 +517,45 @@ size_t shared_partial_bytes(int64_t batch, int64_t n, int64_t width, int32_t num
          sizeof(float);
 }
 
+template <typename K, typename A>
+static hipError_t shared_launch(K k, int threads, const A& a, int blocks, size_t lds,
+                                std::atomic<unsigned long long>& lds_set, hipStream_t st) {
+  const hipError_t attr = lds_limit_once(lds_set, (const void*)k, (int)lds);
+  if (attr != hipSuccess) return attr;
+  k<<<blocks, threads, lds, st>>>(a);
+  return hipGetLastError();
+}
+
+// Threads and positions per thread (NJ) by n.
+#define HCMIX_SHARED_CASES(KERNEL, E, T128, T256, ARGS, BLOCKS)                                   \
+  {                                                                                               \
+    static std::atomic<unsigned long long> lds_set[4];                                            \
+    const size_t lds = shared_lds_bytes<E>(a.n);                                                  \
+    switch (a.n <= 32 ? 1 : a.n / 32) {                                                           \
+      case 1: e = shared_launch(KERNEL<E, 1, 256>, 256, ARGS, BLOCKS, lds, lds_set[0], st); break; \
+      case 2: e = shared_launch(KERNEL<E, 2, 256>, 256, ARGS, BLOCKS, lds, lds_set[1], st); break; \
+      case 4:                                                                                     \
+        e = shared_launch(KERNEL<E, 1024 / T128, T128>, T128, ARGS, BLOCKS, lds, lds_set[2], st); \
+        break;                                                                                    \
+      default:                                                                                    \
+        e = shared_launch(KERNEL<E, 2048 / T256, T256>, T256, ARGS, BLOCKS, lds, lds_set[3], st); \
+    }                                                                                             \
+  }
+
 hipError_t launch_shared_forward(const SharedFwdArgs& a, int batch, int elem_bytes, hipStream_t st) {
   const int blocks = shared_blocks(batch, a.width, elem_bytes);
-  const size_t lds = shared_lds_bytes(a.n, elem_bytes);
-  if (elem_bytes == 2) {
-    static std::atomic<unsigned long long> lds_set{0};
-    const hipError_t attr =
-        lds_limit_once(lds_set, (const void*)shared_fwd_kernel<bf16>, (int)shared_lds_bytes(kSharedMaxN, 2));
-    if (attr != hipSuccess) return attr;
-    shared_fwd_kernel<bf16><<<blocks, SH_THREADS, lds, st>>>(a);
-  } else {
-    static std::atomic<unsigned long long> lds_set{0};
-    const hipError_t attr =
-        lds_limit_once(lds_set, (const void*)shared_fwd_kernel<float>, (int)shared_lds_bytes(kSharedMaxN, 2));
-    if (attr != hipSuccess) return attr;
-    shared_fwd_kernel<float><<<blocks, SH_THREADS, lds, st>>>(a);
-  }
-  return hipGetLastError();
+  hipError_t e;
+  if (elem_bytes == 2) HCMIX_SHARED_CASES(shared_fwd_kernel, bf16, 512, 512, a, blocks)
+  else HCMIX_SHARED_CASES(shared_fwd_kernel, float, 512, 512, a, blocks)
+  return e;
 }
 
 hipError_t launch_shared_backward(const SharedBwdArgs& a, const SharedReduceArgs& r, int batch,
                                   int elem_bytes, hipStream_t st) {
   const int blocks = shared_blocks(batch, a.width, elem_bytes);
-  const size_t lds = shared_lds_bytes(a.n, elem_bytes);
-  if (elem_bytes == 2) {
-    static std::atomic<unsigned long long> lds_set{0};
-    const hipError_t attr =
-        lds_limit_once(lds_set, (const void*)shared_bwd_kernel<bf16>, (int)shared_lds_bytes(kSharedMaxN, 2));
-    if (attr != hipSuccess) return attr;
-    shared_bwd_kernel<bf16><<<blocks, SH_THREADS, lds, st>>>(a);
-  } else {
-    static std::atomic<unsigned long long> lds_set{0};
-    const hipError_t attr =
-        lds_limit_once(lds_set, (const void*)shared_bwd_kernel<float>, (int)shared_lds_bytes(kSharedMaxN, 2));
-    if (attr != hipSuccess) return attr;
-    shared_bwd_kernel<float><<<blocks, SH_THREADS, lds, st>>>(a);
-  }
-  hipError_t e = hipGetLastError();
+  hipError_t e;
+  if (elem_bytes == 2) HCMIX_SHARED_CASES(shared_bwd_kernel, bf16, 256, 256, a, blocks)
+  else HCMIX_SHARED_CASES(shared_bwd_kernel, float, 256, 256, a, blocks)
   if (e != hipSuccess) return e;
   SharedReduceArgs rr = r;
   rr.blocks = blocks;
@@ -437,5 +563,6 @@ hipError_t launch_shared_backward(const SharedBwdArgs& a, const SharedReduceArgs
   shared_dt_reduce_kernel<<<a.num_layers * groups, SH_RED_THREADS, 0, st>>>(rr);
   return hipGetLastError();
 }
+#undef HCMIX_SHARED_CASES
 
 }  // namespace hcmix
