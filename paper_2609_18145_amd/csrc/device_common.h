@@ -34,6 +34,20 @@ __device__ __forceinline__ void dma16(const bf16* src, bf16* lds) {
   __builtin_amdgcn_global_load_lds(src, lds, 16, 0, 0);
 }
 
+// The same from a wave-uniform base and a per-lane byte offset: one instruction
+// with the base in scalar registers.  With a 64-bit address per lane and DMA,
+// the loops recompute eight or more of them per step.
+// `uniform_base`, and the copy of the offset, keep the compiler from folding
+// base and offset into such addresses again ahead of the loop.
+__device__ __forceinline__ const bf16* uniform_base(const bf16* p) {
+  asm volatile("" : "+s"(p));
+  return p;
+}
+__device__ __forceinline__ void dma16_at(const bf16* base, unsigned byte_off, bf16* lds) {
+  asm volatile("" : "+v"(byte_off));
+  __builtin_amdgcn_global_load_lds((const char*)base + byte_off, lds, 16, 0, 0);
+}
+
 // Pointers read from memory (rather than taken from kernel arguments) are
 // generic, and a generic store becomes a FLAT instruction, which also counts
 // on lgkmcnt and so serialises with the LDS reads that feed it; stores through
