@@ -272,7 +272,8 @@ hcmix_status hcmix_stack_backward_data(int64_t batch, int64_t n, int64_t width,
  * also serves a linear map's forward on the transposed weights).  dw is summed in a fixed order
  * (row-range partials, then the ranges in order: bitwise-repeatable) through a
  * workspace of hcmix_head_backward_workspace_bytes (256-byte aligned; unused,
- * may be NULL, without dw); accumulate != 0 adds to dw instead of overwriting.
+ * may be NULL, without dw; a smaller one down to one partial per 256 blocks of
+ * 128 x 128 outputs is taken too, with longer ranges); accumulate != 0 adds to dw instead of overwriting.
  * vocab a multiple of 32, width a multiple of 64; x, w, dlogits and gx 16-byte
  * aligned, dw 4-byte aligned.  Errors as for the entry points above. */
 size_t hcmix_head_backward_workspace_bytes(int64_t rows, int64_t width, int32_t vocab);

@@ -1014,6 +1014,25 @@ hcmix_status hcmix_head_cross_entropy(int64_t rows, int64_t width, int32_t vocab
   return e == hipSuccess ? HCMIX_OK : hip_fail(e);
 }
 
+// Buffers of a weight gradient dl^T x (and whatever else the call writes), with
+// the whole workspace of partial sums or, where the caller's ends before it,
+// the least one; *need is the one to use.
+static hcmix_status check_row_product(int64_t rows, int64_t width, int64_t vocab, const Span* ins,
+                                      const Span* outs, bool dw, const void* workspace,
+                                      size_t workspace_bytes, size_t* need) {
+  auto check = [&](size_t bytes) -> hcmix_status {
+    *need = bytes;
+    if (dw && (!workspace || workspace_bytes < bytes)) return HCMIX_ERR_INVALID_VALUE;
+    const Span all[3] = {outs[0], outs[1], {workspace, bytes}};
+    return check_spans(ins, 3, all, 3, 4);
+  };
+  if (!dw) return check(0);
+  const hcmix_status st =
+      check(head_backward_workspace_bytes((int)rows, (int)width, (int)vocab));
+  if (st == HCMIX_OK) return st;
+  return check(head_backward_least_workspace_bytes((int)rows, (int)width, (int)vocab));
+}
+
 size_t hcmix_head_backward_workspace_bytes(int64_t rows, int64_t width, int32_t vocab) {
   if (check_lm(rows, width, vocab) != HCMIX_OK || vocab % 32) return 0;
   return align256(head_backward_workspace_bytes((int)rows, (int)width, vocab));
@@ -1028,22 +1047,21 @@ hcmix_status hcmix_head_backward(int64_t rows, int64_t width, int32_t vocab, con
   hcmix_status st = check_lm(rows, width, vocab);
   if (st != HCMIX_OK) return st;
   if (vocab % 32 != 0) return HCMIX_ERR_UNSUPPORTED;
-  const size_t need = dw ? head_backward_workspace_bytes((int)rows, (int)width, vocab) : 0;
-  if (dw && (!workspace || workspace_bytes < need)) return HCMIX_ERR_INVALID_VALUE;
   const Span ins[3] = {{w, (size_t)vocab * width * sizeof(bf16)},
                        {dlogits, (size_t)rows * vocab * sizeof(bf16)},
                        {dw ? x : w, dw ? (size_t)rows * width * sizeof(bf16) : 0}};
-  const Span outs[3] = {{gx, gx ? (size_t)rows * width * sizeof(bf16) : 0},
-                        {dw, dw ? (size_t)vocab * width * sizeof(float) : 0},
-                        {workspace, need}};
-  st = check_spans(ins, 3, outs, 3, 4);
+  const Span outs[2] = {{gx, gx ? (size_t)rows * width * sizeof(bf16) : 0},
+                        {dw, dw ? (size_t)vocab * width * sizeof(float) : 0}};
+  size_t need;
+  st = check_row_product(rows, width, vocab, ins, outs, dw != nullptr, workspace, workspace_bytes,
+                         &need);
   if (st != HCMIX_OK) return st;
   if ((dw && !aligned(x, 16)) || !aligned(w, 16) || !aligned(dlogits, 16) ||
       (gx && !aligned(gx, 16)))
     return HCMIX_ERR_UNSUPPORTED;
   if (dw && !aligned(workspace, 256)) return HCMIX_ERR_UNSUPPORTED;
   hipError_t e = launch_head_backward((const bf16*)x, (const bf16*)w, (const bf16*)dlogits,
-                                      (bf16*)gx, dw, accumulate != 0, (float*)workspace,
+                                      (bf16*)gx, dw, accumulate != 0, (float*)workspace, need,
                                       (int)rows, (int)width, vocab, (hipStream_t)stream);
   return e == hipSuccess ? HCMIX_OK : hip_fail(e);
 }
@@ -1316,16 +1334,14 @@ hcmix_status hcmix_linear_backward(int64_t rows, int64_t in_width, int64_t out_w
   if (!w || !dy || (!dx && !dw) || (dw && !x)) return HCMIX_ERR_INVALID_VALUE;
   hcmix_status st = check_linear(rows, in_width, out_width);
   if (st != HCMIX_OK) return st;
-  const size_t need =
-      dw ? head_backward_workspace_bytes((int)rows, (int)in_width, (int)out_width) : 0;
-  if (dw && (!workspace || workspace_bytes < need)) return HCMIX_ERR_INVALID_VALUE;
   const Span ins[3] = {{w, (size_t)out_width * in_width * sizeof(bf16)},
                        {dy, (size_t)rows * out_width * sizeof(bf16)},
                        {dw ? x : w, dw ? (size_t)rows * in_width * sizeof(bf16) : 0}};
-  const Span outs[3] = {{dx, dx ? (size_t)rows * in_width * sizeof(bf16) : 0},
-                        {dw, dw ? (size_t)out_width * in_width * sizeof(float) : 0},
-                        {workspace, need}};
-  st = check_spans(ins, 3, outs, 3, 4);
+  const Span outs[2] = {{dx, dx ? (size_t)rows * in_width * sizeof(bf16) : 0},
+                        {dw, dw ? (size_t)out_width * in_width * sizeof(float) : 0}};
+  size_t need;
+  st = check_row_product(rows, in_width, out_width, ins, outs, dw != nullptr, workspace,
+                         workspace_bytes, &need);
   if (st != HCMIX_OK) return st;
   if ((dw && !aligned(x, 16)) || !aligned(w, 16) || !aligned(dy, 16) || (dx && !aligned(dx, 16)))
     return HCMIX_ERR_UNSUPPORTED;
@@ -1339,8 +1355,8 @@ hcmix_status hcmix_linear_backward(int64_t rows, int64_t in_width, int64_t out_w
   // dW = dy^T x, row ranges summed in a fixed order
   if (e == hipSuccess && dw)
     e = launch_head_backward((const bf16*)x, (const bf16*)w, (const bf16*)dy, nullptr, dw,
-                             accumulate != 0, (float*)workspace, (int)rows, (int)in_width,
-                             (int)out_width, s);
+                             accumulate != 0, (float*)workspace, need, (int)rows,
+                             (int)in_width, (int)out_width, s);
   return e == hipSuccess ? HCMIX_OK : hip_fail(e);
 }
 

@@ -265,10 +265,12 @@ hipError_t launch_head_ce(const bf16* x, const bf16* w, const float* bias, const
 // Head backward: gx = dl W (bf16, optional) and dW (+)= dl^T x (fp32, optional)
 // through head_backward_workspace_bytes of row-range partials summed in order;
 // vocab a multiple of 32.
+// (it also runs, with longer ranges, on the least size).
 size_t head_backward_workspace_bytes(int rows, int width, int vocab);
+size_t head_backward_least_workspace_bytes(int rows, int width, int vocab);
 hipError_t launch_head_backward(const bf16* x, const bf16* w, const bf16* dl, bf16* gx, float* dw,
-                                int accumulate, float* workspace, int rows, int width, int vocab,
-                                hipStream_t st);
+                                int accumulate, float* workspace, size_t workspace_bytes, int rows,
+                                int width, int vocab, hipStream_t st);
 
 struct DecodeLayerArgs {
   const bf16* x_in;

@@ -8,6 +8,8 @@
 // The head computes logits^T = W x^T so that a lane owns one row and 16 of its
 // vocabulary entries per 32 x 32 tile: the row's whole softmax is in-lane plus
 // one exchange with lane ^ 32.
+#include <math.h>
+
 #include "hcmix_internal.h"
 #include "device_common.h"
 
@@ -376,7 +378,7 @@ hipError_t head_launch(const bf16* x, const bf16* w, const float* bias, const in
 // the two products the chain rule gives for logits = W x + bias:
 //   dW[v][k] = sum over rows r of dl[r][v] x[r][k]   (fp32)
 //   gx[r][k] = sum over v of dl[r][v] W[v][k]        (bf16)
-// Both kernels: 128 x 128 output tiles, four waves of 64 x 64 (2 x 2 MFMA
+// The input gradient: 128 x 128 output tiles, four waves of 64 x 64 (2 x 2 MFMA
 // tiles of 32 x 32), 64-wide contraction steps staged in two LDS buffers; each
 // thread loads the next step's pieces into registers before the MFMAs of the
 // current one.  Pieces outside the rows, the vocabulary or the width are zero.
@@ -385,17 +387,52 @@ constexpr int HB_TILE = 128;
 constexpr int HB_KS = 64;
 constexpr int HB_TARGET_BLOCKS = 256;
 
-// Rows per split of the weight gradient (a multiple of HB_KS) and the number
-// of splits, so that about HB_TARGET_BLOCKS blocks work.
+// Weight gradient dl^T x: BO x 128 output tiles (BO = 256 vocabulary entries, or
+// 128 up to a vocabulary of 128), HD_NS stages of 64 rows in LDS by DMA, eight
+// (four) waves of 64 x 64.  A step moves 48 KB into the CU and reads 128 KB of
+// fragments from LDS (transposed) for 4.2 Mflop, and takes about 1.4 us: 0.9 us
+// the DMA alone, 1.2 us the fragment reads and MFMAs alone, 0.5 us the MFMAs.
+// The rows are split into ranges to fill the chip, whose fp32 partials cost
+// memory traffic in turn; see head_dw_split.
+// Measured at 16384 rows without the sum of the ranges (5-7 us): 512 x 1536
+// 42.3 us, 512 x 512 19.8, 512 x 256 16.1, against 57, 25 and 17.5 with 128 x
+// 128 tiles staged through registers.  128 x 64 or 256 x 256 tiles per wave or
+// block (fewer fragment reads, one wave per SIMD or twice the partials) took
+// 46 to 50, 22 to 23 and 19 to 20.
+constexpr int HD_NS = 3;
+
+int head_dw_tile(int vocab) { return vocab > 128 ? 256 : 128; }
+
+// Row ranges of the weight gradient: `range` rows each (a multiple of HB_KS).
+// With s ranges a block walks steps / s steps of 0.85 us (the DMA's time; with
+// the whole step's 1.4 us the sum below moves by less than the runs differ),
+// and the partials' s * vocab * width floats are written and read at about
+// 5 TB/s: the sum is least at the root of the ratio, as long as the blocks fit
+// the chip.
 void head_dw_split(int rows, int width, int vocab, int* range, int* splits) {
+  const int bo = head_dw_tile(vocab);
+  const int tiles = ((vocab + bo - 1) / bo) * ((width + HB_TILE - 1) / HB_TILE);
+  const int steps = (rows + HB_KS - 1) / HB_KS;
+  const double part_us = (double)vocab * width * 8 / 5e6;
+  int s = (int)(sqrt(steps * 0.85 / part_us) + 0.5);
+  if (s > HB_TARGET_BLOCKS / tiles) s = HB_TARGET_BLOCKS / tiles;
+  if (s > steps) s = steps;
+  if (s < 1) s = 1;
+  const int per = (steps + s - 1) / s;                 // steps per range
+  *range = per * HB_KS;
+  *splits = (rows + *range - 1) / *range;
+}
+
+// The least partials a call may come with: one per range of the plan that
+// fills 256 blocks with 128 x 128 tiles.
+int head_dw_least_splits(int rows, int width, int vocab) {
   const int tiles = ((vocab + HB_TILE - 1) / HB_TILE) * ((width + HB_TILE - 1) / HB_TILE);
   int s = (HB_TARGET_BLOCKS + tiles - 1) / tiles;
   const int steps = (rows + HB_KS - 1) / HB_KS;
   if (s > steps) s = steps;
   if (s < 1) s = 1;
-  const int per = (steps + s - 1) / s;                 // steps per split
-  *range = per * HB_KS;
-  *splits = (rows + *range - 1) / *range;
+  const int per = (steps + s - 1) / s;
+  return (steps + per - 1) / per;
 }
 
 // LDS element offset of column `col` (a multiple of 8) of row `row` in a
@@ -404,46 +441,77 @@ __device__ __forceinline__ int hb_tr_off(int row, int col) {
   return row * HB_TILE + trswz<256>(row, col >> 5) * 32 + (col & 31);
 }
 
-// Weight-gradient partials: block (vocabulary tile, width tile, split s) sums
+__device__ __attribute__((aligned(16))) bf16 g_lm_zero16[8];   // DMA source of padding
+
+// Weight-gradient partials: block (vocabulary tile, width tile, range s) sums
 // rows [s * range, (s + 1) * range) into part[s][v][k].  Both operands are
 // row-major over the contraction (the rows), staged as [64 rows][128 columns]
-// tiles and read transposed.
-__global__ __launch_bounds__(256) void head_dw_kernel(const bf16* __restrict__ dl,
-                                                      const bf16* __restrict__ x,
-                                                      float* __restrict__ part, int rows,
-                                                      int width, int vocab, int range) {
-  __shared__ __attribute__((aligned(16))) bf16 ta[2][HB_KS * HB_TILE];
-  __shared__ __attribute__((aligned(16))) bf16 tb[2][HB_KS * HB_TILE];
-  const int tk_n = (width + HB_TILE - 1) / HB_TILE, tv_n = (vocab + HB_TILE - 1) / HB_TILE;
-  int b = blockIdx.x;
+// subtiles and read transposed.  Pieces outside the rows, the vocabulary or
+// the width come from the zero buffer.  Columns fastest, then the range: the
+// blocks on one XCD share rows of dl and x.
+template <int BO>
+__global__ __launch_bounds__(BO * 2) void head_dw_kernel(const bf16* __restrict__ dl,
+                                                         const bf16* __restrict__ x,
+                                                         float* __restrict__ part, int rows,
+                                                         int width, int vocab, int range) {
+  constexpr int NS = HD_NS, BC = HB_TILE;
+  constexpr int WO = BO / 64, NW = WO * 2;             // waves, each 64 x 64
+  constexpr int SUB = HB_KS * HB_TILE;                 // elements of a subtile
+  constexpr int NSO = BO / HB_TILE, NSUB = NSO + BC / HB_TILE, STAGE = NSUB * SUB;
+  constexpr int DMA = NSUB * 16 / NW;                  // 1 KB blocks per wave and stage
+  static_assert(DMA * NW == NSUB * 16 && (NS - 1) * DMA <= 63, "");
+  extern __shared__ __attribute__((aligned(1024))) bf16 smem[];
+  const int tk_n = (width + BC - 1) / BC, tv_n = (vocab + BO - 1) / BO;
+  int b = xcd_tile(blockIdx.x, gridDim.x);
   const int tk = b % tk_n;
   b /= tk_n;
   const int tv = b % tv_n, sp = b / tv_n;
-  const int v0 = tv * HB_TILE, k0 = tk * HB_TILE;
+  const int v0 = tv * BO, k0 = tk * BC;
   const int r0 = sp * range, r1 = min(rows, r0 + range);
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave & 1, wn = wave >> 1;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave % WO, wn = wave / WO;
   const int nsteps = r1 > r0 ? (r1 - r0 + HB_KS - 1) / HB_KS : 0;
-  u32x4 ga[4], gb[4];
-  auto load = [&](int t) {
+
+  // this lane's piece of each DMA block: base of its column, row in the stage
+  const bf16* src[DMA];
+  int row[DMA], stride[DMA];
 #pragma unroll
-    for (int j = 0; j < 4; j++) {
-      const int p = tid + 256 * j, row = p >> 4, col = 8 * (p & 15);
-      const int r = r0 + t * HB_KS + row;
-      const bool rok = r < r1;
-      ga[j] = rok && v0 + col < vocab ? *(const u32x4*)(dl + (size_t)r * vocab + v0 + col)
-                                      : u32x4{0u, 0u, 0u, 0u};
-      gb[j] = rok && k0 + col < width ? *(const u32x4*)(x + (size_t)r * width + k0 + col)
-                                      : u32x4{0u, 0u, 0u, 0u};
+  for (int j = 0; j < DMA; j++) {
+    const int id = j * NW + wave, sub = id / 16;
+    int col;
+    tr_dma_coord<256>(id % 16, lane, &row[j], &col);
+    const bool is_x = sub >= NSO;
+    const int c = is_x ? k0 + (sub - NSO) * HB_TILE + col : v0 + sub * HB_TILE + col;
+    stride[j] = is_x ? width : vocab;
+    src[j] = c < stride[j] ? (is_x ? x : dl) + c : nullptr;
+  }
+  // whole steps of whole tiles: constant offsets from wave-uniform bases (32
+  // bits hold 64 rows of either operand)
+  const bool whole = v0 + BO <= vocab && k0 + BC <= width && vocab < (1 << 24);
+  unsigned off[DMA];
+#pragma unroll
+  for (int j = 0; j < DMA; j++) {
+    const bool is_x = (j * NW + wave) / 16 >= NSO;
+    off[j] = (unsigned)(row[j] * (unsigned)stride[j] * 2 + (src[j] - (is_x ? x + k0 : dl + v0)) * 2);
+  }
+  auto issue = [&](int t, int stage) {
+    if (whole && r0 + (t + 1) * HB_KS <= r1) {
+      const size_t r = r0 + t * HB_KS;
+      const bf16* db = uniform_base(dl + r * vocab + v0);
+      const bf16* xb = uniform_base(x + r * width + k0);
+#pragma unroll
+      for (int j = 0; j < DMA; j++) {
+        const int id = j * NW + wave;
+        dma16_at(id / 16 >= NSO ? xb : db, off[j], smem + stage * STAGE + id * 512);
+      }
+      return;
     }
-  };
-  auto stash = [&](int buf) {
 #pragma unroll
-    for (int j = 0; j < 4; j++) {
-      const int p = tid + 256 * j, row = p >> 4, col = 8 * (p & 15);
-      *(u32x4*)(ta[buf] + hb_tr_off(row, col)) = ga[j];
-      *(u32x4*)(tb[buf] + hb_tr_off(row, col)) = gb[j];
+    for (int j = 0; j < DMA; j++) {
+      const int r = r0 + t * HB_KS + row[j];
+      dma16(src[j] && r < r1 ? src[j] + (size_t)r * stride[j] : g_lm_zero16,
+            smem + stage * STAGE + (j * NW + wave) * 512);
     }
   };
   f32x16 acc[2][2];
@@ -453,28 +521,57 @@ __global__ __launch_bounds__(256) void head_dw_kernel(const bf16* __restrict__ d
     for (int j = 0; j < 2; j++)
 #pragma unroll
       for (int e = 0; e < 16; e++) acc[i][j][e] = 0.f;
-  if (nsteps > 0) {
-    load(0);
-    stash(0);
-  }
-  __syncthreads();
-  for (int t = 0; t < nsteps; t++) {
-    const int buf = t & 1;
-    if (t + 1 < nsteps) load(t + 1);
+  struct Frags { bf16x8 a[2], b[2]; };
+  auto load_frags = [&](Frags& f, const bf16* st, int kk) {
 #pragma unroll
-    for (int kk = 0; kk < HB_KS; kk += 16) {
-      bf16x8 a[2], bb[2];
-#pragma unroll
-      for (int i = 0; i < 2; i++) a[i] = tr_frag<256>(ta[buf], kk, 64 * wm + 32 * i, lane);
-#pragma unroll
-      for (int j = 0; j < 2; j++) bb[j] = tr_frag<256>(tb[buf], kk, 64 * wn + 32 * j, lane);
-#pragma unroll
-      for (int i = 0; i < 2; i++)
-#pragma unroll
-        for (int j = 0; j < 2; j++) acc[i][j] = mfma32(a[i], bb[j], acc[i][j]);
+    for (int i = 0; i < 2; i++) {
+      const int c = 64 * wm + 32 * i;
+      f.a[i] = tr_frag<256>(st + c / HB_TILE * SUB, kk * 16, c % HB_TILE, lane);
     }
-    if (t + 1 < nsteps) stash(buf ^ 1);
+#pragma unroll
+    for (int j = 0; j < 2; j++) {
+      const int c = 64 * wn + 32 * j;
+      f.b[j] = tr_frag<256>(st + (NSO + c / HB_TILE) * SUB, kk * 16, c % HB_TILE, lane);
+    }
+  };
+  auto mma = [&](const Frags& f) {
+#pragma unroll
+    for (int i = 0; i < 2; i++)
+#pragma unroll
+      for (int j = 0; j < 2; j++) acc[i][j] = mfma32(f.a[i], f.b[j], acc[i][j]);
+  };
+  // NS stages in flight; the barrier for the next stage stands before a step's
+  // last MFMAs, whose fragments every wave holds by then, so that the next
+  // stage's first fragments load under them
+#pragma unroll
+  for (int st = 0; st < NS; st++)
+    if (st < nsteps) issue(st, st);
+  Frags f[2];
+  if (nsteps > 0) {
+    wait_stages<NS, DMA>(min(nsteps, NS) - 1);
     __syncthreads();
+    load_frags(f[0], smem, 0);
+  }
+  for (int t = 0; t < nsteps; t++) {
+    const bf16* st = smem + t % NS * STAGE;
+#pragma unroll
+    for (int kk = 0; kk < HB_KS / 16; kk++) {
+      if (kk + 1 < HB_KS / 16) {
+        load_frags(f[(kk + 1) & 1], st, kk + 1);
+        mma(f[kk & 1]);
+        interleave_front<4, 8>();
+      } else {
+        if (t + 1 < nsteps) {
+          wait_stages<NS, DMA>(min(nsteps, t + NS) - (t + 2));
+          __syncthreads();  // stage t + 1 visible to all waves; buffer t % NS free
+          if (t + NS < nsteps) issue(t + NS, t % NS);
+        }
+        load_frags(f[0], smem + (t + 1) % NS * STAGE, 0);
+        mma(f[kk & 1]);
+        interleave_front<4, 8>();
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
   }
   // C[m = v][n = k]: lane l holds column k = .. + l % 32 and rows
   // v = .. + 8 (e / 4) + 4 (l / 32) + e % 4
@@ -488,7 +585,7 @@ __global__ __launch_bounds__(256) void head_dw_kernel(const bf16* __restrict__ d
 #pragma unroll
       for (int e = 0; e < 16; e++) {
         const int v = v0 + 64 * wm + 32 * i + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-        if (v < vocab) out[(size_t)v * width + k] = acc[i][j][e];
+        if (v < vocab) store_wt4(out + (size_t)v * width + k, acc[i][j][e]);
       }
     }
 }
@@ -613,15 +710,33 @@ size_t head_workspace_bytes(int rows, int vocab) {
   return (size_t)((rows + HEAD_ROWS - 1) / HEAD_ROWS) * vocab * sizeof(float);
 }
 
+size_t head_backward_least_workspace_bytes(int rows, int width, int vocab) {
+  return (size_t)head_dw_least_splits(rows, width, vocab) * vocab * width * sizeof(float);
+}
+
 size_t head_backward_workspace_bytes(int rows, int width, int vocab) {
   int range, splits;
   head_dw_split(rows, width, vocab, &range, &splits);
-  return (size_t)splits * vocab * width * sizeof(float);
+  const size_t best = (size_t)splits * vocab * width * sizeof(float);
+  const size_t least = head_backward_least_workspace_bytes(rows, width, vocab);
+  return best > least ? best : least;
+}
+
+template <int BO>
+static hipError_t head_dw_launch(const bf16* dl, const bf16* x, float* part, int rows, int width,
+                                 int vocab, int range, int splits, hipStream_t st) {
+  const size_t lds = (size_t)HD_NS * (BO / HB_TILE + 1) * HB_KS * HB_TILE * sizeof(bf16);
+  static std::atomic<unsigned long long> lds_set{0};
+  const hipError_t e = lds_limit_once(lds_set, (const void*)head_dw_kernel<BO>, (int)lds);
+  if (e != hipSuccess) return e;
+  const int blocks = ((width + HB_TILE - 1) / HB_TILE) * ((vocab + BO - 1) / BO) * splits;
+  head_dw_kernel<BO><<<blocks, BO * 2, lds, st>>>(dl, x, part, rows, width, vocab, range);
+  return hipGetLastError();
 }
 
 hipError_t launch_head_backward(const bf16* x, const bf16* w, const bf16* dl, bf16* gx, float* dw,
-                                int accumulate, float* workspace, int rows, int width, int vocab,
-                                hipStream_t st) {
+                                int accumulate, float* workspace, size_t workspace_bytes, int rows,
+                                int width, int vocab, hipStream_t st) {
   const int tk_n = (width + HB_TILE - 1) / HB_TILE;
   if (gx) {
     const int tr_n = (rows + HB_TILE - 1) / HB_TILE;
@@ -632,9 +747,16 @@ hipError_t launch_head_backward(const bf16* x, const bf16* w, const bf16* dl, bf
   if (!dw) return hipSuccess;
   int range, splits;
   head_dw_split(rows, width, vocab, &range, &splits);
-  const int tv_n = (vocab + HB_TILE - 1) / HB_TILE;
-  head_dw_kernel<<<tk_n * tv_n * splits, 256, 0, st>>>(dl, x, workspace, rows, width, vocab, range);
-  hipError_t e = hipGetLastError();
+  const size_t room = workspace_bytes / ((size_t)vocab * width * sizeof(float));
+  if ((size_t)splits > room) {   // a workspace of the least size: longer ranges
+    const int steps = (rows + HB_KS - 1) / HB_KS;
+    range = (int)((steps + room - 1) / room) * HB_KS;
+    splits = (rows + range - 1) / range;
+  }
+  const hipError_t e =
+      head_dw_tile(vocab) == 256
+          ? head_dw_launch<256>(dl, x, workspace, rows, width, vocab, range, splits, st)
+          : head_dw_launch<128>(dl, x, workspace, rows, width, vocab, range, splits, st);
   if (e != hipSuccess) return e;
   const size_t elems = (size_t)vocab * width;
   embed_bwd_reduce_kernel<<<(unsigned)((elems / 4 + LM_THREADS - 1) / LM_THREADS), LM_THREADS,

@@ -61,3 +61,28 @@ def test_linear(rows, n_in, n_out):
     assert row_rel_err(to_host(y), xd @ wd.T) <= TOL["bf16"]
     assert row_rel_err(to_host(dx), gd @ wd) <= TOL["bf16"]
     assert fro_rel_err(to_host(dw), gd.T @ xd) <= 1e-4
+
+
+@pytest.mark.parametrize("rows,n_in,n_out", [(64, 64, 128), (130, 192, 320), (8192, 128, 96 * 2),
+                                             (4098, 512, 1536)])
+def test_linear_weight_gradient_on_whole_and_least_workspace(rows, n_in, n_out):
+    """Row ranges of the whole plan and of the least workspace (as many partials
+    as 128 x 128 tiles need to make 256 blocks), ragged last ranges among them."""
+    print(f"case: linear dW {rows}x{n_in}x{n_out}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    x = torch.randn(rows, n_in, generator=g, device="cuda").bfloat16()
+    w = torch.zeros(n_out, n_in, device="cuda").bfloat16()
+    dy = torch.randn(rows, n_out, generator=g, device="cuda").bfloat16()
+    tiles = -(-n_out // 128) * -(-n_in // 128)
+    steps = -(-rows // 64)
+    s = max(1, min(-(-256 // tiles), steps))
+    least = -(-steps // -(-steps // s)) * n_in * n_out * 4
+    ref = dy.double().cpu().numpy().T @ x.double().cpu().numpy()
+    whole = hcmix.load().hcmix_linear_backward_workspace_bytes(rows, n_in, n_out)
+    assert whole >= least
+    for nbytes in (whole, least):
+        wsp = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        dw = torch.full((n_out, n_in), 0.25, device="cuda")
+        hcmix.linear_backward(x, w, dy, dw=dw, with_dx=False, accumulate=True, workspace=wsp)
+        torch.cuda.synchronize()
+        assert fro_rel_err(to_host(dw) - 0.25, ref) <= 1e-4
