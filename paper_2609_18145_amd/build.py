@@ -3,7 +3,8 @@
     python -m paper_2609_18145_amd.build
 
 Each .hip source compiles to an object under _build/ (in parallel), then the
-objects link into paper_2609_18145_amd/libhcmix.so.
+objects link into paper_2609_18145_amd/libhcmix.so.  The binding's operand
+checks (csrc/marshal.cpp, host code) compile to paper_2609_18145_amd/_marshal.so.
 """
 from __future__ import annotations
 
@@ -17,6 +18,7 @@ import sys
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "libhcmix.so")
+MARSHAL = os.path.join(PKG, "_marshal.so")
 BUILD_DIR = os.path.join(ROOT, "_build")
 
 HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
@@ -42,11 +44,32 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _build_marshal() -> None:
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths, library_paths
+
+    tmp = MARSHAL + ".tmp%d" % os.getpid()
+    incs = [*include_paths(), sysconfig.get_paths()["include"]]
+    cmd = [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           *[a for p in incs for a in ("-isystem", p)],
+           os.path.join(PKG, "csrc", "marshal.cpp"), "-o", tmp,
+           *["-L" + p for p in library_paths()], "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"g++ failed for marshal.cpp:\n{res.stdout}\n{res.stderr}")
+    os.replace(tmp, MARSHAL)
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD_DIR, exist_ok=True)
     srcs = sources()
-    with cf.ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
+    with cf.ThreadPoolExecutor(max_workers=min(8, len(srcs) + 1)) as ex:
+        marshal = ex.submit(_build_marshal)
         objs = list(ex.map(_compile, srcs))
+        marshal.result()
     tmp = LIB + ".tmp%d" % os.getpid()
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp]
     res = subprocess.run(cmd, capture_output=True, text=True)

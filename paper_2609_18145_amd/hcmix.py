@@ -12,7 +12,10 @@ raises on first use: there is no CPU or PyTorch fallback.
 """
 from __future__ import annotations
 
+import array
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
@@ -44,6 +47,7 @@ EXPORTS = ("hcmix_status_string", "hcmix_last_hip_error", "hcmix_dim", "hcmix_fo
            "hcmix_field_backward")
 
 _lib = None
+_marshal = None
 
 
 class HcmixError(RuntimeError):
@@ -65,7 +69,8 @@ def load():
                                "`python -m paper_2609_18145_amd.build`")
         lib = ctypes.CDLL(LIB_PATH)
         i64, i32, vp, sz = ctypes.c_int64, ctypes.c_int32, ctypes.c_void_p, ctypes.c_size_t
-        fp = ctypes.POINTER(ctypes.c_float)
+        # float*, void** and int32_t* arguments: an address, an array or bytes
+        fp = pp = ip = vp
         lib.hcmix_status_string.argtypes, lib.hcmix_status_string.restype = [i32], ctypes.c_char_p
         lib.hcmix_last_hip_error.argtypes, lib.hcmix_last_hip_error.restype = [], ctypes.c_char_p
         lib.hcmix_dim.argtypes, lib.hcmix_dim.restype = [i32, i64], i32
@@ -79,8 +84,6 @@ def load():
         lib.hcmix_backward_no_alloc.argtypes = [i64, i64, i64, i32, i32, i32, vp, vp, vp, vp, vp,
                                                 fp, fp, i32, vp]
         lib.hcmix_backward_no_alloc.restype = i32
-        pp = ctypes.POINTER(ctypes.c_void_p)
-        ip = ctypes.POINTER(ctypes.c_int32)
         lib.hcmix_stack_forward.argtypes = [i64, i64, i64, i32, ip, i32, i32, vp, pp, pp, pp, vp]
         lib.hcmix_stack_forward.restype = i32
         lib.hcmix_stack_backward_workspace_bytes.argtypes = [i64, i64, i64, i32, i32]
@@ -148,6 +151,22 @@ def load():
     return _lib
 
 
+def _native():
+    """The operand checks in native code (built beside the library)."""
+    global _marshal
+    if _marshal is None:
+        path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_marshal.so")
+        if not os.path.exists(path):
+            raise RuntimeError(f"{path} is missing: build it with "
+                               "`python -m paper_2609_18145_amd.build`")
+        loader = importlib.machinery.ExtensionFileLoader("_marshal", path)
+        spec = importlib.util.spec_from_file_location("_marshal", path, loader=loader)
+        mod = importlib.util.module_from_spec(spec)
+        loader.exec_module(mod)
+        _marshal = mod
+    return _marshal
+
+
 def _dtype_code(t: torch.Tensor) -> int:
     if t.dtype == torch.bfloat16:
         return HCMIX_BF16
@@ -157,17 +176,19 @@ def _dtype_code(t: torch.Tensor) -> int:
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
-def _fptr(t):
-    return ctypes.cast(ctypes.c_void_p(t.data_ptr()), ctypes.POINTER(ctypes.c_float))
+_fptr = _ptr
 
 
 def _need(t, name, shape, dtype, device=None):
     """Validate one operand before anything reaches the library: a tensor of
     exactly `shape` (None entries match any extent), of `dtype`, contiguous,
     and (once the device is known) on `device`.  Raises ValueError."""
+    if (type(t) is torch.Tensor and t.dtype is dtype and t.is_contiguous()
+            and (device is None or t.device == device) and (shape is None or t.shape == shape)):
+        return
     if not isinstance(t, torch.Tensor):
         raise ValueError(f"{name}: expected a tensor, got {type(t).__name__}")
     if shape is not None:
@@ -208,7 +229,7 @@ def _bytes(t):
 
 
 def _stream(x):
-    return ctypes.c_void_p(torch.cuda.current_stream(x.device).cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(x.device.index)
 
 
 def dim(layer: int, n: int) -> int:
@@ -223,10 +244,15 @@ def _act_shape(x, name="x"):
 
 
 def _weights(ws, name, width, dtype, dev, count=None):
+    """Checks [width, width] matrices; returns their addresses for the library."""
     if count is not None and len(ws) != count:
         raise ValueError(f"{name}: {len(ws)} matrices, expected {count}")
+    ptrs = _native().pointers(ws, len(ws), (width, width), dtype, dev)
+    if ptrs is not None:
+        return ptrs
     for k, w in enumerate(ws):
         _need(w, f"{name}[{k}]", (width, width), dtype, dev)
+    return _ptrs(ws)
 
 
 def forward(x: torch.Tensor, w_self: torch.Tensor, w_off: torch.Tensor, layer: int,
@@ -324,14 +350,23 @@ def _ptrs(ts):
 
 
 def _layers(layers):
+    try:
+        return array.array("i", layers).tobytes()
+    except (TypeError, OverflowError):
+        pass
     return (ctypes.c_int32 * len(layers))(*[int(v) for v in layers])
 
 
 def _acts(ts, name, shape, dt, dev, count):
+    """Checks the first `count` tensors; returns their addresses for the library."""
     if len(ts) < count:
         raise ValueError(f"{name}: {len(ts)} tensors, expected {count}")
+    ptrs = _native().pointers(ts, count, shape, dt, dev)
+    if ptrs is not None:
+        return ptrs
     for k in range(count):
         _need(ts[k], f"{name}[{k}]", shape, dt, dev)
+    return _ptrs(ts[:count])
 
 
 def stack_forward(x, w_selfs, w_offs, layers, causal, outs=None):
@@ -342,15 +377,14 @@ def stack_forward(x, w_selfs, w_offs, layers, causal, outs=None):
     dt = _act_dtype(x)
     _need(x, "x", None, dt)
     dev = x.device
-    _weights(w_selfs, "w_selfs", width, dt, dev, L)
-    _weights(w_offs, "w_offs", width, dt, dev, L)
+    p_ws = _weights(w_selfs, "w_selfs", width, dt, dev, L)
+    p_wo = _weights(w_offs, "w_offs", width, dt, dev, L)
     if outs is None:
         outs = [torch.empty_like(x) for _ in range(L)]
-    _acts(outs, "outs", shape, dt, dev, L)
+    p_outs = _acts(outs, "outs", shape, dt, dev, L)
     _gpu(dev)
     rc = load().hcmix_stack_forward(batch, n, width, L, _layers(layers), int(bool(causal)),
-                                    _dtype_code(x), _ptr(x), _ptrs(w_selfs), _ptrs(w_offs),
-                                    _ptrs(outs[:L]), _stream(x))
+                                    _dtype_code(x), _ptr(x), p_ws, p_wo, p_outs, _stream(x))
     if rc != HCMIX_OK:
         raise HcmixError(rc, "hcmix_stack_forward")
     return [x, *outs[:L]]
@@ -376,9 +410,9 @@ def stack_backward(xs, w_selfs, w_offs, layers, dy, causal, dx=None, dws=None, d
     batch, n, width = shape
     dt = _act_dtype(x0, "xs[0]")
     dev = x0.device
-    _acts(xs, "xs", shape, dt, dev, L)
-    _weights(w_selfs, "w_selfs", width, dt, dev, L)
-    _weights(w_offs, "w_offs", width, dt, dev, L)
+    p_xs = _acts(xs, "xs", shape, dt, dev, L)
+    p_ws = _weights(w_selfs, "w_selfs", width, dt, dev, L)
+    p_wo = _weights(w_offs, "w_offs", width, dt, dev, L)
     _need(dy, "dy", shape, dt, dev)
     if dx is None:
         dx = torch.empty_like(x0)
@@ -387,14 +421,14 @@ def stack_backward(xs, w_selfs, w_offs, layers, dy, causal, dx=None, dws=None, d
         dws = [torch.empty((width, width), dtype=torch.float32, device=dev) for _ in range(L)]
     if dwo is None:
         dwo = [torch.empty((width, width), dtype=torch.float32, device=dev) for _ in range(L)]
-    _acts(dws, "dws", (width, width), torch.float32, dev, L)
-    _acts(dwo, "dwo", (width, width), torch.float32, dev, L)
+    p_dws = _acts(dws, "dws", (width, width), torch.float32, dev, L)
+    p_dwo = _acts(dwo, "dwo", (width, width), torch.float32, dev, L)
     _gpu(dev)
     if workspace is None:
         workspace = alloc_stack_workspace(batch, n, width, L, x0.dtype, dev)
     rc = load().hcmix_stack_backward(batch, n, width, L, _layers(layers), int(bool(causal)),
-                                     _dtype_code(x0), _ptrs(xs[:L]), _ptrs(w_selfs), _ptrs(w_offs),
-                                     _ptr(dy), _ptr(dx), _ptrs(dws[:L]), _ptrs(dwo[:L]),
+                                     _dtype_code(x0), p_xs, p_ws, p_wo, _ptr(dy), _ptr(dx),
+                                     p_dws, p_dwo,
                                      int(bool(accumulate)), _ptr(workspace), _bytes(workspace),
                                      _stream(x0))
     if rc != HCMIX_OK:
@@ -413,21 +447,21 @@ def stack_backward_data(w_selfs, w_offs, layers, dy, causal, dx=None, grads=None
     dt = _act_dtype(dy, "dy")
     _need(dy, "dy", None, dt)
     dev = dy.device
-    _weights(w_selfs, "w_selfs", width, dt, dev, L)
-    _weights(w_offs, "w_offs", width, dt, dev, L)
+    p_ws = _weights(w_selfs, "w_selfs", width, dt, dev, L)
+    p_wo = _weights(w_offs, "w_offs", width, dt, dev, L)
     if dx is None:
         dx = torch.empty_like(dy)
     if grads is None:
         grads = [torch.empty_like(dy) for _ in range(L - 1)]
     _need(dx, "dx", shape, dt, dev)
-    _acts(grads, "grads", shape, dt, dev, L - 1)
+    p_grads = _acts(grads, "grads", shape, dt, dev, L - 1)
     _gpu(dev)
     nbytes = load().hcmix_stack_backward_data_workspace_bytes(width, L, _dtype_code(dy))
     if workspace is None and nbytes:
         workspace = torch.empty(nbytes, dtype=torch.uint8, device=dev)
-    gp = _ptrs(grads[:L - 1]) if L > 1 else None
+    gp = p_grads if L > 1 else None
     rc = load().hcmix_stack_backward_data(batch, n, width, L, _layers(layers), int(bool(causal)),
-                                          _dtype_code(dy), _ptrs(w_selfs), _ptrs(w_offs), _ptr(dy),
+                                          _dtype_code(dy), p_ws, p_wo, _ptr(dy),
                                           gp, _ptr(dx), _ptr(workspace), _bytes(workspace),
                                           _stream(dy))
     if rc != HCMIX_OK:
@@ -450,22 +484,22 @@ def stack_weight_gradients(xs, dys, layers, causal, dws=None, dwo=None, accumula
     batch, n, width = shape
     dt = _act_dtype(x0, "xs[0]")
     dev = x0.device
-    _acts(xs, "xs", shape, dt, dev, L)
-    _acts(dys, "dys", shape, dt, dev, L)
+    p_xs = _acts(xs, "xs", shape, dt, dev, L)
+    p_dys = _acts(dys, "dys", shape, dt, dev, L)
     if dws is None:
         dws = [torch.empty((width, width), dtype=torch.float32, device=dev) for _ in range(L)]
     if dwo is None:
         dwo = [torch.empty((width, width), dtype=torch.float32, device=dev) for _ in range(L)]
-    _acts(dws, "dws", (width, width), torch.float32, dev, L)
-    _acts(dwo, "dwo", (width, width), torch.float32, dev, L)
+    p_dws = _acts(dws, "dws", (width, width), torch.float32, dev, L)
+    p_dwo = _acts(dwo, "dwo", (width, width), torch.float32, dev, L)
     _gpu(dev)
     if workspace is None:
         nbytes = weight_gradients_workspace_bytes(batch, n, width, L, x0.dtype)
         workspace = (torch.empty(nbytes, dtype=torch.uint8, device=dev) if nbytes
                      else None)
     rc = load().hcmix_stack_weight_gradients(batch, n, width, L, _layers(layers),
-                                             int(bool(causal)), _dtype_code(x0), _ptrs(xs[:L]),
-                                             _ptrs(dys[:L]), _ptrs(dws[:L]), _ptrs(dwo[:L]),
+                                             int(bool(causal)), _dtype_code(x0), p_xs, p_dys,
+                                             p_dws, p_dwo,
                                              int(bool(accumulate)), _ptr(workspace),
                                              _bytes(workspace), _stream(x0))
     if rc != HCMIX_OK:
@@ -739,8 +773,7 @@ def head_backward(x, w, dlogits, gx=None, dw=None, with_gx=True, with_dw=True,
 def _tables(ts, name, n, dev, count):
     if len(ts) < count:
         raise ValueError(f"{name}: {len(ts)} tables, expected {count}")
-    for k in range(count):
-        _need(ts[k], f"{name}[{k}]", (n, n), torch.float32, dev)
+    return _acts(ts, name, (n, n), torch.float32, dev, count)
 
 
 def shared_stack_forward(x, tables, layers, causal, outs=None):
@@ -752,14 +785,13 @@ def shared_stack_forward(x, tables, layers, causal, outs=None):
     dt = _act_dtype(x)
     _need(x, "x", None, dt)
     dev = x.device
-    _tables(tables, "tables", n, dev, L)
+    p_tab = _tables(tables, "tables", n, dev, L)
     if outs is None:
         outs = [torch.empty_like(x) for _ in range(L)]
-    _acts(outs, "outs", shape, dt, dev, L)
+    p_outs = _acts(outs, "outs", shape, dt, dev, L)
     _gpu(dev)
     rc = load().hcmix_shared_stack_forward(batch, n, width, L, _layers(layers), int(bool(causal)),
-                                           _dtype_code(x), _ptr(x), _ptrs(tables[:L]),
-                                           _ptrs(outs[:L]), _stream(x))
+                                           _dtype_code(x), _ptr(x), p_tab, p_outs, _stream(x))
     if rc != HCMIX_OK:
         raise HcmixError(rc, "hcmix_shared_stack_forward")
     return [x, *outs[:L]]
@@ -775,24 +807,23 @@ def shared_stack_backward(xs, tables, layers, dy, causal, dx=None, dtables=None,
     batch, n, width = shape
     dt = _act_dtype(x0, "xs[0]")
     dev = x0.device
-    _acts(xs, "xs", shape, dt, dev, L)
-    _tables(tables, "tables", n, dev, L)
+    p_xs = _acts(xs, "xs", shape, dt, dev, L)
+    p_tab = _tables(tables, "tables", n, dev, L)
     _need(dy, "dy", shape, dt, dev)
     if dx is None:
         dx = torch.empty_like(x0)
     _need(dx, "dx", shape, dt, dev)
     if dtables is None:
         dtables = [torch.empty((n, n), dtype=torch.float32, device=dev) for _ in range(L)]
-    _tables(dtables, "dtables", n, dev, L)
+    p_dt = _tables(dtables, "dtables", n, dev, L)
     _gpu(dev)
     if workspace is None:
         nbytes = load().hcmix_shared_stack_backward_workspace_bytes(batch, n, width, L,
                                                                     _dtype_code(x0))
         workspace = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=dev)
     rc = load().hcmix_shared_stack_backward(batch, n, width, L, _layers(layers),
-                                            int(bool(causal)), _dtype_code(x0), _ptrs(xs[:L]),
-                                            _ptrs(tables[:L]), _ptr(dy), _ptr(dx),
-                                            _ptrs(dtables[:L]), int(bool(accumulate)),
+                                            int(bool(causal)), _dtype_code(x0), p_xs, p_tab,
+                                            _ptr(dy), _ptr(dx), p_dt, int(bool(accumulate)),
                                             _ptr(workspace), _bytes(workspace), _stream(x0))
     if rc != HCMIX_OK:
         raise HcmixError(rc, "hcmix_shared_stack_backward")
@@ -895,8 +926,8 @@ def decode_step(x, w_selfs, w_offs, layers, n, pos, cache, out=None):
     dt = _act_dtype(x)
     _need(x, "x", None, dt)
     dev = x.device
-    _weights(w_selfs, "w_selfs", width, dt, dev, L)
-    _weights(w_offs, "w_offs", width, dt, dev, L)
+    p_ws = _weights(w_selfs, "w_selfs", width, dt, dev, L)
+    p_wo = _weights(w_offs, "w_offs", width, dt, dev, L)
     if out is None:
         out = torch.empty_like(x)
     _need(out, "out", (batch, width), dt, dev)
@@ -904,7 +935,7 @@ def decode_step(x, w_selfs, w_offs, layers, n, pos, cache, out=None):
         raise ValueError(f"cache: expected a tensor on {dev}")
     _gpu(dev)
     rc = load().hcmix_decode_step(batch, n, width, L, _layers(layers), _dtype_code(x), pos,
-                                  _ptr(x), _ptrs(w_selfs), _ptrs(w_offs), _ptr(cache),
+                                  _ptr(x), p_ws, p_wo, _ptr(cache),
                                   _bytes(cache), _ptr(out), _stream(x))
     if rc != HCMIX_OK:
         raise HcmixError(rc, "hcmix_decode_step")

@@ -1,0 +1,37 @@
+"""The binding's native operand checks: what they hand over, and what they leave
+to the binding's own checks (by returning None)."""
+import pytest
+import torch
+
+from paper_2609_18145_amd import hcmix
+
+bf, f32 = torch.bfloat16, torch.float32
+
+
+def call(ts, count, shape, dtype=f32, dev="cpu"):
+    return hcmix._native().pointers(ts, count, shape, dtype, torch.device(dev))
+
+
+def test_cpu_tensors_and_other_operands_are_left_to_the_binding():
+    t = torch.zeros(2, 3)
+    assert call([t], 1, (2, 3)) is None                       # not in GPU memory
+    assert call([t.tolist()], 1, (2, 3), dev="cuda:0") is None
+    assert call([t], 2, (2, 3), dev="cuda:0") is None         # fewer than count
+    assert call(iter([t]), 1, (2, 3), dev="cuda:0") is None   # no list or tuple
+    assert call([torch.zeros(2, 3, device="meta")], 1, (2, 3), dev="meta") is None
+    assert call([], 0, (2, 3)) == b""
+
+
+@pytest.mark.gpu
+def test_addresses_of_matching_tensors_only():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    a = torch.zeros(4, 6, device="cuda:0")
+    p = torch.nn.Parameter(torch.zeros(4, 6, device="cuda:0"))
+    got = call((a, p), 2, (4, 6), dev="cuda:0")
+    assert memoryview(got).cast("P").tolist() == [a.data_ptr(), p.data_ptr()]
+    assert call([a, p], 1, (4, 6), dev="cuda:0") == got[:8]
+    for bad in (a.t(), a[:, :3], a.to(bf), a.cpu(), torch.zeros(4, 7, device="cuda:0"),
+                torch.zeros(4, 6, 1, device="cuda:0"), None, 3):
+        assert call([a, bad], 2, (4, 6), dev="cuda:0") is None
+    assert call([a.t()], 1, (6, 4), dev="cuda:0") is None     # not contiguous
