@@ -1152,7 +1152,7 @@ hcmix_status hcmix_decode_step(int64_t batch, int64_t n, int64_t width, int32_t 
       a.in_stride = a.partner_stride = a.out_stride = a.rec_stride = width;
       a.batch = (int)batch;
       a.width = (int)width;
-      e = whole_width(dtype, width) ? launch_decode_bf16(a, s) : launch_decode_bf16_fma(a, s);
+      e = launch_decode_bf16(a, s);
     } else {
       DecodeLayerArgsF32 a = {};
       a.x_in = (const float*)in;

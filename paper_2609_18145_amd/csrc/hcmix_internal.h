@@ -292,9 +292,7 @@ struct DecodeLayerArgsF32 {
   int64_t in_stride, partner_stride, out_stride, rec_stride;
   int batch, width;
 };
-hipError_t launch_decode_bf16(const DecodeLayerArgs& a, hipStream_t st);   // width % 64 == 0
+hipError_t launch_decode_bf16(const DecodeLayerArgs& a, hipStream_t st);   // width % 8 == 0
 hipError_t launch_decode_f32(const DecodeLayerArgsF32& a, hipStream_t st);
-// bf16 widths that are not a multiple of 64: plain fp32 FMAs, one rounding
-hipError_t launch_decode_bf16_fma(const DecodeLayerArgs& a, hipStream_t st);
 
 }  // namespace hcmix

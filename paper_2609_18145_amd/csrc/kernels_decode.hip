@@ -15,18 +15,58 @@ namespace hcmix {
 
 namespace {
 
-// bf16: one block per 16 output columns x 16 windows (128 blocks at width 512
-// and 64 windows), 16x16x32 MFMAs with the weights as the A operand, so the
-// result is C[o][b].  The 4 waves split the contraction in 32-wide steps
-// (wave w takes steps w, w + 4, ...); each wave loads the self and partner
-// operands of CH steps before any of their MFMAs, so at width 512 every load of
-// the block is in flight at once and a layer costs one memory latency.  The
-// wave partials are summed through LDS in wave order.  Against 32 x 32 blocks
-// of 8 waves (32 blocks at that shape) this spreads the loads over four times
-// as many CUs: 6.3 -> 4.1 us per layer launch in a graph, with partners.
+// One block per 16 output columns x 16 windows (128 blocks at width 512 and 64
+// windows), 16x16 MFMAs with the weights as the A operand, so the result is
+// C[o][b]; bf16 on 16x16x32, fp32 on four 16x16x4 (fp32 products and sums) per
+// step of 16.  The 4 waves split the contraction in steps (wave w takes steps
+// w, w + 4, ...); each wave loads the self and partner operands of CH steps
+// before any of their MFMAs, so at width 512 (bf16) every load of the block is
+// in flight at once and a layer costs one memory latency.  The wave partials
+// are summed through LDS in wave order.  Against 32 x 32 blocks of 8 waves (32
+// blocks at that shape) this spreads the loads over four times as many CUs:
+// 6.3 -> 4.1 us per layer launch in a graph, with partners.
+// RAG: a width that does not fill steps of 64 (bf16: a multiple of 8; fp32: any
+// width and alignment), whose last pieces and columns are zero.  fp32 at width
+// 384 and 64 windows took 91 us per layer with a thread per output, reading
+// a weight row each, against 5.7 us.
 constexpr int DEC_WAVES = 4;
-template <int CH>
-__global__ __launch_bounds__(64 * DEC_WAVES) void decode_bf16_kernel(DecodeLayerArgs a) {
+
+template <typename E> struct DecPiece;   // what a lane loads of one operand and step
+template <> struct DecPiece<bf16> { typedef bf16x8 T; static constexpr int V = 8; };
+template <> struct DecPiece<float> { typedef f32x4 T; static constexpr int V = 4; };
+
+__device__ __forceinline__ f32x4 dec_mma(const bf16x8& a, const bf16x8& b, const f32x4& c) {
+  return mfma16(a, b, c);
+}
+__device__ __forceinline__ f32x4 dec_mma(const f32x4& a, const f32x4& b, f32x4 c) {
+#pragma unroll
+  for (int e = 0; e < 4; e++) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], c, 0, 0, 0);
+  return c;
+}
+
+// V elements from column k of a row (zero past the width)
+template <typename E, bool RAG>
+__device__ __forceinline__ typename DecPiece<E>::T dec_load(const E* row, int k, int w) {
+  typedef typename DecPiece<E>::T T;
+  if constexpr (!RAG) return *(const T*)(row + k);
+  T v = {};
+  if constexpr (sizeof(E) == 2) {
+    if (k < w) v = *(const T*)(row + k);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; e++)
+      if (k + e < w) v[e] = row[k + e];
+  }
+  return v;
+}
+
+__device__ __forceinline__ bf16 dec_round(float v, bf16) { return to_bf16(v); }
+__device__ __forceinline__ float dec_round(float v, float) { return v; }
+
+template <typename E, typename Args, int CH, bool RAG>
+__global__ __launch_bounds__(64 * DEC_WAVES) void decode_kernel(Args a) {
+  typedef typename DecPiece<E>::T T;
+  constexpr int V = DecPiece<E>::V, STEP = 4 * V;
   __shared__ f32x4 part[DEC_WAVES][64];
   // `wave` and `has_partner` are wave-uniform and must be known so: an MFMA
   // under a lane mask (EXEC) still writes its whole result, so every MFMA
@@ -37,38 +77,47 @@ __global__ __launch_bounds__(64 * DEC_WAVES) void decode_bf16_kernel(DecodeLayer
   const int o0 = blockIdx.x * 16, b0 = blockIdx.y * 16;
   const int w = a.width;
   const int b = min(b0 + (lane & 15), a.batch - 1);      // clamped; stores are masked
-  const int q = lane >> 4;                               // K piece 8q .. 8q + 7 of a step
-  const bf16* xin = a.x_in + (size_t)b * a.in_stride;
-  const bf16* xp = has_partner ? a.x_partner + (size_t)b * a.partner_stride : a.x_in;
-  const bf16* ws = a.w_self + (size_t)(o0 + (lane & 15)) * w;
-  const bf16* wo = a.w_off + (size_t)(o0 + (lane & 15)) * w;
+  const int orow = RAG ? min(o0 + (lane & 15), w - 1) : o0 + (lane & 15);
+  const int q = lane >> 4;                               // K piece V q .. V q + V - 1 of a step
+  const E* xin = a.x_in + (size_t)b * a.in_stride;
+  const E* xp = has_partner ? a.x_partner + (size_t)b * a.partner_stride : a.x_in;
+  const E* ws = a.w_self + (size_t)orow * w;
+  const E* wo = a.w_off + (size_t)orow * w;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  const int ksteps = w / 32;
+  const int ksteps = RAG ? (w + STEP - 1) / STEP : w / STEP;
   for (int kb = wave; kb < ksteps; kb += DEC_WAVES * CH) {
-    bf16x8 sw[CH], sx[CH], pw[CH], px[CH];
+    T sw[CH], sx[CH], pw[CH], px[CH];
 #pragma unroll
     for (int j = 0; j < CH; j++) {
       const int k = kb + DEC_WAVES * j;
-      const int k0 = (k < ksteps ? k : 0) * 32 + 8 * q;   // clamped; the MFMA is skipped
-      sw[j] = *(const bf16x8*)(ws + k0);
-      sx[j] = *(const bf16x8*)(xin + k0);
+      const int k0 = (k < ksteps ? k : 0) * STEP + V * q;   // clamped; the MFMA is skipped
+      sw[j] = dec_load<E, RAG>(ws, k0, w);
+      sx[j] = dec_load<E, RAG>(xin, k0, w);
       if (has_partner) {
-        pw[j] = *(const bf16x8*)(wo + k0);
-        px[j] = *(const bf16x8*)(xp + k0);
+        pw[j] = dec_load<E, RAG>(wo, k0, w);
+        px[j] = dec_load<E, RAG>(xp, k0, w);
       }
     }
 #pragma unroll
     for (int j = 0; j < CH; j++) {
       if (kb + DEC_WAVES * j >= ksteps) continue;
-      acc = mfma16(sw[j], sx[j], acc);
-      if (has_partner) acc = mfma16(pw[j], px[j], acc);
+      acc = dec_mma(sw[j], sx[j], acc);
+      if (has_partner) acc = dec_mma(pw[j], px[j], acc);
     }
   }
   part[wave][lane] = acc;
   // the layer records its input for a later position: this block's 16 columns
   if (a.record && wave == 0 && b0 + (lane & 15) < a.batch) {
     const int c = o0 + 4 * q;
-    *(bf16x4*)(a.record + (size_t)b * a.rec_stride + c) = *(const bf16x4*)(xin + c);
+    E* rec = a.record + (size_t)b * a.rec_stride;
+    if constexpr (RAG) {
+#pragma unroll
+      for (int e = 0; e < 4; e++)
+        if (c + e < w) rec[c + e] = xin[c + e];
+    } else {
+      typedef E E4 __attribute__((ext_vector_type(4)));
+      *(E4*)(rec + c) = *(const E4*)(xin + c);
+    }
   }
   __syncthreads();
   if (wave != 0) return;
@@ -77,57 +126,43 @@ __global__ __launch_bounds__(64 * DEC_WAVES) void decode_bf16_kernel(DecodeLayer
   for (int v = 1; v < DEC_WAVES; v++) s += part[v][lane];
   if (b0 + (lane & 15) >= a.batch) return;
   // C[o][b]: lane l holds window b0 + l%16 and outputs o0 + 4 (l/16) + 0..3
-  const bf16x4 v = {to_bf16(s[0]), to_bf16(s[1]), to_bf16(s[2]), to_bf16(s[3])};
-  *(bf16x4*)(a.out + (size_t)b * a.out_stride + o0 + 4 * q) = v;
-}
-
-// fp32 arithmetic, one thread per output (window b, column o), plain FMAs:
-// fp32 data, or bf16 widths that are not a multiple of 64 (operands widened
-// exactly, the output rounded once).
-__device__ __forceinline__ float dec_widen(float v) { return v; }
-__device__ __forceinline__ float dec_widen(bf16 v) { return (float)v; }
-__device__ __forceinline__ void dec_store(float* p, float v) { *p = v; }
-__device__ __forceinline__ void dec_store(bf16* p, float v) { *p = to_bf16(v); }
-
-template <typename Args>
-__global__ __launch_bounds__(256) void decode_fma_kernel(Args a) {
-  const int o = blockIdx.x * 64 + (threadIdx.x & 63);
-  const int b = blockIdx.y * 4 + (threadIdx.x >> 6);
-  if (o >= a.width || b >= a.batch) return;
-  const auto* xin = a.x_in + (size_t)b * a.in_stride;
-  float acc = 0.f;
-  for (int c = 0; c < a.width; c++)
-    acc = fmaf(dec_widen(a.w_self[(size_t)o * a.width + c]), dec_widen(xin[c]), acc);
-  if (a.x_partner) {
-    const auto* xp = a.x_partner + (size_t)b * a.partner_stride;
-    for (int c = 0; c < a.width; c++)
-      acc = fmaf(dec_widen(a.w_off[(size_t)o * a.width + c]), dec_widen(xp[c]), acc);
+  E* out = a.out + (size_t)b * a.out_stride + o0 + 4 * q;
+  if constexpr (RAG) {
+#pragma unroll
+    for (int e = 0; e < 4; e++)
+      if (o0 + 4 * q + e < w) out[e] = dec_round(s[e], E());
+  } else {
+    typedef E E4 __attribute__((ext_vector_type(4)));
+    *(E4*)out = E4{dec_round(s[0], E()), dec_round(s[1], E()), dec_round(s[2], E()),
+                   dec_round(s[3], E())};
   }
-  if (a.record) a.record[(size_t)b * a.rec_stride + o] = xin[o];
-  dec_store(a.out + (size_t)b * a.out_stride + o, acc);
 }
 
 }  // namespace
 
-hipError_t launch_decode_bf16(const DecodeLayerArgs& a, hipStream_t st) {
-  // CH: steps per wave per round, as many as cover the width (no clamped
-  // duplicate loads) up to 4 (the whole of width 512 in one round)
-  const dim3 grid(a.width / 16, (a.batch + 15) / 16);
-  const int ksteps = a.width / 32;
-  if (ksteps <= DEC_WAVES) decode_bf16_kernel<1><<<grid, 64 * DEC_WAVES, 0, st>>>(a);
-  else if (ksteps <= 2 * DEC_WAVES) decode_bf16_kernel<2><<<grid, 64 * DEC_WAVES, 0, st>>>(a);
-  else decode_bf16_kernel<4><<<grid, 64 * DEC_WAVES, 0, st>>>(a);
+// CH: steps per wave per round, as many as cover the width (no clamped
+// duplicate loads) up to 4 (the whole of a bf16 width of 512 in one round).
+template <typename E, bool RAG, typename Args>
+static hipError_t decode_launch(const Args& a, hipStream_t st) {
+  constexpr int STEP = 4 * DecPiece<E>::V;
+  const dim3 grid((a.width + 15) / 16, (a.batch + 15) / 16);
+  const int ksteps = (a.width + STEP - 1) / STEP;
+  if (ksteps <= DEC_WAVES) decode_kernel<E, Args, 1, RAG><<<grid, 64 * DEC_WAVES, 0, st>>>(a);
+  else if (ksteps <= 2 * DEC_WAVES) decode_kernel<E, Args, 2, RAG><<<grid, 64 * DEC_WAVES, 0, st>>>(a);
+  else decode_kernel<E, Args, 4, RAG><<<grid, 64 * DEC_WAVES, 0, st>>>(a);
   return hipGetLastError();
+}
+
+hipError_t launch_decode_bf16(const DecodeLayerArgs& a, hipStream_t st) {
+  return a.width % 64 == 0 ? decode_launch<bf16, false>(a, st) : decode_launch<bf16, true>(a, st);
 }
 
 hipError_t launch_decode_f32(const DecodeLayerArgsF32& a, hipStream_t st) {
-  decode_fma_kernel<<<dim3((a.width + 63) / 64, (a.batch + 3) / 4), 256, 0, st>>>(a);
-  return hipGetLastError();
-}
-
-hipError_t launch_decode_bf16_fma(const DecodeLayerArgs& a, hipStream_t st) {
-  decode_fma_kernel<<<dim3((a.width + 63) / 64, (a.batch + 3) / 4), 256, 0, st>>>(a);
-  return hipGetLastError();
+  auto al = [](const void* p) { return ((uintptr_t)p & 15) == 0; };   // (null: aligned)
+  const bool whole = a.width % 16 == 0 && a.in_stride % 4 == 0 && a.partner_stride % 4 == 0 &&
+                     a.out_stride % 4 == 0 && a.rec_stride % 4 == 0 && al(a.x_in) &&
+                     al(a.x_partner) && al(a.w_self) && al(a.w_off) && al(a.out) && al(a.record);
+  return whole ? decode_launch<float, false>(a, st) : decode_launch<float, true>(a, st);
 }
 
 }  // namespace hcmix

@@ -109,3 +109,28 @@ def test_stack_backward_with_whole_and_least_workspace(batch, n, width, dtype, s
     for _, acc in got:
         for g, r in zip(acc, rws + rwo):
             assert fro_rel_err(to_host(g) - 0.5, r) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("batch,width,dtype,off", [
+    (17, 1, "f32", 0), (5, 33, "f32", 0), (16, 64, "f32", 0), (3, 64, "f32", 1), (18, 272, "f32", 0),
+    (17, 40, "bf16", 0), (3, 264, "bf16", 0)])
+def test_decode(batch, width, dtype, off):
+    """Widths off the kernel's steps and columns, and 4-byte aligned fp32 (off)."""
+    n, codes, refs = 8, [0, 2, hcmix.LAYER_NEAR, 1], [0, 2, oracle.NEAR, 1]
+    s = inputs.make_stack(batch, n, width, 4, True, dtype, seed=width, layers=refs, with_dy=False)
+    want = oracle.stack_forward(s.x, s.w_self, s.w_off, refs, True)[-1]
+
+    def dev(a):
+        t = to_dev(np.ascontiguousarray(a), dtype)
+        buf = torch.zeros(t.numel() + off, dtype=t.dtype, device="cuda")
+        v = buf[off:].view(t.shape)
+        v.copy_(t)
+        return v
+
+    ws, wo = ([dev(w) for w in m] for m in (s.w_self, s.w_off))
+    cache = hcmix.alloc_decode_cache(batch, n, width, codes, ws[0].dtype, ws[0].device)
+    cache.fill_(0xFF)
+    got = np.stack([to_host(hcmix.decode_step(dev(s.x[:, pos]), ws, wo, codes, n, pos, cache))
+                    for pos in range(n)], 1)
+    # (four bf16 roundings of rows of 40 values: two thirds of the tolerance)
+    assert row_rel_err(got, want) <= TOL[dtype]
