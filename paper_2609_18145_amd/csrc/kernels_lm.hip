@@ -737,11 +737,17 @@ static hipError_t head_dw_launch(const bf16* dl, const bf16* x, float* part, int
 hipError_t launch_head_backward(const bf16* x, const bf16* w, const bf16* dl, bf16* gx, float* dw,
                                 int accumulate, float* workspace, size_t workspace_bytes, int rows,
                                 int width, int vocab, hipStream_t st) {
-  const int tk_n = (width + HB_TILE - 1) / HB_TILE;
   if (gx) {
-    const int tr_n = (rows + HB_TILE - 1) / HB_TILE;
-    head_gx_kernel<<<tr_n * tk_n, 256, 0, st>>>(dl, w, gx, rows, width, vocab);
-    hipError_t e = hipGetLastError();
+    // gx = dl W is the linear maps' input gradient; that block takes whole
+    // 64-wide slices and row pairs (16384 rows, 512 x 256: 15.8 -> 9.5 us)
+    hipError_t e;
+    if (vocab % 64 == 0 && rows % 2 == 0) {
+      e = launch_gemm_bf16(dl, w, gx, rows, vocab, width, width, width, /*transpose_b=*/true, st);
+    } else {
+      const int tk_n = (width + HB_TILE - 1) / HB_TILE, tr_n = (rows + HB_TILE - 1) / HB_TILE;
+      head_gx_kernel<<<tr_n * tk_n, 256, 0, st>>>(dl, w, gx, rows, width, vocab);
+      e = hipGetLastError();
+    }
     if (e != hipSuccess) return e;
   }
   if (!dw) return hipSuccess;
