@@ -61,12 +61,13 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attn_fwd_kernel(
   constexpr int n = NT * 32;
   __shared__ __attribute__((aligned(1024))) bf16 sK[n * HD], sV[n * HD];
   const int bh = blockIdx.x, b = bh / heads, h = bh % heads;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
+  const int lane = threadIdx.x & 63, half = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const size_t rs = (size_t)3 * heads * HD;                 // qkv row stride
   const bf16* base = qkv + (size_t)b * n * rs + (size_t)h * HD;
   att_load_tiles<NT>(base + (size_t)heads * HD, rs, sK, base + (size_t)2 * heads * HD, rs, sV);
   __syncthreads();
-  const float sc = 0.125f * LOG2E;     // scores in log2 units
+  const float sc = 0.125f * LOG2E;     // to log2 units
 #pragma unroll
   for (int which = 0; which < 2; which++) {
     const int qt = att_tile(wave, which);
@@ -84,23 +85,21 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attn_fwd_kernel(
       f32x16 acc = {};
 #pragma unroll
       for (int ks = 0; ks < 4; ks++) acc = mfma32(att_frag(sK, kt * 32, 16 * ks, lane), qf[ks], acc);
+      if (kt == qt)    // the diagonal tile: wave-uniform, no select in the others
 #pragma unroll
-      for (int e = 0; e < 16; e++) {
-        float v = acc[e] * sc;
-        if (kt == qt && att_masked(e, lane)) v = -INFINITY;
-        acc[e] = v;
-        mx = fmaxf(mx, v);
-      }
+        for (int e = 0; e < 16; e++) acc[e] = att_masked(e, lane) ? -INFINITY : acc[e];
+#pragma unroll
+      for (int e = 0; e < 16; e++) mx = fmaxf(mx, acc[e]);
       s[kt] = acc;
     }
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    mx = fmaxf(mx, __shfl_xor(mx, 32)) * sc;     // log2 units; the scores stay unscaled
     float sum = 0.f;
 #pragma unroll
     for (int kt = 0; kt < NT; kt++) {
       if (kt > qt) continue;
 #pragma unroll
       for (int e = 0; e < 16; e++) {
-        const float p = __builtin_amdgcn_exp2f(s[kt][e] - mx);
+        const float p = __builtin_amdgcn_exp2f(fmaf(s[kt][e], sc, -mx));
         s[kt][e] = p;
         sum += p;
       }
@@ -145,41 +144,66 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attn_fwd_kernel(
 // P, S and dP are recomputed rather than stored; no atomics, deterministic.
 // ---------------------------------------------------------------------------
 
-// lse in log2 units and D = rowsum(dO * O) of the window's rows into LDS.
-__device__ __forceinline__ void att_row_stats(const bf16* __restrict__ obase,
-                                              const bf16* __restrict__ dobase, size_t os,
-                                              const float* __restrict__ lse_row, int n, float* sL,
-                                              float* sD) {
-  for (int i = threadIdx.x; i < n; i += ATT_THREADS) {
-    float d = 0.f;
-#pragma unroll
-    for (int p = 0; p < 8; p++) {
-      const bf16x8 a = *(const bf16x8*)(obase + (size_t)i * os + 8 * p);
-      const bf16x8 g = *(const bf16x8*)(dobase + (size_t)i * os + 8 * p);
-#pragma unroll
-      for (int e = 0; e < 8; e++) d += (float)a[e] * (float)g[e];
-    }
-    sD[i] = d;
-    sL[i] = lse_row[i] * LOG2E;
-  }
+// Sum over the 8 lanes of an aligned group, by lane moves.
+template <int CTRL>
+__device__ __forceinline__ float att_dpp(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float att_sum8(float v) {
+  v += att_dpp<0xb1>(v);          // quad_perm [1,0,3,2]
+  v += att_dpp<0x4e>(v);          // quad_perm [2,3,0,1]
+  return v + att_dpp<0x141>(v);   // row_half_mirror
 }
 
 template <int NT>
 __global__ __launch_bounds__(ATT_THREADS, 2) void attn_bwd_kv_kernel(
     const bf16* __restrict__ qkv, const bf16* __restrict__ out, const float* __restrict__ lse,
-    const bf16* __restrict__ dout, bf16* __restrict__ dqkv, int heads) {
+    const bf16* __restrict__ dout, bf16* dqkv, int heads) {
   constexpr int n = NT * 32;
   __shared__ __attribute__((aligned(1024))) bf16 sQ[n * HD], sO[n * HD];   // sO: dO
   __shared__ __attribute__((aligned(16))) float sL[n], sD[n];
   const int bh = blockIdx.x, b = bh / heads, h = bh % heads;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
+  const int lane = threadIdx.x & 63, half = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const size_t rs = (size_t)3 * heads * HD, os = (size_t)heads * HD;
   const bf16* base = qkv + (size_t)b * n * rs + (size_t)h * HD;
   const bf16* dobase = dout + (size_t)b * n * os + (size_t)h * HD;
   bf16* gbase = dqkv + (size_t)b * n * rs + (size_t)h * HD;
-  att_load_tiles<NT>(base, rs, sQ, dobase, os, sO);
-  att_row_stats(out + (size_t)b * n * os + (size_t)h * HD, dobase, os, lse + (size_t)bh * n, n,
-                sL, sD);
+  // Q and dO to LDS, and D = rowsum(dO * O) on the way: the 8 lanes that load a
+  // row's pieces of dO load those of O too.  D also goes to the first four
+  // bytes of the row's dQ, where attn_bwd_q_kernel finds it before it writes dQ
+  // (reading O and dO again there, a row per thread, took a fifth of its time).
+  {
+    const bf16* obase = out + (size_t)b * n * os + (size_t)h * HD;
+    u32x4 vq[NT], vd[NT], vo[NT];
+#pragma unroll
+    for (int j = 0; j < NT; j++) {
+      const int pi = threadIdx.x + ATT_THREADS * j, r = pi >> 3, p = pi & 7;
+      vd[j] = *(const u32x4*)(dobase + (size_t)r * os + 8 * p);
+      vo[j] = *(const u32x4*)(obase + (size_t)r * os + 8 * p);
+      vq[j] = *(const u32x4*)(base + (size_t)r * rs + 8 * p);
+    }
+    for (int i = threadIdx.x; i < n; i += ATT_THREADS) sL[i] = lse[(size_t)bh * n + i] * LOG2E;
+#pragma unroll
+    for (int j = 0; j < NT; j++) {
+      const int pi = threadIdx.x + ATT_THREADS * j, r = pi >> 3, p = pi & 7;
+      *(u32x4*)(sO + att_off(r, 8 * p)) = vd[j];
+      const bf16x8 a = __builtin_bit_cast(bf16x8, vd[j]), o = __builtin_bit_cast(bf16x8, vo[j]);
+      float d = 0.f;
+#pragma unroll
+      for (int e = 0; e < 8; e++) d += (float)a[e] * (float)o[e];
+      d = att_sum8(d);
+      if (p == 0) {
+        sD[r] = d;
+        *(float*)(gbase + (size_t)r * rs) = d;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < NT; j++) {
+      const int pi = threadIdx.x + ATT_THREADS * j, r = pi >> 3, p = pi & 7;
+      *(u32x4*)(sQ + att_off(r, 8 * p)) = vq[j];
+    }
+  }
   __syncthreads();
   const float sc = 0.125f * LOG2E;
 #pragma unroll
@@ -210,15 +234,21 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attn_bwd_kv_kernel(
       for (int g = 0; g < 4; g++) {
         const int q0 = qt * 32 + 8 * g + 4 * half;
         const f32x4 l4 = *(const f32x4*)(sL + q0);
-        const f32x4 d4 = *(const f32x4*)(sD + q0);
 #pragma unroll
         for (int r = 0; r < 4; r++) {
           const int e = 4 * g + r;
-          const bool masked = qt == kt && (lane & 31) > 8 * g + 4 * half + r;
-          const float pe = masked ? 0.f : __builtin_amdgcn_exp2f(sacc[e] * sc - l4[r]);
-          p[e] = pe;
-          ds[e] = pe * (pacc[e] - d4[r]);
+          p[e] = __builtin_amdgcn_exp2f(fmaf(sacc[e], sc, -l4[r]));
         }
+      }
+      if (qt == kt)    // wave-uniform
+#pragma unroll
+        for (int e = 0; e < 16; e++)
+          p[e] = (lane & 31) > 8 * (e >> 2) + 4 * half + (e & 3) ? 0.f : p[e];
+#pragma unroll
+      for (int g = 0; g < 4; g++) {
+        const f32x4 d4 = *(const f32x4*)(sD + qt * 32 + 8 * g + 4 * half);
+#pragma unroll
+        for (int r = 0; r < 4; r++) ds[4 * g + r] = p[4 * g + r] * (pacc[4 * g + r] - d4[r]);
       }
 #pragma unroll
       for (int m = 0; m < 2; m++) {
@@ -250,20 +280,23 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attn_bwd_kv_kernel(
 
 template <int NT>
 __global__ __launch_bounds__(ATT_THREADS, 2) void attn_bwd_q_kernel(
-    const bf16* __restrict__ qkv, const bf16* __restrict__ out, const float* __restrict__ lse,
-    const bf16* __restrict__ dout, bf16* __restrict__ dqkv, int heads) {
+    const bf16* __restrict__ qkv, const float* __restrict__ lse, const bf16* __restrict__ dout,
+    bf16* dqkv, int heads) {
   constexpr int n = NT * 32;
   __shared__ __attribute__((aligned(1024))) bf16 sK[n * HD], sV[n * HD];
   __shared__ __attribute__((aligned(16))) float sL[n], sD[n];
   const int bh = blockIdx.x, b = bh / heads, h = bh % heads;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
+  const int lane = threadIdx.x & 63, half = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const size_t rs = (size_t)3 * heads * HD, os = (size_t)heads * HD;
   const bf16* base = qkv + (size_t)b * n * rs + (size_t)h * HD;
   const bf16* dobase = dout + (size_t)b * n * os + (size_t)h * HD;
   bf16* gbase = dqkv + (size_t)b * n * rs + (size_t)h * HD;
+  for (int i = threadIdx.x; i < n; i += ATT_THREADS) {
+    sD[i] = *(const float*)(gbase + (size_t)i * rs);   // left there by attn_bwd_kv_kernel
+    sL[i] = lse[(size_t)bh * n + i] * LOG2E;
+  }
   att_load_tiles<NT>(base + os, rs, sK, base + 2 * os, rs, sV);
-  att_row_stats(out + (size_t)b * n * os + (size_t)h * HD, dobase, os, lse + (size_t)bh * n, n,
-                sL, sD);
   __syncthreads();
   const float sc = 0.125f * LOG2E;
 #pragma unroll
@@ -290,11 +323,12 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attn_bwd_q_kernel(
       }
       f32x16 ds;
 #pragma unroll
-      for (int e = 0; e < 16; e++) {
-        const bool masked = kt == qt && att_masked(e, lane);
-        const float pe = masked ? 0.f : __builtin_amdgcn_exp2f(sacc[e] * sc - lq);
-        ds[e] = pe * (pacc[e] - dq);
-      }
+      for (int e = 0; e < 16; e++) ds[e] = __builtin_amdgcn_exp2f(fmaf(sacc[e], sc, -lq));
+      if (kt == qt)    // wave-uniform
+#pragma unroll
+        for (int e = 0; e < 16; e++) ds[e] = att_masked(e, lane) ? 0.f : ds[e];
+#pragma unroll
+      for (int e = 0; e < 16; e++) ds[e] *= pacc[e] - dq;
 #pragma unroll
       for (int m = 0; m < 2; m++) {
         const bf16x8 sf = att_pack(ds, m);
@@ -328,7 +362,7 @@ hipError_t attn_bwd_launch(const bf16* qkv, const bf16* out, const float* lse, c
   attn_bwd_kv_kernel<NT><<<batch * heads, ATT_THREADS, 0, st>>>(qkv, out, lse, dout, dqkv, heads);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  attn_bwd_q_kernel<NT><<<batch * heads, ATT_THREADS, 0, st>>>(qkv, out, lse, dout, dqkv, heads);
+  attn_bwd_q_kernel<NT><<<batch * heads, ATT_THREADS, 0, st>>>(qkv, lse, dout, dqkv, heads);
   return hipGetLastError();
 }
 
