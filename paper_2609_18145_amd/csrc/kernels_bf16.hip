@@ -52,7 +52,8 @@ __device__ __forceinline__ int whole_tiles(int width, int tile) {
 // ---------------------------------------------------------------------------
 // WK: groups of WM x WN waves that share the tile and split each K-step's k16
 // slices; their sums meet in LDS at the end, in group order.
-template <int BMP, int BN, int WM, int WN, int WK, int BK, int NS>
+// NB: B operands (2 with a partner term, 1 for a plain product).
+template <int BMP, int BN, int WM, int WN, int WK, int BK, int NS, int NB>
 struct MixCfg {
   static constexpr int NW = WM * WN * WK;
   static constexpr int NT = 64 * NW;
@@ -61,7 +62,7 @@ struct MixCfg {
   static constexpr int TN = BN / (32 * WN);     // 32-column blocks per wave
   static constexpr int A_ELEMS = BM * BK;
   static constexpr int B_ELEMS = BN * BK;       // same size in both layouts
-  static constexpr int STAGE = A_ELEMS + 2 * B_ELEMS;
+  static constexpr int STAGE = A_ELEMS + NB * B_ELEMS;
   static constexpr int LDO = BN + 8;            // row stride of the output staging tile
   static constexpr int ACC = 2 * TMP * TN * 16; // accumulators per lane
   static constexpr int O_ELEMS = BM * LDO + (WK - 1) * WM * WN * ACC * 64 * 2;
@@ -71,8 +72,9 @@ struct MixCfg {
   static constexpr int O_IT = BM * (BN / 8) / NT;
   static_assert(TMP >= 1 && TN >= 1, "tile too small for the wave grid");
   static_assert(A_DMA * NW * 1024 == A_ELEMS * 2 && B_DMA * NW * 1024 == B_ELEMS * 2, "");
+  static constexpr int DPS = A_DMA + NB * B_DMA;          // DMA instructions per wave per stage
   static_assert(O_IT * NT == BM * (BN / 8), "stores must tile evenly");
-  static_assert(NS >= 2 && (NS - 1) * (A_DMA + 2 * B_DMA) <= 63, "vmcnt range");
+  static_assert(NS >= 2 && (NS - 1) * DPS <= 63, "vmcnt range");
 };
 
 // One block's work: `block` indexes the (row tile, column tile) grid, dealt
@@ -90,10 +92,10 @@ __device__ __forceinline__ void mix_bf16_block(
     const bf16* __restrict__ A, const bf16* __restrict__ B1, const bf16* __restrict__ B2,
     bf16* __restrict__ out, int pairs, int K, int N, int ldb, int ldo, int d, int block,
     bf16* smem) {
-  using C = MixCfg<BMP, BN, WM, WN, WK, BK, NS>;
-  constexpr int RB = BN * 2;   // bytes per row of a transposed B tile
   constexpr bool HAS_B2 = PL || PU;
-  constexpr int DPS = C::A_DMA + (HAS_B2 ? 2 : 1) * C::B_DMA;   // DMA instructions per wave and stage
+  using C = MixCfg<BMP, BN, WM, WN, WK, BK, NS, HAS_B2 ? 2 : 1>;
+  constexpr int RB = BN * 2;   // bytes per row of a transposed B tile
+  constexpr int DPS = C::DPS;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1040,6 +1042,7 @@ constexpr int DW_TARGET_BLOCKS = 256;  // split-K blocks aimed for (8 waves each
 // big one, 4/14 of a 256-column and 4/5 of a 64-column one (widths 1024, 192).
 // Weights read transposed need 64 columns at least: the small block is then
 // 32 x 64, 6.6 us at 2048 rows x 512, in one round only.
+// The linear maps' big block is 64 x 128, two to a CU: as many rows to a round.
 enum class Tile { kSmall, kMid, kBig };
 Tile pick_tile(int pairs, int width, int big_cols, bool transposed) {
   auto blocks = [&](int p, int c) { return (int64_t)((pairs + p - 1) / p) * ((width + c - 1) / c); };
@@ -1053,7 +1056,7 @@ Tile pick_tile(int pairs, int width, int big_cols, bool transposed) {
 template <int BMP, int BN, int WM, int WN, int WK, int BK, int NS, bool TRANS_B, bool RAG>
 hipError_t mix_launch(const bf16* A, const bf16* B1, const bf16* B2, bf16* out, int pairs,
                       int width, int d, int partner_lower, int partner_upper, hipStream_t st) {
-  using C = MixCfg<BMP, BN, WM, WN, WK, BK, NS>;
+  using C = MixCfg<BMP, BN, WM, WN, WK, BK, NS, 2>;
   const int blocks = ((pairs + BMP - 1) / BMP) * ((width + BN - 1) / BN);
   const size_t lds = (size_t)C::LDS_ELEMS * sizeof(bf16);
 #define HCMIX_MIX(PL, PU)                                                                   \
@@ -1074,14 +1077,14 @@ hipError_t mix_launch(const bf16* A, const bf16* B1, const bf16* B2, bf16* out, 
 // The plain product instance (no partner terms): out [rows][N] (row stride
 // ldo) = A [rows][K] B^T with B [N][ldb] k-contiguous, or A B with B [K][ldb]
 // (TRANS_B).  Rows in consecutive pairs (dimension 0).
-template <int BMP, int BN, int WM, int WN, int WK, int NS, bool TRANS_B>
+template <int BMP, int BN, int WM, int WN, int WK, int BK, int NS, bool TRANS_B>
 hipError_t gemm_launch(const bf16* A, const bf16* B, bf16* out, int rows, int K, int N, int ldb,
                        int ldo, hipStream_t st) {
-  using C = MixCfg<BMP, BN, WM, WN, WK, MIX_BK, NS>;
+  using C = MixCfg<BMP, BN, WM, WN, WK, BK, NS, 1>;
   const int pairs = rows / 2;
   const int blocks = ((pairs + BMP - 1) / BMP) * (N / BN);
   const size_t lds = (size_t)C::LDS_ELEMS * sizeof(bf16);
-  auto k = mix_bf16_kernel<BMP, BN, WM, WN, WK, MIX_BK, NS, false, false, TRANS_B, false>;
+  auto k = mix_bf16_kernel<BMP, BN, WM, WN, WK, BK, NS, false, false, TRANS_B, false>;
   static std::atomic<unsigned long long> lds_set{0};
   const hipError_t attr = lds_limit_once(lds_set, (const void*)k, (int)lds);
   if (attr != hipSuccess) return attr;
@@ -1225,18 +1228,23 @@ hipError_t dw_launch(const bf16* X, const bf16* dY, float* partial, int pairs, i
 
 hipError_t launch_gemm_bf16(const bf16* A, const bf16* B, bf16* out, int rows, int K, int N,
                             int ldb, int ldo, bool transpose_b, hipStream_t st) {
-#define HCMIX_GEMM(BMP, BN, WM, WN, WK, NS)                                                       \
-  (transpose_b ? gemm_launch<BMP, BN, WM, WN, WK, NS, true>(A, B, out, rows, K, N, ldb, ldo, st)  \
-               : gemm_launch<BMP, BN, WM, WN, WK, NS, false>(A, B, out, rows, K, N, ldb, ldo, st))
+#define HCMIX_GEMM(...)                                                                    \
+  (transpose_b ? gemm_launch<__VA_ARGS__, true>(A, B, out, rows, K, N, ldb, ldo, st)       \
+               : gemm_launch<__VA_ARGS__, false>(A, B, out, rows, K, N, ldb, ldo, st))
   const bool wide = N % 128 == 0;
   const Tile tile = pick_tile(rows / 2, N, wide ? 128 : 64, transpose_b);
   if (tile == Tile::kSmall)
     return transpose_b
-               ? gemm_launch<32, 64, 1, 2, 2, 3, true>(A, B, out, rows, K, N, ldb, ldo, st)
-               : gemm_launch<32, 32, 1, 1, 4, 3, false>(A, B, out, rows, K, N, ldb, ldo, st);
-  if (tile == Tile::kMid) return HCMIX_GEMM(64, 64, 2, 2, 1, 3);
-  if (wide) return HCMIX_GEMM(MIX_BMP, 128, 2, 4, 1, MIX_NS);
-  return HCMIX_GEMM(MIX_BMP, 64, 4, 1, 1, MIX_NS);
+               ? gemm_launch<32, 64, 1, 2, 2, MIX_BK, 3, true>(A, B, out, rows, K, N, ldb, ldo, st)
+               : gemm_launch<32, 32, 1, 1, 4, MIX_BK, 3, false>(A, B, out, rows, K, N, ldb, ldo, st);
+  if (tile == Tile::kMid) return HCMIX_GEMM(64, 64, 2, 2, 1, MIX_BK, 3);
+  // 64 pairs x 128 columns in eight waves, two blocks per CU, so that one's
+  // first loads and stores pass under the other's products.  us, against 128 x
+  // 128 (one block per CU), as given | transposed: 16384 x 512 -> 512 12.9 | 12.8
+  // to 11.9 | 12.9, 8192 x 512 -> 1536 21.1 | 22.9 to 18.0 | 19.3, 16384 x 256 ->
+  // 512 8.7 | 10.1 to 8.3 | 7.9, 16384 x 512 -> 1536 37.2 | 29.4 to 37.2 | 29.0.
+  if (wide) return HCMIX_GEMM(64, 128, 2, 4, 1, MIX_BK, MIX_NS);
+  return HCMIX_GEMM(MIX_BMP, 64, 4, 1, 1, MIX_BK, MIX_NS);
 #undef HCMIX_GEMM
 }
 
