@@ -119,15 +119,9 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attn_fwd_kernel(
     }
     // O^T register e of lane l: query q, dimension 32 dt + 8 (e / 4) + 4 half + e % 4
     const float inv = 1.f / sum;
-    bf16* orow = out + (((size_t)b * n + q) * heads + h) * HD;
+    bf16* otile = out + (((size_t)b * n + qt * 32) * heads + h) * HD;
 #pragma unroll
-    for (int dt = 0; dt < 2; dt++)
-#pragma unroll
-      for (int g = 0; g < 4; g++) {
-        const bf16x4 v = {to_bf16(o[dt][4 * g] * inv), to_bf16(o[dt][4 * g + 1] * inv),
-                          to_bf16(o[dt][4 * g + 2] * inv), to_bf16(o[dt][4 * g + 3] * inv)};
-        *(bf16x4*)(orow + 32 * dt + 8 * g + 4 * half) = v;
-      }
+    for (int dt = 0; dt < 2; dt++) att_store(otile + 32 * dt, (size_t)heads * HD, o[dt], inv, lane);
     if (half == 0) lse[(size_t)bh * n + q] = (mx + __builtin_amdgcn_logf(sum)) * 0.6931471805599453f;
   }
 }
@@ -261,20 +255,12 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attn_bwd_kv_kernel(
       }
     }
     // dK^T / dV^T register e of lane l: key kt*32 + l%32, dim 32 dt + 8 (e/4) + 4 half + e%4
-    bf16* krow = gbase + (size_t)key * rs + os;
-    bf16* vrow = gbase + (size_t)key * rs + 2 * os;
+    bf16* ktile = gbase + (size_t)(kt * 32) * rs + os;
 #pragma unroll
-    for (int dt = 0; dt < 2; dt++)
-#pragma unroll
-      for (int g = 0; g < 4; g++) {
-        const int c = 32 * dt + 8 * g + 4 * half;
-        const bf16x4 kv = {to_bf16(dk[dt][4 * g] * 0.125f), to_bf16(dk[dt][4 * g + 1] * 0.125f),
-                           to_bf16(dk[dt][4 * g + 2] * 0.125f), to_bf16(dk[dt][4 * g + 3] * 0.125f)};
-        const bf16x4 vv = {to_bf16(dv[dt][4 * g]), to_bf16(dv[dt][4 * g + 1]),
-                           to_bf16(dv[dt][4 * g + 2]), to_bf16(dv[dt][4 * g + 3])};
-        *(bf16x4*)(krow + c) = kv;
-        *(bf16x4*)(vrow + c) = vv;
-      }
+    for (int dt = 0; dt < 2; dt++) {
+      att_store(ktile + 32 * dt, rs, dk[dt], 0.125f, lane);
+      att_store(ktile + os + 32 * dt, rs, dv[dt], 1.f, lane);
+    }
   }
 }
 
@@ -337,15 +323,9 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attn_bwd_q_kernel(
           gq[dt] = mfma32(att_trfrag(sK, kt * 32 + 16 * m, 32 * dt, lane), sf, gq[dt]);
       }
     }
-    bf16* qrow = gbase + (size_t)q * rs;
+    bf16* qtile = gbase + (size_t)(qt * 32) * rs;
 #pragma unroll
-    for (int dt = 0; dt < 2; dt++)
-#pragma unroll
-      for (int g = 0; g < 4; g++) {
-        const bf16x4 v = {to_bf16(gq[dt][4 * g] * 0.125f), to_bf16(gq[dt][4 * g + 1] * 0.125f),
-                          to_bf16(gq[dt][4 * g + 2] * 0.125f), to_bf16(gq[dt][4 * g + 3] * 0.125f)};
-        *(bf16x4*)(qrow + 32 * dt + 8 * g + 4 * half) = v;
-      }
+    for (int dt = 0; dt < 2; dt++) att_store(qtile + 32 * dt, rs, gq[dt], 0.125f, lane);
   }
 }
 

@@ -548,7 +548,7 @@ __global__ __launch_bounds__(FT) void field_readout_kernel(const bf16x8* __restr
   bf16* sX = (bf16*)smem;
   const int lin = xcd_tile(blockIdx.x, gridDim.x);
   const int b = lin / slabs, s = lin % slabs;
-  const int lane = threadIdx.x & 63, half = lane >> 5;
+  const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform
   const int qt = wave_tile(wave);
   Slab<NT, SW> slab;
@@ -583,18 +583,10 @@ __global__ __launch_bounds__(FT) void field_readout_kernel(const bf16x8* __restr
                          cur[mm], o[dt]);
     }
   }
-  const int q = qt * 32 + (lane & 31);
-  if (q >= n) return;
   // register e of o[dt]: column 32 dt + 8 (e / 4) + 4 half + e % 4
-  bf16* yrow = y + ((size_t)b * n + q) * width + (size_t)s * SW;
+  bf16* ytile = y + ((size_t)b * n + qt * 32) * width + (size_t)s * SW;
 #pragma unroll
-  for (int dt = 0; dt < DT; dt++)
-#pragma unroll
-    for (int g = 0; g < 4; g++) {
-      const bf16x4 v = {to_bf16(o[dt][4 * g]), to_bf16(o[dt][4 * g + 1]), to_bf16(o[dt][4 * g + 2]),
-                        to_bf16(o[dt][4 * g + 3])};
-      *(bf16x4*)(yrow + 32 * dt + 8 * g + 4 * half) = v;
-    }
+  for (int dt = 0; dt < DT; dt++) att_store(ytile + 32 * dt, width, o[dt], 1.f, lane, n - qt * 32);
 }
 
 // ---------------------------------------------------------------------------
@@ -797,17 +789,9 @@ __device__ __forceinline__ void dx_block(int bid, int nblk, const bf16* __restri
                          cur[mm], o[dt]);
     }
   }
-  const int j = kt * 32 + (lane & 31);
-  if (j >= n) return;
-  bf16* xrow = dx + ((size_t)b * n + j) * width + (size_t)s * SW;
+  bf16* xtile = dx + ((size_t)b * n + kt * 32) * width + (size_t)s * SW;
 #pragma unroll
-  for (int dt = 0; dt < DT; dt++)
-#pragma unroll
-    for (int gq = 0; gq < 4; gq++) {
-      const bf16x4 v = {to_bf16(o[dt][4 * gq]), to_bf16(o[dt][4 * gq + 1]),
-                        to_bf16(o[dt][4 * gq + 2]), to_bf16(o[dt][4 * gq + 3])};
-      *(bf16x4*)(xrow + 32 * dt + 8 * gq + 4 * half) = v;
-    }
+  for (int dt = 0; dt < DT; dt++) att_store(xtile + 32 * dt, width, o[dt], 1.f, lane, n - kt * 32);
 }
 
 // ---------------------------------------------------------------------------

@@ -51,6 +51,41 @@ __device__ __forceinline__ bf16x8 att_pack(const f32x16& s, int m) {
   return v;
 }
 
+// Store of a 32 x 32 result tile whose rows are lanes (register e of lane l:
+// row l % 32, column 8 (e / 4) + 4 (l / 32) + e % 4) to `tile`, rows `stride`
+// elements apart, the first `rows` of them; 16-byte aligned.  Lanes l and l ^ 32
+// hold alternating runs of four columns of one row: a swap of two of them gives
+// each eight, and a swap with l ^ 16 brings a row's four eights to one
+// instruction, which then writes 64 bytes of each of 16 rows instead of 16 of
+// 32.  Every lane of the wave must call it.  ATT_STORE_FIGURES
+__device__ __forceinline__ void att_store(bf16* tile, size_t stride, const f32x16& o, float scale,
+                                          int lane, int rows = 32) {
+  u32x4 v[2];
+#pragma unroll
+  for (int pr = 0; pr < 2; pr++) {
+    bf16x4 a, b;
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      a[e] = to_bf16(o[8 * pr + e] * scale);
+      b[e] = to_bf16(o[8 * pr + 4 + e] * scale);
+    }
+    const uint2 ua = __builtin_bit_cast(uint2, a), ub = __builtin_bit_cast(uint2, b);
+    const auto s0 = __builtin_amdgcn_permlane32_swap(ua.x, ub.x, false, false);
+    const auto s1 = __builtin_amdgcn_permlane32_swap(ua.y, ub.y, false, false);
+    v[pr] = u32x4{s0[0], s1[0], s0[1], s1[1]};   // columns 16 pr + 8 (l / 32) .. + 8
+  }
+#pragma unroll
+  for (int k = 0; k < 4; k++) {
+    const auto s = __builtin_amdgcn_permlane16_swap(v[0][k], v[1][k], false, false);
+    v[0][k] = s[0];
+    v[1][k] = s[1];
+  }
+  const int r = lane & 15, col = (lane & 16) + 8 * (lane >> 5);
+#pragma unroll
+  for (int u = 0; u < 2; u++)
+    if (r + 16 * u < rows) *(u32x4*)(tile + (size_t)(r + 16 * u) * stride + col) = v[u];
+}
+
 // The query tiles (of 32 positions) of wave w: w and 7 - w, so that every wave
 // has the same causal work (w + 1 and 8 - w key tiles) at n = 256.
 __device__ __forceinline__ int att_tile(int wave, int which) { return which ? 7 - wave : wave; }
