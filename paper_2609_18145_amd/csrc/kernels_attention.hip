@@ -149,6 +149,15 @@ __device__ __forceinline__ float att_sum8(float v) {
   return v + att_dpp<0x141>(v);   // row_half_mirror
 }
 
+// Where the D of position i waits between the two kernels: in the window's own
+// dQ rows of this head, 32 to a row (a cache line), which attn_bwd_q_kernel reads
+// before it writes dQ.  (Reading O and dO again there, a row per thread, took a
+// fifth of that kernel's time.  A D in each row's
+// first bytes touches every line: 26.8 + 23.4 us, 25.8 + 20.2 so.)
+__device__ __forceinline__ float& att_row_sum(bf16* dq, size_t stride, int i) {
+  return ((float*)(dq + (size_t)(i >> 5) * stride))[i & 31];
+}
+
 template <int NT>
 __global__ __launch_bounds__(ATT_THREADS, 2) void attn_bwd_kv_kernel(
     const bf16* __restrict__ qkv, const bf16* __restrict__ out, const float* __restrict__ lse,
@@ -164,9 +173,7 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attn_bwd_kv_kernel(
   const bf16* dobase = dout + (size_t)b * n * os + (size_t)h * HD;
   bf16* gbase = dqkv + (size_t)b * n * rs + (size_t)h * HD;
   // Q and dO to LDS, and D = rowsum(dO * O) on the way: the 8 lanes that load a
-  // row's pieces of dO load those of O too.  D also goes to the first four
-  // bytes of the row's dQ, where attn_bwd_q_kernel finds it before it writes dQ
-  // (reading O and dO again there, a row per thread, took a fifth of its time).
+  // row's pieces of dO load those of O too.
   {
     const bf16* obase = out + (size_t)b * n * os + (size_t)h * HD;
     u32x4 vq[NT], vd[NT], vo[NT];
@@ -187,10 +194,7 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attn_bwd_kv_kernel(
 #pragma unroll
       for (int e = 0; e < 8; e++) d += (float)a[e] * (float)o[e];
       d = att_sum8(d);
-      if (p == 0) {
-        sD[r] = d;
-        *(float*)(gbase + (size_t)r * rs) = d;
-      }
+      if (p == 0) sD[r] = d;
     }
 #pragma unroll
     for (int j = 0; j < NT; j++) {
@@ -199,6 +203,7 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attn_bwd_kv_kernel(
     }
   }
   __syncthreads();
+  for (int i = threadIdx.x; i < n; i += ATT_THREADS) att_row_sum(gbase, rs, i) = sD[i];
   const float sc = 0.125f * LOG2E;
 #pragma unroll
   for (int which = 0; which < 2; which++) {
@@ -279,7 +284,7 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attn_bwd_q_kernel(
   const bf16* dobase = dout + (size_t)b * n * os + (size_t)h * HD;
   bf16* gbase = dqkv + (size_t)b * n * rs + (size_t)h * HD;
   for (int i = threadIdx.x; i < n; i += ATT_THREADS) {
-    sD[i] = *(const float*)(gbase + (size_t)i * rs);   // left there by attn_bwd_kv_kernel
+    sD[i] = att_row_sum(gbase, rs, i);   // left there by attn_bwd_kv_kernel
     sL[i] = lse[(size_t)bh * n + i] * LOG2E;
   }
   att_load_tiles<NT>(base + os, rs, sK, base + 2 * os, rs, sV);
