@@ -57,7 +57,10 @@ __device__ __forceinline__ bf16x8 att_pack(const f32x16& s, int m) {
 // hold alternating runs of four columns of one row: a swap of two of them gives
 // each eight, and a swap with l ^ 16 brings a row's four eights to one
 // instruction, which then writes 64 bytes of each of 16 rows instead of 16 of
-// 32.  Every lane of the wave must call it.  ATT_STORE_FIGURES
+// 32.  Every lane of the wave must call it.
+// us, against 8-byte stores of the registers as they are, 64 windows of 256:
+// attention forward 19.0 to 17.3 and backward 30.0 + 24.4 to 26.7 + 23.3 (8 heads),
+// field readout 12.4 to 10.1, its dx with the coordinates 19.2 to 16.9 (512 columns).
 __device__ __forceinline__ void att_store(bf16* tile, size_t stride, const f32x16& o, float scale,
                                           int lane, int rows = 32) {
   u32x4 v[2];
