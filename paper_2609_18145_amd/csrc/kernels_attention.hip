@@ -152,8 +152,8 @@ __device__ __forceinline__ float att_sum8(float v) {
 // Where the D of position i waits between the two kernels: in the window's own
 // dQ rows of this head, 32 to a row (a cache line), which attn_bwd_q_kernel reads
 // before it writes dQ.  (Reading O and dO again there, a row per thread, took a
-// fifth of that kernel's time.  A D in each row's
-// first bytes touches every line: 26.8 + 23.4 us, 25.8 + 20.2 so.)
+// fifth of that kernel's time; a D in each row's first bytes touches every line:
+// 26.8 + 23.4 us for the two kernels, 25.8 + 20.2 so.)
 __device__ __forceinline__ float& att_row_sum(bf16* dq, size_t stride, int i) {
   return ((float*)(dq + (size_t)(i >> 5) * stride))[i & 31];
 }

@@ -36,7 +36,7 @@ __device__ __attribute__((aligned(16))) bf16 g_zero16[8];
 // width, so a lane whose piece is outside takes its DMA from g_zero16 (both
 // operands are zero there: nothing the tensors hold is multiplied by padding)
 // and its outputs are not stored.  Measured at 8192 rows x 200, 8 layers,
-// forward and backward: 193 us, against 16583 us on fp32 FMAs in 64 x 64
+// forward and backward: 132 us, against 16583 us on fp32 FMAs in 64 x 64
 // tiles with one block per weight-gradient tile.
 __device__ __forceinline__ int whole_tiles(int width, int tile) {
   return (width + tile - 1) / tile;
