@@ -350,10 +350,14 @@ def _ptrs(ts):
 
 
 def _layers(layers):
-    try:
-        return array.array("i", layers).tobytes()
-    except (TypeError, OverflowError):
-        pass
+    """The schedule's codes as int32.  Only lists, tuples and ranges go to
+    array.array: it takes bytes and bytearray for raw machine words, and the
+    length of its result is then not len(layers)."""
+    if type(layers) in (list, tuple, range):
+        try:
+            return array.array("i", layers).tobytes()
+        except (TypeError, OverflowError):
+            pass
     return (ctypes.c_int32 * len(layers))(*[int(v) for v in layers])
 
 

@@ -1,5 +1,9 @@
 """The binding's native operand checks: what they hand over, and what they leave
-to the binding's own checks (by returning None)."""
+to the binding's own checks (by returning None).  And the schedule's codes as
+the library reads them, whatever sequence they come in."""
+import array
+
+import numpy as np
 import pytest
 import torch
 
@@ -20,6 +24,25 @@ def test_cpu_tensors_and_other_operands_are_left_to_the_binding():
     assert call(iter([t]), 1, (2, 3), dev="cuda:0") is None   # no list or tuple
     assert call([torch.zeros(2, 3, device="meta")], 1, (2, 3), dev="meta") is None
     assert call([], 0, (2, 3)) == b""
+
+
+@pytest.mark.parametrize("kind", [list, tuple, bytes, bytearray, np.array,
+                                  lambda v: array.array("q", v), lambda v: [np.int64(e) for e in v],
+                                  lambda v: np.array(v, dtype=np.uint8),
+                                  lambda v: [float(e) for e in v], lambda v: memoryview(bytes(v))])
+@pytest.mark.parametrize("codes", [[0, 1, 2, 3], [2, 0, 1], [5]])
+def test_layer_codes_of_any_sequence(kind, codes):
+    """One code per item, as int32: lengths that are and are not a multiple of
+    four, which is what bytes taken for machine words would go by."""
+    assert np.frombuffer(hcmix._layers(kind(codes)), dtype=np.int32).tolist() == codes
+    want = hcmix.decode_cache_bytes(4, 256, 64, codes, f32)
+    assert want > 0 and hcmix.decode_cache_bytes(4, 256, 64, kind(codes), f32) == want
+
+
+def test_layer_codes_of_a_range_and_of_the_local_layer():
+    assert np.frombuffer(hcmix._layers(range(7)), dtype=np.int32).tolist() == list(range(7))
+    codes = [hcmix.LAYER_NEAR, 3, 2 ** 40 + 1]      # the last one wraps, as in a C int
+    assert np.frombuffer(hcmix._layers(codes), dtype=np.int32).tolist() == [-1, 3, 1]
 
 
 @pytest.mark.gpu
