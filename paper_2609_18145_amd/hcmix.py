@@ -167,6 +167,13 @@ def _native():
     return _marshal
 
 
+def _addresses(ts, count, shape, dtype, dev):
+    """The tensors' addresses from the native checks, or None where those leave
+    the operands to the checks here: operands that are not on a GPU (which are
+    refused here, so whether anything is built does not matter) among them."""
+    return _native().pointers(ts, count, shape, dtype, dev) if dev.type == "cuda" else None
+
+
 def _dtype_code(t: torch.Tensor) -> int:
     if t.dtype == torch.bfloat16:
         return HCMIX_BF16
@@ -247,7 +254,7 @@ def _weights(ws, name, width, dtype, dev, count=None):
     """Checks [width, width] matrices; returns their addresses for the library."""
     if count is not None and len(ws) != count:
         raise ValueError(f"{name}: {len(ws)} matrices, expected {count}")
-    ptrs = _native().pointers(ws, len(ws), (width, width), dtype, dev)
+    ptrs = _addresses(ws, len(ws), (width, width), dtype, dev)
     if ptrs is not None:
         return ptrs
     for k, w in enumerate(ws):
@@ -365,7 +372,7 @@ def _acts(ts, name, shape, dt, dev, count):
     """Checks the first `count` tensors; returns their addresses for the library."""
     if len(ts) < count:
         raise ValueError(f"{name}: {len(ts)} tensors, expected {count}")
-    ptrs = _native().pointers(ts, count, shape, dt, dev)
+    ptrs = _addresses(ts, count, shape, dt, dev)
     if ptrs is not None:
         return ptrs
     for k in range(count):

@@ -165,3 +165,17 @@ def test_workspace_must_be_gpu_memory():
     with pytest.raises(ValueError, match="contiguous"):
         hcmix._bytes(torch.zeros(8, 8, dtype=torch.uint8).t())
     assert hcmix._bytes(None) == 0
+
+
+def test_cpu_tensors_are_refused_where_nothing_is_built(monkeypatch):
+    """The refusals need no built library: neither libhcmix.so (every test here)
+    nor the extension of the native operand checks."""
+    def boom():
+        raise RuntimeError("_marshal.so is missing")
+    monkeypatch.setattr(hcmix, "_native", boom)
+    x, w, t = z(B, N, W), z(W, W), z(N, N, dtype=f32)
+    refused(hcmix.forward, x, w, z(W, W - 1), 0, True, match="w_self/w_off")
+    refused(hcmix.forward, x, w, w, 0, True, match="GPU")
+    refused(hcmix.stack_backward, [x], [w], [w], [0], x, True, match="GPU")
+    refused(hcmix.shared_stack_forward, x, [t], [0], True, match="GPU")
+    refused(hcmix.decode_step, z(B, W), [w], [w], [0], N, 0, z(64, dtype=torch.uint8), match="GPU")
