@@ -28,6 +28,7 @@ constexpr int NT = 512;   // two groups of four waves, one k16 step of a slice e
 // tile's width + 16), and must fall 16 banks apart.
 constexpr int LDK = KC + 4;
 constexpr int LDT = BN + 4;
+constexpr int MAX_TILES_X = 1 << 22;   // row tiles along a launch's x (NT threads each)
 
 __device__ __forceinline__ f32x4 mfma4(float a, float b, const f32x4& c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
@@ -90,15 +91,18 @@ __global__ __launch_bounds__(NT) void mix_f32_kernel(
   const int wave = (tid >> 6) & 3, group = tid >> 8;
   const int l15 = lane & 15, g = lane >> 4;
   const int j0 = blockIdx.y * BN;
+  // (tiles past the rows, where the launch's z does not divide them: every
+  // row_of is -1, so they load nothing and store nothing)
+  const int row_tile = blockIdx.x + blockIdx.z * gridDim.x;
   const int s = NEAR ? 0 : 1 << d;
   const int pairs = rows / 2;
   // tile row m -> row of the tensor (-1: outside)
   auto row_of = [&](int m) {
     if constexpr (NEAR) {
-      const int r = blockIdx.x * BM + m;
+      const int r = row_tile * BM + m;
       return r < rows ? r : -1;
     }
-    const int q = blockIdx.x * (BM / 2) + (m & 31);
+    const int q = row_tile * (BM / 2) + (m & 31);
     return q < pairs ? lower_row(q, d) + (m >= 32 ? s : 0) : -1;
   };
 
@@ -349,8 +353,11 @@ bool vec16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 hipError_t launch_mix_f32(const float* A, const float* W1, const float* W2, float* out, int rows,
                           int width, int d, int partner_lower, int partner_upper, int n, int shift,
                           bool transpose_w, hipStream_t st) {
-  const dim3 grid(d < 0 ? (rows + BM - 1) / BM : (rows / 2 + BM / 2 - 1) / (BM / 2),
-                  (width + BN - 1) / BN);
+  // a launch takes fewer than 2^32 threads along x: from 2^28 rows the row
+  // tiles go over z as well
+  const int tiles = d < 0 ? (rows + BM - 1) / BM : (rows / 2 + BM / 2 - 1) / (BM / 2);
+  const int nz = (tiles + MAX_TILES_X - 1) / MAX_TILES_X;
+  const dim3 grid((tiles + nz - 1) / nz, (width + BN - 1) / BN, nz);
   // fp32 tensors need only be 4-byte aligned
   const bool vec = width % 4 == 0 && vec16(A) && vec16(W1) && vec16(W2) && vec16(out);
 #define HCMIX_MF(V, T, N)                                                                    \

@@ -216,3 +216,34 @@ def test_language_model_ends_beyond_2_31_elements():
         e = fro_rel_err(to_host(full), to_host(a) + to_host(b))
         log(f"  {name} additivity {e:.2e}")
         assert e <= 1e-5
+
+
+@pytest.mark.parametrize("batch,n,layer", [(1 << 20, 512, 3), ((1 << 20) + 1, 512, 8),
+                                           (1 << 28, 2, 0), ((1 << 21) + 5, 256, -1)])
+def test_fp32_layer_beyond_2_29_rows(batch, n, layer):
+    """Row tiles of 512 threads whose count times 512 reaches 2^32: forward and dX
+    of a one-column layer against its two products (fp32 rounds each once and
+    the sum once: 2^-22 of the two terms' sizes)."""
+    log(f"case: fp32 layer B={batch} n={n} w=1 layer={layer} ({batch * n} rows)")
+    assert batch * n >= 1 << 29
+    code = hcmix.LAYER_NEAR if layer < 0 else layer
+    g = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.randn(batch, n, 1, generator=g, device="cuda")
+    ws = torch.full((1, 1), 0.75, device="cuda")
+    wo = torch.full((1, 1), -1.25, device="cuda")
+    i = torch.arange(n, device="cuda")
+    for back in (False, True):
+        if layer < 0:      # forward: from i - 1, dX: from i + 1
+            p, takes = (i + 1, i < n - 1) if back else (i - 1, i > 0)
+        else:
+            p, takes = i ^ (1 << layer), ((i >> layer) & 1) == (0 if back else 1)
+        if back:
+            y, _ = hcmix.stack_backward_data([ws], [wo], [code], x, True)
+        else:
+            y = hcmix.forward(x, ws, wo, code, True)
+        other = x[:, p % n] * takes.to(x.dtype)[None, :, None]
+        size = x.abs().mul_(0.75).add_(other.abs(), alpha=1.25)
+        y.sub_(x, alpha=0.75).sub_(other, alpha=-1.25).abs_()
+        torch.cuda.synchronize()
+        assert bool((y <= size * 2.0 ** -22).all())
+        del y, other, size
