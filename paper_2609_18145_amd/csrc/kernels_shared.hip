@@ -390,7 +390,7 @@ __global__ __launch_bounds__(T, T / 128) void shared_bwd_kernel(SharedBwdArgs a)
       const float ai = cf[i].x;
       const float cr = sends ? cf[r].y : 0.f;
       const Piece<E> xi = unpack<E>(xo[j]);
-      xo[j] = fetch(xnext, j);     // the next layer's, once this one's is taken
+      if (l > 0) xo[j] = fetch(xnext, j);     // the next layer's, once this one's is taken
       float sd = 0.f, so = 0.f;
 #pragma unroll
       for (int v = 0; v < V; v++) {
