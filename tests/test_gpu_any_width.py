@@ -111,6 +111,70 @@ def test_stack_backward_with_whole_and_least_workspace(batch, n, width, dtype, s
             assert fro_rel_err(to_host(g) - 0.5, r) <= TOL[dtype]
 
 
+def _near(codes):
+    return [hcmix.LAYER_NEAR if v == oracle.NEAR else v for v in codes]
+
+
+@pytest.mark.parametrize("batch,n,width,layers,causal", [
+    (5, 16, 129, 24, True),       # 80 rows (a ragged slice), scalar loads, ragged second tile
+    (5, 16, 132, 24, False),      # the same by 16 bytes
+    (17, 64, 129, 13, True),      # two row ranges, the second shorter
+    (17, 64, 256, 12, False),     # whole tiles
+    (5, 16, 65, 96, True)])       # 64 x 64 tiles again, in launches of 64 and 32 layers
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_fp32_weight_gradients_on_128_tiles(batch, n, width, layers, causal, accumulate):
+    """Stacks that have 192 blocks of 128 x 128 outputs (layers x row ranges x two
+    matrices x tiles): those tiles, as against 64 x 64 below."""
+    rows, te, batched = batch * n, -(-width // 128), min(layers, 64)
+    splits = max(1, min(-(-512 // (batched * 2 * te * te)), rows // 512))
+    assert width > 64 and (batched * splits * 2 * te * te >= 192) == (layers < 96)
+    print(f"case: fp32 dW {rows}x{width} L={layers} causal={causal} splits={splits}", flush=True)
+    codes = [v % (n.bit_length() - 1) for v in range(layers)]
+    if causal:
+        codes[3] = codes[layers - 2] = oracle.NEAR
+    rng = np.random.default_rng(width)
+    xs, dys = (rng.standard_normal((layers, batch, n, width)).astype(np.float32) for _ in "xg")
+    zero = np.zeros((width, width), dtype=np.float32)
+    start = 0.5 if accumulate else 7.0
+    dws, dwo = ([torch.full((width, width), start, device="cuda") for _ in codes] for _ in "so")
+    hcmix.stack_weight_gradients([to_dev(x, "f32") for x in xs], [to_dev(g, "f32") for g in dys],
+                                 _near(codes), causal, dws=dws, dwo=dwo, accumulate=accumulate)
+    torch.cuda.synchronize()
+    for l, code in enumerate(codes):
+        _, rws, rwo = oracle.backward(xs[l], zero, zero, dys[l], code, causal)
+        for got, ref in ((dws[l], rws), (dwo[l], rwo)):
+            assert fro_rel_err(to_host(got) - (start if accumulate else 0.0), ref) <= 1e-5
+
+
+@pytest.mark.parametrize("batch,n,width,dtype,layers", [
+    (3, 32, 20, "f32", 66), (3, 32, 33, "f32", 130), (17, 64, 72, "bf16", 66)])
+def test_stack_backward_of_more_layers_than_a_launch_takes(batch, n, width, dtype, layers):
+    """Chunks of 64 layers' weight gradients, the ring of gradient buffers reused
+    from chunk to chunk: the same sums as the data chain with every gradient
+    kept, and the oracle's."""
+    print(f"case: ring {batch}x{n}x{width} {dtype} L={layers}", flush=True)
+    codes = [v % (n.bit_length() - 1) for v in range(layers)]
+    codes[2] = codes[65] = oracle.NEAR
+    s = inputs.make_stack(batch, n, width, layers, True, dtype, seed=layers, layers=codes)
+    ws, wo = ([to_dev(w, dtype) for w in m] for m in (s.w_self, s.w_off))
+    x, dy = to_dev(s.x, dtype), to_dev(s.dy, dtype)
+    xs = hcmix.stack_forward(x, ws, wo, _near(codes), True)
+    dx, dws, dwo = hcmix.stack_backward(xs, ws, wo, _near(codes), dy, True)
+    dx2, grads = hcmix.stack_backward_data(ws, wo, _near(codes), dy, True)
+    aws, awo = hcmix.stack_weight_gradients(xs[:layers], [*grads, dy], _near(codes), True)
+    torch.cuda.synchronize()
+    assert torch.equal(dx, dx2)
+    for a, b in zip(dws + dwo, aws + awo):
+        assert torch.equal(a, b)
+    # each layer's products alone, from the operands that the launch was given
+    tol = 1e-5 if dtype == "f32" else 1e-4
+    for l in (0, 1, 2, 63, 64, 65, layers - 1):
+        g = to_host(dy if l == layers - 1 else grads[l])
+        _, rws, rwo = oracle.backward(to_host(xs[l]), s.w_self[l], s.w_off[l], g, codes[l], True)
+        assert fro_rel_err(to_host(dws[l]), rws) <= tol
+        assert fro_rel_err(to_host(dwo[l]), rwo) <= tol
+
+
 @pytest.mark.parametrize("batch,width,dtype,off", [
     (17, 1, "f32", 0), (5, 33, "f32", 0), (16, 64, "f32", 0), (3, 64, "f32", 1), (18, 272, "f32", 0),
     (17, 40, "bf16", 0), (3, 264, "bf16", 0)])

@@ -128,3 +128,19 @@ def test_workload_shape_every_output_repeat_and_accumulate():
     for a, b, c in zip(dts, dts2, acc):
         assert torch.equal(a, b)
         assert torch.equal(c, a + 1.0)
+
+
+@pytest.mark.parametrize("layers_n", [17, 33])
+@pytest.mark.parametrize("n", [16, 256])
+@pytest.mark.parametrize("dtype,width", [("bf16", 64), ("f32", 32)])
+@pytest.mark.parametrize("causal", [False, True])
+def test_stack_deeper_than_the_coefficients_in_lds(layers_n, n, dtype, width, causal):
+    """Stacks whose coefficients are read into LDS in groups of 16 layers: one
+    layer into the second and into the third group, local layers among them."""
+    layers = list(range(layers_n))
+    if causal:
+        layers[7] = layers[16] = oracle.NEAR
+    log(f"case: shared stack n={n} L={layers_n} causal={causal} {dtype}")
+    s = inputs.make_shared_stack(2, n, width, layers_n, causal, dtype, seed=layers_n + n,
+                                 layers=layers)
+    run_and_check(s)

@@ -23,7 +23,32 @@ def _need_gpu():
 # (batch, n, width): small, mid and big blocks of both kinds of width
 SHAPES = [(3, 2, 64), (35, 2, 448), (3, 256, 512), (33, 64, 512), (63, 64, 512), (129, 64, 512),
           (33, 128, 192), (65, 256, 192), (1, 1024, 1024), (5, 512, 1024), (9, 1024, 1024),
-          (33, 64, 200), (130, 64, 328)]
+          (33, 64, 200), (130, 64, 328), (128, 64, 200), (512, 64, 136)]
+
+
+def tile(rows, width, transposed):
+    """The block shape of a hypercube layer's product (rows / 2 pairs; the local
+    layer's counts are the same), and whether the width is ragged in it."""
+    pairs, wide = rows // 2, -(-width // 64) % 2 == 0
+    big = 256 if not transposed and width % 256 == 0 and width >= 1024 else 128 if wide else 64
+
+    def blocks(p, c):
+        return -(-pairs // p) * -(-width // c)
+
+    if blocks(32, 64 if transposed else 32) <= (256 if transposed else 512):
+        kind = "small"
+    else:
+        mid, large = (-(-b // 256) for b in (blocks(64, 64), blocks(128, big)))
+        kind = "mid" if mid * 4 <= large * {256: 14, 128: 7, 64: 5}[big] else f"big{big}"
+    return kind, width % 64 != 0
+
+
+def test_the_shapes_reach_every_block():
+    got = {(*tile(b * n, w, t), t) for b, n, w in SHAPES for t in (False, True)}
+    for ragged in (False, True):
+        for kind in ("small", "mid", "big64", "big128"):
+            assert (kind, ragged, False) in got and (kind, ragged, True) in got, (kind, ragged)
+    assert ("big256", False, False) in got
 
 
 @pytest.mark.parametrize("batch,n,width", SHAPES)
