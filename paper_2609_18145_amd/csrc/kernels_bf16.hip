@@ -1243,7 +1243,10 @@ hipError_t launch_gemm_bf16(const bf16* A, const bf16* B, bf16* out, int rows, i
   // 128 (one block per CU), as given | transposed: 16384 x 512 -> 512 12.9 | 12.8
   // to 11.9 | 12.9, 8192 x 512 -> 1536 21.1 | 22.9 to 18.0 | 19.3, 16384 x 256 ->
   // 512 8.7 | 10.1 to 8.3 | 7.9, 16384 x 512 -> 1536 37.2 | 29.4 to 37.2 | 29.0.
-  if (wide) return HCMIX_GEMM(64, 128, 2, 4, 1, MIX_BK, MIX_NS);
+  // (A launch takes fewer than 2^32 threads along x: outputs of 2^37 elements
+  // and more go to the last block shape, which has half as many.)
+  const int64_t blocks = (int64_t)((rows + 127) / 128) * (N / 128);
+  if (wide && blocks < ((int64_t)1 << 32) / 512) return HCMIX_GEMM(64, 128, 2, 4, 1, MIX_BK, MIX_NS);
   return HCMIX_GEMM(MIX_BMP, 64, 4, 1, 1, MIX_BK, MIX_NS);
 #undef HCMIX_GEMM
 }
