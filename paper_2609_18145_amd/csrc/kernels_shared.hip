@@ -543,6 +543,18 @@ static hipError_t shared_launch(K k, int threads, const A& a, int blocks, size_t
   }
 
 hipError_t launch_shared_forward(const SharedFwdArgs& a, int batch, int elem_bytes, hipStream_t st) {
+  // A launch takes fewer than 2^32 threads along x, up to 512 of them a block:
+  // more windows than that take a launch more (128 GiB per tensor and above).
+  const int most = ((1 << 23) - 1) / shared_blocks(1, a.width, elem_bytes);
+  if (batch > most) {
+    const hipError_t first = launch_shared_forward(a, most, elem_bytes, st);
+    if (first != hipSuccess) return first;
+    const size_t skip = (size_t)most * a.n * a.width * elem_bytes;
+    SharedFwdArgs rest = a;
+    rest.x0 = (const char*)a.x0 + skip;
+    for (int l = 0; l < a.num_layers; l++) rest.xs[l] = (char*)a.xs[l] + skip;
+    return launch_shared_forward(rest, batch - most, elem_bytes, st);
+  }
   const int blocks = shared_blocks(batch, a.width, elem_bytes);
   hipError_t e;
   if (elem_bytes == 2) HCMIX_SHARED_CASES(shared_fwd_kernel, bf16, 512, 512, a, blocks)

@@ -99,3 +99,21 @@ def test_linear_map(launches, rows, n_in, n_out):
                   i64(rows, n_out, n_in) + [mem(0), mem(1), mem(2), mem(3), NONE] + i32(0)
                   + [NONE, ["size_t", 0], NONE])
     assert len(ls) == 1 and ls[0][0][0] == x
+
+
+@pytest.mark.parametrize("batch,width,dtype", [((1 << 23) - 1, 64, 1), (1 << 23, 64, 1),
+                                               (1 << 23, 32, 0), (933054, 576, 1),
+                                               (1 << 22, 128, 1)])
+def test_channel_shared_forward(launches, batch, width, dtype):
+    """Windows of 128 positions, 128 GiB per tensor: launches that start where the
+    one before ended and cover every window and slice of channels."""
+    n, es, slices = 128, 2 if dtype else 4, width // (64 if dtype else 32)
+    ls = launches("hcmix_shared_stack_forward",
+                  i64(batch, n, width) + i32(1) + [["codes", [0]]] + i32(1, dtype)
+                  + [mem(0), ["ptrs", [mem(1)[1]]], ["ptrs", [mem(2)[1]]], NONE])
+    assert (len(ls) == 1) == (batch * slices * 512 < 1 << 32)
+    done = 0
+    for (x, _, _), _, x0 in ls:
+        assert x % slices == 0 and x0 == mem(0)[1] + done * n * width * es
+        done += x // slices
+    assert done == batch
