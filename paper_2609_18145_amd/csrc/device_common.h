@@ -18,6 +18,16 @@ __device__ __forceinline__ int xcd_tile(int bid, int total) {
   return (bid % 8) * (total / 8) + bid / 8;
 }
 
+// This wave's index in a block of NW waves (a power of two): wave-uniform, and
+// known to lie in 0 .. NW - 1.  Without the mask the compiler knows no sign,
+// and every division of what is computed from it takes a correction: a third
+// of the mix blocks' set-up (0.3 us a round of blocks).
+template <int NW>
+__device__ __forceinline__ int wave_index() {
+  static_assert((NW & (NW - 1)) == 0, "");
+  return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & (NW - 1);
+}
+
 __device__ __forceinline__ f32x16 mfma32(const bf16x8& a, const bf16x8& b, const f32x16& c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }

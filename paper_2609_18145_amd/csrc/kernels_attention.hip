@@ -62,7 +62,7 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attn_fwd_kernel(
   __shared__ __attribute__((aligned(1024))) bf16 sK[n * HD], sV[n * HD];
   const int bh = blockIdx.x, b = bh / heads, h = bh % heads;
   const int lane = threadIdx.x & 63, half = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave = wave_index<ATT_THREADS / 64>();
   const size_t rs = (size_t)3 * heads * HD;                 // qkv row stride
   const bf16* base = qkv + (size_t)b * n * rs + (size_t)h * HD;
   att_load_tiles<NT>(base + (size_t)heads * HD, rs, sK, base + (size_t)2 * heads * HD, rs, sV);
@@ -167,7 +167,7 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attn_bwd_kv_kernel(
   __shared__ __attribute__((aligned(16))) float sL[n], sD[n];
   const int bh = blockIdx.x, b = bh / heads, h = bh % heads;
   const int lane = threadIdx.x & 63, half = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave = wave_index<ATT_THREADS / 64>();
   const size_t rs = (size_t)3 * heads * HD, os = (size_t)heads * HD;
   const bf16* base = qkv + (size_t)b * n * rs + (size_t)h * HD;
   const bf16* dobase = dout + (size_t)b * n * os + (size_t)h * HD;
@@ -278,7 +278,7 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attn_bwd_q_kernel(
   __shared__ __attribute__((aligned(16))) float sL[n], sD[n];
   const int bh = blockIdx.x, b = bh / heads, h = bh % heads;
   const int lane = threadIdx.x & 63, half = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave = wave_index<ATT_THREADS / 64>();
   const size_t rs = (size_t)3 * heads * HD, os = (size_t)heads * HD;
   const bf16* base = qkv + (size_t)b * n * rs + (size_t)h * HD;
   const bf16* dobase = dout + (size_t)b * n * os + (size_t)h * HD;

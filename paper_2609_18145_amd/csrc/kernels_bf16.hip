@@ -98,7 +98,7 @@ __device__ __forceinline__ void mix_bf16_block(
   constexpr int DPS = C::DPS;
 
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = wave_index<C::NW>();
   const int wm = wave % WM, wn = wave / WM % WN, wk = wave / (WM * WN);
   const int s = 1 << d;
   const int tiles_n = RAG ? whole_tiles(N, BN) : N / BN;
@@ -418,7 +418,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void shift_bf16_kernel(
   extern __shared__ __attribute__((aligned(1024))) bf16 smem[];
 
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = wave_index<C::NW>();
   const int wm = wave % WM, wn = wave / WM % WN, wk = wave / (WM * WN);
   const int tiles_n = RAG ? whole_tiles(width, BN) : width / BN;
   const int tiles_m = (rows + BM - 1) / BM;
@@ -693,7 +693,7 @@ __device__ __forceinline__ void dw_bf16_block(
   constexpr int RBG = BO * 2, RBX = BC * 2;
 
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_all = wave_index<C::NW * C::NG>();
   const int group = wave_all / C::NW, wave = wave_all % C::NW;
   bf16* smem = smem_all + group * 2 * C::STAGE;
   const int wo = wave % WO, wc = wave / WO;

@@ -469,7 +469,7 @@ __global__ __launch_bounds__(BO * 2) void head_dw_kernel(const bf16* __restrict_
   const int v0 = tv * BO, k0 = tk * BC;
   const int r0 = sp * range, r1 = min(rows, r0 + range);
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave = wave_index<NW>();
   const int wm = wave % WO, wn = wave / WO;
   const int nsteps = r1 > r0 ? (r1 - r0 + HB_KS - 1) / HB_KS : 0;
 

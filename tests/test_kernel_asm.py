@@ -193,3 +193,29 @@ def test_write_through_stores_never_take_mfma_results(tmp_path):
     bad = [(os.path.basename(src), k, line, why) for src, asm in zip(srcs, asms)
            for k, line, why in wt_store_hazards(asm)]
     assert not bad, f"write-through stores with unsafe data: {bad[:5]}"
+
+
+def _kernels(src: str, name: str, out_dir: str) -> dict:
+    """symbol -> assembly of the kernels of csrc/<src> whose symbol holds `name`."""
+    asm = _device_asm(os.path.join(pkg_build.PKG, "csrc", src), out_dir)
+    out = {}
+    for m in re.finditer(r"^(_Z\S+):", asm, re.M):
+        if name in m.group(1) and "_kernel" in m.group(1):
+            out[m.group(1)] = asm[m.end():asm.index(".Lfunc_end", m.end())]
+    return out
+
+
+@pytest.mark.skipif(not os.path.exists(pkg_build.HIPCC) and shutil.which("hipcc") is None,
+                    reason="hipcc not available")
+@pytest.mark.parametrize("src,name", [("kernels_bf16.hip", "mix_bf16_kernel"),
+                                      ("kernels_bf16.hip", "shift_bf16_kernel"),
+                                      ("kernels_attention.hip", "attn_")])
+def test_set_up_has_no_signed_divisions(tmp_path, src, name):
+    """Every index of these kernels is a division or remainder by a constant of
+    what is known not to be negative (wave_index); one whose sign is unknown
+    takes a correction, which begins with the sign bit spread over a register."""
+    kernels = _kernels(src, name, str(tmp_path))
+    assert len(kernels) > 10
+    bad = {k: n for k, b in kernels.items()
+           if (n := len(re.findall(r"v_ashrrev_i32_e32 v\d+, 31, ", b)))}
+    assert not bad, bad
