@@ -12,21 +12,22 @@
 // top (exchanging partners, barriers, waiting for its coefficients) has to
 // stay out of the stream's way.
 //
-// Thread mapping (256 threads): thread tid owns memory piece k = tid % 8 of
-// the positions tid / 8 + 32 j.  A wave covers 8 consecutive positions, and
+// Thread mapping: thread tid of T (256 or 512) owns memory piece k = tid % 8 of
+// the positions tid / 8 + (T / 8) j.  A wave covers 8 consecutive positions, and
 // its global accesses are 128 contiguous bytes per position.  So the partner
 // along dimension d is
 //   d = 0, 1, 2: in another lane of the wave (lane ^ 8, 16, 32: lane moves);
-//   d = 3, 4 (and the local layer's neighbour): in another wave (through LDS);
-//   d = 5, 6, 7: in another register of the same thread.
-// Only the middle case needs LDS and barriers.  The coefficients of up to 16
-// layers are read ahead into LDS at once: read layer by layer, each layer
-// waited for them (a gather of one line per position).
+//   d = 3, 4 (5 too with 512 threads) and the local layer's neighbour: in
+//     another wave (through LDS);
+//   the dimensions above: in another register of the same thread.
+// Only the middle case needs LDS and barriers.  The coefficients are read ahead
+// into LDS for many layers at once (shared_ring): read layer by layer, each
+// layer waited for them (a gather of one line per position).
 // Measured at 64 windows x 256 x 512 bf16, 16 layers, us per launch: forward
 // 57.4 (62.6 with the tile in LDS), backward 82.9 (94.0); 285 and 306 MB at a
-// device copy's 5.2 TB/s are 55 and 59.  The forward takes 512 threads (four
-// positions each, dimension 5 through LDS too: 57 against 65 us), the backward
-// 256, whose gradients and prefetched inputs do not fit 128 registers.
+// device copy's 5.2 TB/s are 55 and 59.  The forward takes 512 threads from n =
+// 128 (two or four positions each: 57 against 65 us), the backward 256, whose
+// gradients and prefetched inputs do not fit 128 registers.
 #include "device_common.h"
 #include "hcmix_internal.h"
 
@@ -38,7 +39,6 @@ namespace {
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int SH_THREADS = 256;
 constexpr int SH_PIECES = 8;   // 16-byte pieces of a row that one block owns
 
 // 16 bytes of E as floats.
@@ -119,12 +119,12 @@ __device__ __forceinline__ float sum8(float v) {
 }
 
 // (A_l[i], B_l[i]) of every position of layers l0 .. l0 + count - 1 (at most
-// SH_COEF) into coef[l % SH_COEF][i], U layers' loads in flight: all of them
-// before the tile is loaded, few once it fills the registers.
-constexpr int SH_COEF = 16;
+// `ring`, a power of two) into coef[l % ring][i], U layers' loads in flight.
+// Four ahead of the first layer: with sixteen a stack of one layer read its
+// lines sixteen times over (64 x 256 x 512 fp32, forward: 19.1 us, now 10.3).
 template <int U>
 __device__ __forceinline__ void load_coefs(const float* const* tabs, const int* dims, int l0,
-                                           int count, int n, int bidir, float2* coef) {
+                                           int count, int ring, int n, int bidir, float2* coef) {
   const int i = threadIdx.x;
   if (i >= n) return;
 #pragma unroll 1
@@ -132,7 +132,9 @@ __device__ __forceinline__ void load_coefs(const float* const* tabs, const int* 
     float ca[U], cb[U];
 #pragma unroll
     for (int u = 0; u < U; u++) {
-      const int l = l0 + min(u0 + u, count - 1);
+      ca[u] = cb[u] = 0.f;
+      if (u0 + u >= count) continue;    // uniform
+      const int l = l0 + u0 + u;
       bool takes;
       const int p = fwd_partner(i, dims[l], bidir, &takes);
       const float* row = tabs[l] + (size_t)i * n;
@@ -141,7 +143,7 @@ __device__ __forceinline__ void load_coefs(const float* const* tabs, const int* 
     }
 #pragma unroll
     for (int u = 0; u < U; u++)
-      if (u0 + u < count) coef[((l0 + u0 + u) % SH_COEF) * n + i] = make_float2(ca[u], cb[u]);
+      if (u0 + u < count) coef[((l0 + u0 + u) & (ring - 1)) * n + i] = make_float2(ca[u], cb[u]);
   }
 }
 
@@ -197,15 +199,15 @@ __device__ __forceinline__ float lane_partner(float x) {
   }
 }
 
-// Rows exchanged through LDS at a time: four positions per thread (128 rows,
-// 32 KB of bf16 slices), and one row beyond them for the local layer.
+// Rows exchanged through LDS at a time (32 KB of bf16 slices; four positions
+// per thread of 256, two of 512), and one row beyond them for the local layer.
 constexpr int SH_ROWS = 128;
 template <typename E>
 constexpr size_t shared_exchange_bytes(int n) {
   return (size_t)((n < SH_ROWS ? n : SH_ROWS) + 1) * SH_PIECES * Slice<E>::V * 4;
 }
 
-// Calls f(j, p) once for every position i0 + 32 j of this thread, p being the
+// Calls f(j, p) once for every position i0 + PJ j of this thread, p being the
 // row of its partner as it was before any of these calls (f may change s[j]):
 // XOR 2^d for d >= 0, i + near for the local layer (near = -1 or 1; the row
 // itself where that leaves the window).  `tile` is the LDS exchange buffer;
@@ -243,7 +245,7 @@ __device__ __forceinline__ void for_partners(const Piece<E> (&s)[NJ], int d, int
   HCMIX_LANES(2)
 #undef HCMIX_LANES
 #undef HCMIX_REGS
-  // through LDS, SH_XJ positions per thread at a time; the local layer takes
+  // through LDS, G positions per thread at a time; the local layer takes
   // the group first whose outer neighbour belongs to the other
   constexpr int G = NJ < SH_ROWS / PJ ? NJ : SH_ROWS / PJ;
   const int rows = min(n, PJ * G);
@@ -281,7 +283,7 @@ __device__ __forceinline__ void for_partners(const Piece<E> (&s)[NJ], int d, int
 }
 
 template <typename E, int NJ, int T>
-__global__ __launch_bounds__(T, T / 128) void shared_fwd_kernel(SharedFwdArgs a) {
+__global__ __launch_bounds__(T, T / 128) void shared_fwd_kernel(SharedFwdArgs a, int ring) {
   using S = Slice<E>;
   constexpr int V = S::V, PJ = T / SH_PIECES;
   const int n = a.n, width = a.width;
@@ -290,7 +292,7 @@ __global__ __launch_bounds__(T, T / 128) void shared_fwd_kernel(SharedFwdArgs a)
   const int c0 = (blockIdx.x % chunks) * SH_PIECES * V;
   extern __shared__ __align__(16) unsigned char smem[];
   f32x4* tile = (f32x4*)smem;
-  float2* coef = (float2*)(smem + shared_exchange_bytes<E>(n));   // [SH_COEF][n]
+  float2* coef = (float2*)(smem + shared_exchange_bytes<E>(n));   // [ring][n]
   const int k = threadIdx.x % SH_PIECES;
   const int i0 = threadIdx.x / SH_PIECES;
   const bool mine = i0 < n;
@@ -302,19 +304,23 @@ __global__ __launch_bounds__(T, T / 128) void shared_fwd_kernel(SharedFwdArgs a)
 #pragma unroll
   for (int j = 0; j < NJ; j++)
     first[j] = mine ? *(const u32x4*)(x0 + at0 + j * step) : u32x4{0u, 0u, 0u, 0u};
-  load_coefs<SH_COEF>(a.tab, a.dim, 0, min(SH_COEF, a.num_layers), n, a.bidir, coef);
+  load_coefs<4>(a.tab, a.dim, 0, min(ring, a.num_layers), ring, n, a.bidir, coef);
   __syncthreads();
   Piece<E> x[NJ];
 #pragma unroll
   for (int j = 0; j < NJ; j++) x[j] = unpack<E>(first[j]);
+  // The tile is there from here on.  The compiler counts no store_wt16 and
+  // would wait for the loads where the loop first uses them, and with them for
+  // the stores of the layer before, in every layer.
+  __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
 
   for (int l = 0; l < a.num_layers; l++) {
-    if (l > 0 && l % SH_COEF == 0) {
+    if (l > 0 && (l & (ring - 1)) == 0) {
       __syncthreads();
-      load_coefs<2>(a.tab, a.dim, l, min(SH_COEF, a.num_layers - l), n, a.bidir, coef);
+      load_coefs<8>(a.tab, a.dim, l, min(ring, a.num_layers - l), ring, n, a.bidir, coef);
       __syncthreads();
     }
-    const float2* cf = coef + (l % SH_COEF) * n;
+    const float2* cf = coef + (l & (ring - 1)) * n;
     const int d = a.dim[l];
     E* out = (E*)a.xs[l];
     for_partners<E, NJ, PJ>(x, d, -1, n, i0, k, tile, [&](int j, const Piece<E>& p) {
@@ -331,8 +337,9 @@ __global__ __launch_bounds__(T, T / 128) void shared_fwd_kernel(SharedFwdArgs a)
   }
 }
 
-template <typename E, int NJ, int T>
-__global__ __launch_bounds__(T, T / 128) void shared_bwd_kernel(SharedBwdArgs a) {
+// NT: dy and the inputs are read non-temporally (shared_bwd_streams).
+template <typename E, int NJ, int T, bool NT>
+__global__ __launch_bounds__(T, T / 128) void shared_bwd_kernel(SharedBwdArgs a, int ring) {
   using S = Slice<E>;
   constexpr int V = S::V, PJ = T / SH_PIECES;
   const int n = a.n, width = a.width;
@@ -356,15 +363,18 @@ __global__ __launch_bounds__(T, T / 128) void shared_bwd_kernel(SharedBwdArgs a)
   // holds x[i] and needs g[r] for dX anyway.
   Piece<E> g[NJ];
   u32x4 xo[NJ];
-  auto fetch = [&](const E* src, int j) {   // read once: 84.5 -> 82.9 us as non-temporal
-    return mine ? __builtin_nontemporal_load((const u32x4*)(src + at0 + j * step))
-                : u32x4{0u, 0u, 0u, 0u};
+  auto fetch = [&](const E* src, int j) {
+    const u32x4 none = {0u, 0u, 0u, 0u};
+    if constexpr (NT)
+      return mine ? __builtin_nontemporal_load((const u32x4*)(src + at0 + j * step)) : none;
+    else
+      return mine ? *(const u32x4*)(src + at0 + j * step) : none;
   };
 #pragma unroll
   for (int j = 0; j < NJ; j++) xo[j] = fetch(dy, j);
   {
-    const int lo = (L - 1) / SH_COEF * SH_COEF;
-    load_coefs<SH_COEF>(a.tab, a.dim, lo, L - lo, n, a.bidir, coef);
+    const int lo = (L - 1) & -ring;
+    load_coefs<4>(a.tab, a.dim, lo, L - lo, ring, n, a.bidir, coef);
     __syncthreads();
   }
 #pragma unroll
@@ -373,13 +383,14 @@ __global__ __launch_bounds__(T, T / 128) void shared_bwd_kernel(SharedBwdArgs a)
   for (int j = 0; j < NJ; j++) xo[j] = fetch((const E*)a.xs[L - 1], j);
 
   for (int l = L - 1; l >= 0; l--) {
-    if (l < L - 1 && l % SH_COEF == SH_COEF - 1) {
+    if (l < L - 1 && (l & (ring - 1)) == ring - 1) {
       __syncthreads();
-      load_coefs<2>(a.tab, a.dim, l - (SH_COEF - 1), SH_COEF, n, a.bidir, coef);
+      // few at a time where the tile fills the registers
+      load_coefs<NJ == 8 ? 2 : 8>(a.tab, a.dim, l - (ring - 1), ring, ring, n, a.bidir, coef);
       __syncthreads();
     }
     const E* xnext = (const E*)a.xs[l > 0 ? l - 1 : 0];
-    const float2* cf = coef + (l % SH_COEF) * n;
+    const float2* cf = coef + (l & (ring - 1)) * n;
     const int d = a.dim[l];
     float keep_d = 0.f, keep_o = 0.f;
     for_partners<E, NJ, PJ>(g, d, 1, n, i0, k, tile, [&](int j, const Piece<E>& p) {
@@ -500,11 +511,17 @@ bool shared_stack_eligible(int64_t n, int64_t width, int32_t num_layers, int32_t
          num_layers <= kSharedMaxLayers;
 }
 
-// The exchange buffer and 16 layers' coefficients: 66 KB at n = 256, two
-// blocks per CU.
+// Layers whose coefficients are in LDS at a time: as many as the stack has, in
+// 32 KB (bf16) or 16 KB (fp32, whose exchange buffer is half as large: four
+// blocks per CU then, where 32 KB left three for the four of 64 x 256 x 512, a
+// round and a third: 17 layers forward 132 us, now 125).
+constexpr int SH_MAX_LDS = (int)shared_exchange_bytes<bf16>(kSharedMaxN) + (32 << 10);
 template <typename E>
-static size_t shared_lds_bytes(int n) {
-  return shared_exchange_bytes<E>(n) + (size_t)SH_COEF * n * sizeof(float2);
+static int shared_ring(int n, int num_layers) {
+  constexpr int room = (sizeof(E) == 4 ? 16 : 32) << 10;
+  int ring = 1;
+  while (ring < num_layers && 2 * ring * n * (int)sizeof(float2) <= room) ring *= 2;
+  return ring;
 }
 
 static int shared_blocks(int batch, int width, int elem_bytes) {
@@ -517,30 +534,44 @@ size_t shared_partial_bytes(int64_t batch, int64_t n, int64_t width, int32_t num
          sizeof(float);
 }
 
+// The saved inputs do not fit the 256 MB Infinity Cache, so most of what the
+// forward left there is gone when the backward comes to it: better read past
+// the cache.  Backward after forward, us, non-temporal against ordinary loads:
+// 64 x 256 x 512 bf16, 16 layers (268 MB) 96.6 | 101, 12 layers (201 MB) 70.9 |
+// 68.7; fp32, 10 layers 104 | 140, 4 layers 52 | 47 (and the forward 43 | 30).
+static bool shared_bwd_streams(const SharedBwdArgs& a, int batch, int elem_bytes) {
+  return (size_t)a.num_layers * batch * a.n * a.width * elem_bytes >= (size_t)256 << 20;
+}
+
 template <typename K, typename A>
-static hipError_t shared_launch(K k, int threads, const A& a, int blocks, size_t lds,
+static hipError_t shared_launch(K k, int threads, const A& a, int ring, int blocks, size_t lds,
                                 std::atomic<unsigned long long>& lds_set, hipStream_t st) {
-  const hipError_t attr = lds_limit_once(lds_set, (const void*)k, (int)lds);
+  // the limit is set once per kernel: the most that any n and depth asks for
+  const hipError_t attr = lds_limit_once(lds_set, (const void*)k, SH_MAX_LDS);
   if (attr != hipSuccess) return attr;
-  k<<<blocks, threads, lds, st>>>(a);
+  k<<<blocks, threads, lds, st>>>(a, ring);
   return hipGetLastError();
 }
 
-// Threads and positions per thread (NJ) by n.
+// Threads and positions per thread (NJ) by n; KERNEL(E, NJ, T) names the instance.
 #define HCMIX_SHARED_CASES(KERNEL, E, T128, T256, ARGS, BLOCKS)                                   \
   {                                                                                               \
     static std::atomic<unsigned long long> lds_set[4];                                            \
-    const size_t lds = shared_lds_bytes<E>(a.n);                                                  \
+    const int ring = shared_ring<E>(a.n, a.num_layers);                                           \
+    const size_t lds = shared_exchange_bytes<E>(a.n) + (size_t)ring * a.n * sizeof(float2);       \
+    auto go = [&](auto k, int threads, int c) {                                                   \
+      return shared_launch(k, threads, ARGS, ring, BLOCKS, lds, lds_set[c], st);                  \
+    };                                                                                            \
     switch (a.n <= 32 ? 1 : a.n / 32) {                                                           \
-      case 1: e = shared_launch(KERNEL<E, 1, 256>, 256, ARGS, BLOCKS, lds, lds_set[0], st); break; \
-      case 2: e = shared_launch(KERNEL<E, 2, 256>, 256, ARGS, BLOCKS, lds, lds_set[1], st); break; \
-      case 4:                                                                                     \
-        e = shared_launch(KERNEL<E, 1024 / T128, T128>, T128, ARGS, BLOCKS, lds, lds_set[2], st); \
-        break;                                                                                    \
-      default:                                                                                    \
-        e = shared_launch(KERNEL<E, 2048 / T256, T256>, T256, ARGS, BLOCKS, lds, lds_set[3], st); \
+      case 1: e = go(KERNEL(E, 1, 256), 256, 0); break;                                           \
+      case 2: e = go(KERNEL(E, 2, 256), 256, 1); break;                                           \
+      case 4: e = go(KERNEL(E, 1024 / T128, T128), T128, 2); break;                               \
+      default: e = go(KERNEL(E, 2048 / T256, T256), T256, 3);                                     \
     }                                                                                             \
   }
+#define HCMIX_SHARED_FWD(E, NJ, T) shared_fwd_kernel<E, NJ, T>
+#define HCMIX_SHARED_BWD(E, NJ, T) shared_bwd_kernel<E, NJ, T, false>
+#define HCMIX_SHARED_BWD_NT(E, NJ, T) shared_bwd_kernel<E, NJ, T, true>
 
 hipError_t launch_shared_forward(const SharedFwdArgs& a, int batch, int elem_bytes, hipStream_t st) {
   // A launch takes fewer than 2^32 threads along x, up to 512 of them a block:
@@ -557,8 +588,8 @@ hipError_t launch_shared_forward(const SharedFwdArgs& a, int batch, int elem_byt
   }
   const int blocks = shared_blocks(batch, a.width, elem_bytes);
   hipError_t e;
-  if (elem_bytes == 2) HCMIX_SHARED_CASES(shared_fwd_kernel, bf16, 512, 512, a, blocks)
-  else HCMIX_SHARED_CASES(shared_fwd_kernel, float, 512, 512, a, blocks)
+  if (elem_bytes == 2) HCMIX_SHARED_CASES(HCMIX_SHARED_FWD, bf16, 512, 512, a, blocks)
+  else HCMIX_SHARED_CASES(HCMIX_SHARED_FWD, float, 512, 512, a, blocks)
   return e;
 }
 
@@ -566,8 +597,13 @@ hipError_t launch_shared_backward(const SharedBwdArgs& a, const SharedReduceArgs
                                   int elem_bytes, hipStream_t st) {
   const int blocks = shared_blocks(batch, a.width, elem_bytes);
   hipError_t e;
-  if (elem_bytes == 2) HCMIX_SHARED_CASES(shared_bwd_kernel, bf16, 256, 256, a, blocks)
-  else HCMIX_SHARED_CASES(shared_bwd_kernel, float, 256, 256, a, blocks)
+  if (shared_bwd_streams(a, batch, elem_bytes)) {
+    if (elem_bytes == 2) HCMIX_SHARED_CASES(HCMIX_SHARED_BWD_NT, bf16, 256, 256, a, blocks)
+    else HCMIX_SHARED_CASES(HCMIX_SHARED_BWD_NT, float, 256, 256, a, blocks)
+  } else {
+    if (elem_bytes == 2) HCMIX_SHARED_CASES(HCMIX_SHARED_BWD, bf16, 256, 256, a, blocks)
+    else HCMIX_SHARED_CASES(HCMIX_SHARED_BWD, float, 256, 256, a, blocks)
+  }
   if (e != hipSuccess) return e;
   SharedReduceArgs rr = r;
   rr.blocks = blocks;
@@ -575,6 +611,9 @@ hipError_t launch_shared_backward(const SharedBwdArgs& a, const SharedReduceArgs
   shared_dt_reduce_kernel<<<a.num_layers * groups, SH_RED_THREADS, 0, st>>>(rr);
   return hipGetLastError();
 }
+#undef HCMIX_SHARED_BWD_NT
+#undef HCMIX_SHARED_BWD
+#undef HCMIX_SHARED_FWD
 #undef HCMIX_SHARED_CASES
 
 }  // namespace hcmix

@@ -131,12 +131,13 @@ def test_workload_shape_every_output_repeat_and_accumulate():
 
 
 @pytest.mark.parametrize("layers_n", [17, 33])
-@pytest.mark.parametrize("n", [16, 256])
+@pytest.mark.parametrize("n", [16, 128, 256])
 @pytest.mark.parametrize("dtype,width", [("bf16", 64), ("f32", 32)])
 @pytest.mark.parametrize("causal", [False, True])
 def test_stack_deeper_than_the_coefficients_in_lds(layers_n, n, dtype, width, causal):
-    """Stacks whose coefficients are read into LDS in groups of 16 layers: one
-    layer into the second and into the third group, local layers among them."""
+    """Coefficients are in LDS for 16 layers at a time at n = 256 (fp32: 8), 32 (16)
+    at 128 and all 64 at 16: one layer into a further group, or several, local
+    layers among them."""
     layers = list(range(layers_n))
     if causal:
         layers[7] = layers[16] = oracle.NEAR
@@ -144,3 +145,33 @@ def test_stack_deeper_than_the_coefficients_in_lds(layers_n, n, dtype, width, ca
     s = inputs.make_shared_stack(2, n, width, layers_n, causal, dtype, seed=layers_n + n,
                                  layers=layers)
     run_and_check(s)
+
+
+@pytest.mark.parametrize("n", [16, 64, 128, 256])
+@pytest.mark.parametrize("dtype,width", [("bf16", 128), ("f32", 64)])
+def test_backward_of_inputs_past_the_cache_equals_its_halves(n, dtype, width):
+    """From 256 MiB of saved inputs on the backward reads them past the cache: the
+    same windows in two halves take the other kernel, and every dX is the same;
+    the table gradients are sums of the halves' (2^-20 of the terms)."""
+    L, batch = 8, 131072 // n
+    log(f"case: shared backward of {batch} windows n={n} w={width} {dtype} L={L}")
+    g = torch.Generator(device="cuda").manual_seed(n)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    x, dy = (torch.randn(batch, n, width, generator=g, device="cuda").to(dt) for _ in "xy")
+    assert L * x.numel() * x.element_size() >= 1 << 28 > L * x.numel() * x.element_size() // 2
+    tabs = [torch.randn(n, n, generator=g, device="cuda") * 0.7 for _ in range(L)]
+    codes = list(range(L - 1)) + [oracle.NEAR]
+    xs = hcmix.shared_stack_forward(x, tabs, codes, True)
+    dx, dts = hcmix.shared_stack_backward(xs[:-1], tabs, codes, dy, True)
+    half = batch // 2
+    sums = [torch.zeros_like(t) for t in dts]
+    for part in (slice(0, half), slice(half, batch)):
+        xp = [t[part] for t in xs]
+        dxp, dtp = hcmix.shared_stack_backward(xp[:-1], tabs, codes, dy[part], True)
+        torch.cuda.synchronize()
+        assert torch.equal(dx[part], dxp)
+        for a, b in zip(sums, dtp):
+            a += b
+    for l, (a, b) in enumerate(zip(dts, sums)):
+        terms = (xs[l].float().square().mean() * batch * width).sqrt() * (batch * width) ** 0.5
+        assert (a - b).abs().max() <= 2.0 ** -20 * terms, l

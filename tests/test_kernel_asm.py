@@ -219,3 +219,16 @@ def test_set_up_has_no_signed_divisions(tmp_path, src, name):
     bad = {k: n for k, b in kernels.items()
            if (n := len(re.findall(r"v_ashrrev_i32_e32 v\d+, 31, ", b)))}
     assert not bad, bad
+
+
+@pytest.mark.skipif(not os.path.exists(pkg_build.HIPCC) and shutil.which("hipcc") is None,
+                    reason="hipcc not available")
+def test_channel_shared_forward_does_not_wait_for_its_stores(tmp_path):
+    """The layer loop stores without the compiler's knowledge (store_wt16): a wait
+    for loads inside it would be one for every store before it, layer by layer.
+    After the first store only the kernel's end waits, and needs no instruction."""
+    kernels = _kernels("kernels_shared.hip", "shared_fwd_kernel", str(tmp_path))
+    assert len(kernels) == 8
+    for k, b in kernels.items():
+        first = b.index("off sc1")
+        assert not re.findall(r"s_waitcnt.*vmcnt", b[first:]), k
