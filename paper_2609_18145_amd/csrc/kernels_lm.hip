@@ -146,7 +146,14 @@ __global__ __launch_bounds__(LM_THREADS) void embed_bwd_reduce_kernel(
 #pragma unroll
     for (int u = 0; u < 8; u++) s += v[u];
   }
-  for (; c < chunks; c++) s += p[(size_t)c * cs];
+  // the last few in flight together as well (one by one: 0.3 us each)
+  f32x4 v[7];
+#pragma unroll
+  for (int u = 0; u < 7; u++)
+    if (c + u < chunks) v[u] = p[(size_t)(c + u) * cs];
+#pragma unroll
+  for (int u = 0; u < 7; u++)
+    if (c + u < chunks) s += v[u];
   float* d = dtable + i4 * 4;
 #pragma unroll
   for (int e = 0; e < 4; e++) d[e] = accumulate ? d[e] + s[e] : s[e];
@@ -387,13 +394,13 @@ constexpr int HB_TILE = 128;
 constexpr int HB_KS = 64;
 constexpr int HB_TARGET_BLOCKS = 256;
 
-// Weight gradient dl^T x: BO x 128 output tiles (BO = 256 vocabulary entries, or
-// 128 up to a vocabulary of 128), HD_NS stages of 64 rows in LDS by DMA, eight
-// (four) waves of 64 x 64.  A step moves 48 KB into the CU and reads 128 KB of
-// fragments from LDS (transposed) for 4.2 Mflop, and takes about 1.4 us: 0.9 us
-// the DMA alone, 1.2 us the fragment reads and MFMAs alone, 0.5 us the MFMAs.
-// The rows are split into ranges to fill the chip, whose fp32 partials cost
-// memory traffic in turn; see head_dw_split.
+// Weight gradient dl^T x: BO x 128 output tiles (BO = 256 or 128 vocabulary
+// entries, see head_dw_plan), HD_NS stages of 64 rows in LDS by DMA, eight
+// (four) waves of 64 x 64.  With BO = 256 a step moves 48 KB into the CU and
+// reads 128 KB of fragments from LDS (transposed) for 4.2 Mflop, and takes about
+// 1.4 us: 0.9 us the DMA alone, 1.2 us the fragment reads and MFMAs alone, 0.5
+// us the MFMAs.  The rows are split into ranges to fill the chip, whose fp32
+// partials cost memory traffic in turn.
 // Measured at 16384 rows without the sum of the ranges (5-7 us): 512 x 1536
 // 42.3 us, 512 x 512 19.8, 512 x 256 16.1, against 57, 25 and 17.5 with 128 x
 // 128 tiles staged through registers.  128 x 64 or 256 x 256 tiles per wave or
@@ -401,26 +408,48 @@ constexpr int HB_TARGET_BLOCKS = 256;
 // 46 to 50, 22 to 23 and 19 to 20.
 constexpr int HD_NS = 3;
 
-int head_dw_tile(int vocab) { return vocab > 128 ? 256 : 128; }
+// Tile and row ranges of the weight gradient: BO of the output tile, `range` rows
+// each (a multiple of HB_KS), `splits` of them.  A round of blocks takes 1.5 us
+// and 0.8 (BO = 128) or 0.9 us per step of 64 rows; a range's partials, vocab *
+// width floats, are written and read at 5 TB/s, and its place in the sum takes
+// 0.03 us; blocks that cannot be dealt evenly to the 8 XCDs read rows again,
+// 0.5 us.  The least of the sum over both tiles, in one round if it can be.
+// (These rates pick, of 500 measured plans of 2 to 32768 rows, 64 x 64 to 512 x
+// 1536, one that is 0.6% from the fastest on average.)  Few rows or small
+// outputs want the small tile, whose ranges fill the chip with half the
+// partials: us, 256 | 128: 512 rows 512 -> 160 9.9 | 8.2, 8192 rows 512 -> 512
+// 22.8 | 21.1, but 512 -> 1536 32.9 | 41.
+struct HeadDwPlan { int tile, range, splits; };
 
-// Row ranges of the weight gradient: `range` rows each (a multiple of HB_KS).
-// With s ranges a block walks steps / s steps of 0.85 us (the DMA's time; with
-// the whole step's 1.4 us the sum below moves by less than the runs differ),
-// and the partials' s * vocab * width floats are written and read at about
-// 5 TB/s: the sum is least at the root of the ratio, as long as the blocks fit
-// the chip.
-void head_dw_split(int rows, int width, int vocab, int* range, int* splits) {
-  const int bo = head_dw_tile(vocab);
-  const int tiles = ((vocab + bo - 1) / bo) * ((width + HB_TILE - 1) / HB_TILE);
+HeadDwPlan head_dw_plan(int rows, int width, int vocab) {
   const int steps = (rows + HB_KS - 1) / HB_KS;
-  const double part_us = (double)vocab * width * 8 / 5e6;
-  int s = (int)(sqrt(steps * 0.85 / part_us) + 0.5);
-  if (s > HB_TARGET_BLOCKS / tiles) s = HB_TARGET_BLOCKS / tiles;
-  if (s > steps) s = steps;
-  if (s < 1) s = 1;
-  const int per = (steps + s - 1) / s;                 // steps per range
-  *range = per * HB_KS;
-  *splits = (rows + *range - 1) / *range;
+  const double part_us = (double)vocab * width * 8 / 5e6 + 0.03;
+  HeadDwPlan best = {};
+  double best_us = 0;
+  for (int bo = 128; bo <= (vocab > 128 ? 256 : 128); bo *= 2) {
+    const double step_us = bo == 128 ? 0.8 : 0.9;
+    const int64_t tiles = (int64_t)((vocab + bo - 1) / bo) * ((width + HB_TILE - 1) / HB_TILE);
+    int most = tiles < HB_TARGET_BLOCKS ? HB_TARGET_BLOCKS / (int)tiles : 1;
+    if (most > steps) most = steps;
+    const int least_per = (steps + most - 1) / most;          // steps per range
+    // the sum is least here, but for rounding: half to twice of it is tried
+    int at = (int)sqrt(steps * part_us / step_us);
+    if (at < least_per) at = least_per;
+    if (at > steps) at = steps;
+    for (int per = at / 2 > least_per ? at / 2 : least_per; per <= 2 * at && per <= steps;
+         per += 1 + at / 16) {
+      const int splits = (steps + per - 1) / per;
+      const int64_t blocks = tiles * splits;
+      const int64_t rounds = (blocks + HB_TARGET_BLOCKS - 1) / HB_TARGET_BLOCKS;
+      const double us = rounds * (1.5 + per * step_us) + splits * part_us +
+                        (blocks > 8 && blocks % 8 ? 0.5 : 0.0);
+      if (!best.splits || us < best_us) {
+        best = {bo, per * HB_KS, splits};
+        best_us = us;
+      }
+    }
+  }
+  return best;
 }
 
 // The least partials a call may come with: one per range of the plan that
@@ -715,9 +744,8 @@ size_t head_backward_least_workspace_bytes(int rows, int width, int vocab) {
 }
 
 size_t head_backward_workspace_bytes(int rows, int width, int vocab) {
-  int range, splits;
-  head_dw_split(rows, width, vocab, &range, &splits);
-  const size_t best = (size_t)splits * vocab * width * sizeof(float);
+  const size_t best =
+      (size_t)head_dw_plan(rows, width, vocab).splits * vocab * width * sizeof(float);
   const size_t least = head_backward_least_workspace_bytes(rows, width, vocab);
   return best > least ? best : least;
 }
@@ -751,8 +779,7 @@ hipError_t launch_head_backward(const bf16* x, const bf16* w, const bf16* dl, bf
     if (e != hipSuccess) return e;
   }
   if (!dw) return hipSuccess;
-  int range, splits;
-  head_dw_split(rows, width, vocab, &range, &splits);
+  auto [tile, range, splits] = head_dw_plan(rows, width, vocab);
   const size_t room = workspace_bytes / ((size_t)vocab * width * sizeof(float));
   if ((size_t)splits > room) {   // a workspace of the least size: longer ranges
     const int steps = (rows + HB_KS - 1) / HB_KS;
@@ -760,7 +787,7 @@ hipError_t launch_head_backward(const bf16* x, const bf16* w, const bf16* dl, bf
     splits = (rows + range - 1) / range;
   }
   const hipError_t e =
-      head_dw_tile(vocab) == 256
+      tile == 256
           ? head_dw_launch<256>(dl, x, workspace, rows, width, vocab, range, splits, st)
           : head_dw_launch<128>(dl, x, workspace, rows, width, vocab, range, splits, st);
   if (e != hipSuccess) return e;

@@ -117,3 +117,24 @@ def test_channel_shared_forward(launches, batch, width, dtype):
         assert x % slices == 0 and x0 == mem(0)[1] + done * n * width * es
         done += x // slices
     assert done == batch
+
+
+@pytest.mark.parametrize("rows,n_in,n_out,tile", [
+    (2, 64, 64, 128), (512, 512, 512, 128), (8192, 256, 512, 128), (8192, 512, 512, 128),
+    (2048, 512, 1536, 128), (8192, 512, 1536, 256), (32768, 512, 512, 256),
+    (16384, 8192, 8192, 256), (1 << 20, 64, 64, 128)])
+def test_weight_gradient_plan(launches, rows, n_in, n_out, tile):
+    """The tile that was measured to be the faster, ranges that fit the workspace
+    that the query answers, one round of blocks unless the tiles alone are more."""
+    from paper_2609_18145_amd import hcmix
+    nbytes = hcmix.load().hcmix_linear_backward_workspace_bytes(rows, n_in, n_out)
+    ls = launches("hcmix_linear_backward",
+                  i64(rows, n_in, n_out) + [mem(0), mem(1), mem(2), NONE, mem(3)] + i32(0)
+                  + [mem(4), ["size_t", nbytes], NONE])
+    (blocks, _, _), (threads, _, _), _ = ls[0]
+    assert len(ls) == 2 and threads == 2 * tile           # the gradient, the sum of the ranges
+    tiles = -(-n_out // tile) * -(-n_in // 128)
+    assert blocks % tiles == 0
+    splits = blocks // tiles
+    assert blocks <= max(256, tiles) and splits <= -(-rows // 64)
+    assert splits * n_in * n_out * 4 <= nbytes
