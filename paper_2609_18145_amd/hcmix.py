@@ -1,8 +1,10 @@
-"""Python binding of libhcmix.so (ctypes; argument marshalling only).
+"""Python binding of libhcmix.so (ctypes; argument marshalling only, the checks
+of tensor lists in the extension _marshal.so, built beside it against the
+installed PyTorch).
 
 Every step of the layer runs in the HIP library; PyTorch supplies device
-memory and the current stream.  If the library is not built this module
-raises on first use: there is no CPU or PyTorch fallback.
+memory and the current stream.  If either is not built this module raises on
+the first call with GPU tensors: there is no CPU or PyTorch fallback.
 
     y = forward(x, w_self, w_off, layer, causal)
     dx, dws, dwo = backward(x, w_self, w_off, dy, layer, causal)
@@ -171,7 +173,9 @@ def _addresses(ts, count, shape, dtype, dev):
     """The tensors' addresses from the native checks, or None where those leave
     the operands to the checks here: operands that are not on a GPU (which are
     refused here, so whether anything is built does not matter) among them."""
-    return _native().pointers(ts, count, shape, dtype, dev) if dev.type == "cuda" else None
+    if _marshal is None and dev.type != "cuda":
+        return None
+    return (_marshal or _native()).pointers(ts, count, shape, dtype, dev)
 
 
 def _dtype_code(t: torch.Tensor) -> int:
@@ -236,6 +240,8 @@ def _bytes(t):
 
 
 def _stream(x):
+    """The current stream of x's GPU: torch.cuda.current_stream(x.device).cuda_stream
+    without a Stream object for every call."""
     return torch._C._cuda_getCurrentRawStream(x.device.index)
 
 
@@ -402,6 +408,11 @@ def stack_forward(x, w_selfs, w_offs, layers, causal, outs=None):
 
 
 def stack_workspace_bytes(batch, n, width, num_layers, dtype) -> int:
+    """Bytes of the workspace that ``stack_backward`` allocates where the caller
+    gives none.  fp32, and bf16 widths that are no multiple of 64: the gradients
+    of as many layers as 1 GiB holds (two at least) and the partial sums; the
+    backward also takes a smaller one, down to two gradients, and is slower on
+    it, with the weight gradients summed in another order."""
     code = HCMIX_BF16 if dtype == torch.bfloat16 else HCMIX_F32
     return load().hcmix_stack_backward_workspace_bytes(batch, n, width, num_layers, code)
 

@@ -172,6 +172,7 @@ def test_cpu_tensors_are_refused_where_nothing_is_built(monkeypatch):
     nor the extension of the native operand checks."""
     def boom():
         raise RuntimeError("_marshal.so is missing")
+    monkeypatch.setattr(hcmix, "_marshal", None)
     monkeypatch.setattr(hcmix, "_native", boom)
     x, w, t = z(B, N, W), z(W, W), z(N, N, dtype=f32)
     refused(hcmix.forward, x, w, z(W, W - 1), 0, True, match="w_self/w_off")
