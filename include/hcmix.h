@@ -185,8 +185,10 @@ hcmix_status hcmix_stack_forward(int64_t batch, int64_t n, int64_t width, int32_
  *  - fused path: the per-window weight-gradient partials;
  *  - fp32, and bf16 widths that are not a multiple of 64: the intermediate
  *    gradients of as many layers as 1 GiB holds (at least two buffers) and the
- *    row-range partials of those layers' weight gradients.  The backward also
- *    runs, slower, on two gradient buffers alone (none for one layer);
+ *    row-range partials of those layers' weight gradients.  A workspace that
+ *    ends before that is taken down to two gradient buffers (none for one
+ *    layer): then slower, one layer's weight gradients at a time over all rows,
+ *    whose sums are taken in another order;
  *  - otherwise, layer by layer: two gradient buffers, the split-K partials of
  *    one layer and (two or more layers) the transposed weights. */
 size_t hcmix_stack_backward_workspace_bytes(int64_t batch, int64_t n, int64_t width,
@@ -222,10 +224,11 @@ hcmix_status hcmix_stack_backward(int64_t batch, int64_t n, int64_t width, int32
  * per 64 layers whose blocks each own a 128 x 128 tile of both matrices over
  * every row (or, when layers x tiles cannot fill the chip, over a row range,
  * plus a fixed-order sum of the ranges); fp32 and widths that are not a
- * multiple of 64: the same scheme, running without the workspace too (no row
- * ranges then); other shapes: the per-layer kernels of hcmix_backward.  Bitwise-repeatable.  The workspace (256-byte aligned,
+ * multiple of 64: the same scheme, and without the whole workspace the same
+ * launch with every block over all rows; other shapes: the per-layer kernels
+ * of hcmix_backward.  Bitwise-repeatable.  The workspace (256-byte aligned,
  * hcmix_stack_weight_gradients_workspace_bytes, possibly 0) holds those
- * partial sums. */
+ * partial sums; bf16 with a width that is a multiple of 64 needs all of it. */
 size_t hcmix_stack_weight_gradients_workspace_bytes(int64_t batch, int64_t n, int64_t width,
                                                      int32_t num_layers, int32_t dtype);
 

@@ -3,14 +3,13 @@
 // below 32 bits), for any width, alignment and row count.
 //
 // What bounds it: the matrix cores, which do 256 flop per clock and CU in fp32
-// (a 8192^3 library product reaches 154 TFLOP/s), four times what one FMA per
-// lane and clock would give a kernel that also has to read its operands from
-// LDS.  The tiles are 64 x 64 with 32-wide contraction slices: 16 flop per
-// byte moved into the CU, 16 B/clk at full matrix rate, which L2 serves; two
-// slices sit in LDS and the next one travels through registers meanwhile.
-// Measured at 4096 rows x 256, 8 layers, forward and backward: 255 us (76
-// TFLOP/s), against 6998 us with 4 x 4 FMAs per thread and a launch of one
-// block per weight-gradient tile for every layer.
+// (a 8192^3 library product reaches 154 TFLOP/s), twice what one FMA per lane
+// and clock gives.  The tiles are 64 x 64 with 32-wide contraction slices: 16
+// flop per byte moved into the CU, 16 B/clk at full matrix rate, which L2
+// serves; two slices sit in LDS and the next one travels through registers
+// meanwhile.  Measured at 4096 rows x 256, 8 layers, forward and backward: 255
+// us (76 TFLOP/s), against 6998 us with 4 x 4 FMAs per thread and a launch of
+// one block per weight-gradient tile for every layer.
 #include "hcmix_internal.h"
 
 namespace hcmix {

@@ -1,6 +1,6 @@
 """bf16 widths that are a multiple of 8 but not of 64 (the boundary accepts
-any multiple of 8; the MFMA tiles need 64, so these run on the fp32 FMA
-kernels with bf16 storage): the local layer, whole stacks (rotated and mixa
+any multiple of 8; the MFMA tiles are 64 wide, so these run on instances that
+pad them with zeros): the local layer, whole stacks (rotated and mixa
 schedules, causal and bidirectional), the backward's data chain and weight
 gradients on their own, the decode step and the no-allocation backward,
 against the oracle or bitwise against the entry point they must equal.  The

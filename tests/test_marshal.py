@@ -46,6 +46,17 @@ def test_layer_codes_of_a_range_and_of_the_local_layer():
 
 
 @pytest.mark.gpu
+def test_the_stream_is_the_current_one():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    x = torch.zeros(1, device="cuda:0")
+    side = torch.cuda.Stream()
+    assert hcmix._stream(x) == torch.cuda.current_stream(x.device).cuda_stream
+    with torch.cuda.stream(side):
+        assert hcmix._stream(x) == side.cuda_stream != 0
+
+
+@pytest.mark.gpu
 def test_addresses_of_matching_tensors_only():
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
